@@ -831,9 +831,7 @@ void fill_pair_tables(const kc_pair* pairs, uint32_t n_pairs, const std::vector<
 int run_compare(kc_ctx* c, const CmpPairDev* dpairs, const CmpTileDev* dtiles, const std::vector<uint64_t>& tile_off,
                 uint32_t n_pairs, uint32_t tile_bytes, unsigned long long* dacc, uint64_t acc_words, bool* acc_dirty,
                 kc_cmp_result* res_d, hipStream_t s) {
-  // built-in shape: 2 workgroups per CU, 4 when there are few tiles to share (a persistent grid reads the c4 pairs
-  // 4 % faster than one workgroup per tile)
-  const uint32_t grid = grid_for(c, KC_OP_COMPARE, tile_off[n_pairs] < 16ull * c->n_cu ? 4 : 2);
+  const uint32_t grid = grid_for(c, KC_OP_COMPARE, kCompareGridPerCu);
   if (*acc_dirty) KC_HIP(launch_fill_u64(reinterpret_cast<uint64_t*>(dacc), acc_words, 0, s));
   *acc_dirty = true;
   {

@@ -109,7 +109,7 @@ int kc_compare_noalloc(kc_ctx* c, const kc_pair* pairs, uint32_t n_pairs, kc_cmp
       a.tile_end[j] = (uint32_t)t;
     }
     a.n_tiles = (uint32_t)t;
-    const uint32_t grid = grid_for(c, KC_OP_COMPARE, t < 16ull * c->n_cu ? 4 : 2);
+    const uint32_t grid = grid_for(c, KC_OP_COMPARE, kCompareGridPerCu);
     KC_HIP(launch_compare_args(a, tile_bytes, acc + (uint64_t)b0 * kAccWords, res_d + b0, grid, s));
   }
   return KC_OK;
