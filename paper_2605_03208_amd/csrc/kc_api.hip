@@ -761,17 +761,26 @@ uint32_t elem_size(uint32_t dtype) {
   }
 }
 
-// Tuned tile size, else 64 KiB halved (down to 16 KiB) while the pairs would
+// Tuned tile size, else 64 KiB, halved (down to 16 KiB) while the pairs would
 // give fewer than eight tiles per compute unit: small batches still spread
-// over the whole chip.
+// over the whole chip.  The smallest batches keep 64 KiB (kCompareWideTile).
 uint32_t compare_tile_bytes(const kc_ctx* c, const kc_pair* pairs, uint32_t n_pairs) {
   if (c->tune[KC_OP_COMPARE].tile_bytes) return c->tune[KC_OP_COMPARE].tile_bytes;
-  uint64_t total = 0;
-  for (uint32_t i = 0; i < n_pairs; ++i)
-    if (pairs[i].dtype <= KC_I64 && pairs[i].n_elems <= (1ull << 60)) total += pairs[i].n_elems * elem_size(pairs[i].dtype);
+  uint64_t total = 0, wide_tiles = 0;
+  for (uint32_t i = 0; i < n_pairs; ++i) {
+    if (pairs[i].dtype > KC_I64 || pairs[i].n_elems > (1ull << 60)) continue;  // refused later
+    const uint64_t nb = pairs[i].n_elems * elem_size(pairs[i].dtype);
+    total += nb;
+    wide_tiles += nb == 0 ? 1 : (nb + kCompareWideTile - 1) / kCompareWideTile;
+  }
+  if (compare_wide(c, wide_tiles, kCompareWideTile)) return kCompareWideTile;
   uint32_t tb = 64u << 10;
   while (tb > (16u << 10) && total / tb < 8ull * c->n_cu) tb >>= 1;
   return tb;
+}
+
+bool compare_wide(const kc_ctx* c, uint64_t n_tiles, uint32_t tile_bytes) {
+  return n_tiles <= c->n_cu && tile_bytes >= kCompareWideTile;
 }
 
 }  // namespace kc
@@ -824,7 +833,8 @@ void fill_pair_tables(const kc_pair* pairs, uint32_t n_pairs, const std::vector<
 }
 
 // Run the pass (one launch, or one per pair), write the reports.  The
-// accumulators are zero on entry and the finalize kernel zeroes them again.
+// accumulators are zero on entry and the finalize kernel zeroes them again; if
+// every pair is one tile, the pass writes the reports and uses none of them.
 // A call that failed between the pass and the finalize leaves *acc_dirty set;
 // the next call clears the whole accumulator area first (fill kernel, so the
 // call stays capturable).
@@ -832,19 +842,21 @@ int run_compare(kc_ctx* c, const CmpPairDev* dpairs, const CmpTileDev* dtiles, c
                 uint32_t n_pairs, uint32_t tile_bytes, unsigned long long* dacc, uint64_t acc_words, bool* acc_dirty,
                 kc_cmp_result* res_d, hipStream_t s) {
   const uint32_t grid = grid_for(c, KC_OP_COMPARE, kCompareGridPerCu);
+  const bool direct = tile_off[n_pairs] == n_pairs;  // every pair one tile
   if (*acc_dirty) KC_HIP(launch_fill_u64(reinterpret_cast<uint64_t*>(dacc), acc_words, 0, s));
   *acc_dirty = true;
   {
     KernelTimer timer(c, KC_OP_COMPARE, s);
     if (!c->tune[KC_OP_COMPARE].per_item) {
-      KC_HIP(launch_compare(dpairs, dtiles, (uint32_t)tile_off[n_pairs], tile_bytes, dacc, grid, s));
+      KC_HIP(launch_compare(dpairs, dtiles, (uint32_t)tile_off[n_pairs], tile_bytes, dacc, res_d, grid,
+                            compare_wide(c, tile_off[n_pairs], tile_bytes), direct, s));
     } else {
       for (uint32_t i = 0; i < n_pairs; ++i)
         KC_HIP(launch_compare(dpairs, dtiles + tile_off[i], (uint32_t)(tile_off[i + 1] - tile_off[i]), tile_bytes,
-                              dacc, grid, s));
+                              dacc, res_d, grid, false, direct, s));
     }
   }
-  KC_HIP(launch_compare_finalize(dpairs, n_pairs, dacc, res_d, s));
+  if (!direct) KC_HIP(launch_compare_finalize(dpairs, n_pairs, dacc, res_d, s));
   *acc_dirty = false;
   return KC_OK;
 }

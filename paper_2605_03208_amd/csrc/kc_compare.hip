@@ -25,15 +25,17 @@
 //
 // A workgroup's totals of a pair go to per-pair accumulators with integer
 // atomics (max of non-negative doubles via their bit patterns, first mismatch
-// via max of its complement), nothing if its elements were all equal.  A
-// second small kernel writes each pair's report once the pass has finished.
+// via max of its complement), nothing if its elements were all equal, and a
+// second small kernel writes the reports once the pass has finished.  When every
+// pair is one tile neither is needed: its workgroup writes the report, and the
+// call is one launch (16 pairs of 64 KiB: see kCompareWideTile).
 #include "kc_device.h"
 #include "kc_internal.h"
 
 namespace kc {
 namespace {
 
-constexpr uint32_t kThreads = 256;
+constexpr uint32_t kThreads = 256, kWideThreads = 1024;
 constexpr uint32_t kUnroll = 4;
 constexpr uint32_t kBins = 48;
 
@@ -135,7 +137,6 @@ template <> struct Fmt<KC_I64> : IntFmt<8, uint64_t> {};
 template <> struct Fmt<KC_U8> {
   using B = uint32_t;
   static constexpr uint32_t size = 1, kind = 2;
-  static constexpr B mag = 0xFFu;
   __device__ static bool nan(B) { return false; }
   __device__ static bool inf(B) { return false; }
   __device__ static double value(B) { return 0.0; }
@@ -177,6 +178,7 @@ struct TileLds {
   unsigned long long max_abs, max_rel;  // bits of non-negative doubles
   unsigned long long first;             // lowest differing element
   uint32_t cnt[8];                      // kCntMis .. kCntNotClose below
+  uint32_t bins[kBins];                 // the histogram's totals, once a pair is done
 };
 enum : uint32_t { kCntMis = 0, kCntBytes, kCntNanBoth, kCntNanCand, kCntNanGold, kCntOver, kCntNotClose };
 
@@ -311,13 +313,12 @@ template <uint32_t ES> struct Mask { typedef uint32_t T; };
 template <> struct Mask<1> { typedef uint64_t T; };
 
 // The bytes [b0, b1) of a pair.  stage: kUnroll runs of each side per thread.
-template <uint32_t DT>
+template <uint32_t DT, uint32_t T>
 __device__ __forceinline__ void tile_body(const CmpPairDev& pr, uint64_t b0, uint64_t b1, Partial& p, TileLds& lds,
                                           uint4* stage) {
   using B = typename Fmt<DT>::B;
   constexpr uint32_t es = Fmt<DT>::size;
   constexpr uint32_t epv = 16u / es;  // elements per run
-  constexpr uint32_t T = kThreads;
   const uint32_t tid = threadIdx.x;
   const uint32_t nvec = (uint32_t)((b1 - b0) / 16u), per_round = T * kUnroll;
   const Tol tol{pr.tol, pr.atol, pr.rtol};
@@ -452,42 +453,88 @@ __device__ __forceinline__ void clear_tile_lds(TileLds& lds) {
   }
 }
 
-// The state of a workgroup that starts on a pair: nothing found, and the
-// pair's maxima so far as thresholds below which nothing needs to be recorded
-// (they only grow).  lds is clear.
-__device__ __forceinline__ Partial begin_pair(const unsigned long long* acc) {
-  return Partial{0, 0, 0, 0, false, bits_dbl(acc[kAccMaxAbs]), bits_dbl(acc[kAccMaxRel]), 0.0};
-}
-
 // The bytes [b0, b1) of a pair, added to what the workgroup has found of it.
 // No barrier: its waves share only counters.
+template <uint32_t T>
 __device__ __forceinline__ void compare_bytes(const CmpPairDev& pr, uint64_t b0, uint64_t b1, Partial& p, TileLds& lds,
                                               uint4* stage) {
   switch (pr.dtype) {
-    case KC_F32: tile_body<KC_F32>(pr, b0, b1, p, lds, stage); break;
-    case KC_BF16: tile_body<KC_BF16>(pr, b0, b1, p, lds, stage); break;
-    case KC_F16: tile_body<KC_F16>(pr, b0, b1, p, lds, stage); break;
-    case KC_FP8_E4M3FN: tile_body<KC_FP8_E4M3FN>(pr, b0, b1, p, lds, stage); break;
-    case KC_F64: tile_body<KC_F64>(pr, b0, b1, p, lds, stage); break;
-    case KC_FP8_E4M3FNUZ: tile_body<KC_FP8_E4M3FNUZ>(pr, b0, b1, p, lds, stage); break;
-    case KC_FP8_E5M2: tile_body<KC_FP8_E5M2>(pr, b0, b1, p, lds, stage); break;
-    case KC_FP8_E5M2FNUZ: tile_body<KC_FP8_E5M2FNUZ>(pr, b0, b1, p, lds, stage); break;
-    case KC_I8: tile_body<KC_I8>(pr, b0, b1, p, lds, stage); break;
-    case KC_I16: tile_body<KC_I16>(pr, b0, b1, p, lds, stage); break;
-    case KC_I32: tile_body<KC_I32>(pr, b0, b1, p, lds, stage); break;
-    case KC_I64: tile_body<KC_I64>(pr, b0, b1, p, lds, stage); break;
-    default: tile_body<KC_U8>(pr, b0, b1, p, lds, stage); break;
+    case KC_F32: tile_body<KC_F32, T>(pr, b0, b1, p, lds, stage); break;
+    case KC_BF16: tile_body<KC_BF16, T>(pr, b0, b1, p, lds, stage); break;
+    case KC_F16: tile_body<KC_F16, T>(pr, b0, b1, p, lds, stage); break;
+    case KC_FP8_E4M3FN: tile_body<KC_FP8_E4M3FN, T>(pr, b0, b1, p, lds, stage); break;
+    case KC_F64: tile_body<KC_F64, T>(pr, b0, b1, p, lds, stage); break;
+    case KC_FP8_E4M3FNUZ: tile_body<KC_FP8_E4M3FNUZ, T>(pr, b0, b1, p, lds, stage); break;
+    case KC_FP8_E5M2: tile_body<KC_FP8_E5M2, T>(pr, b0, b1, p, lds, stage); break;
+    case KC_FP8_E5M2FNUZ: tile_body<KC_FP8_E5M2FNUZ, T>(pr, b0, b1, p, lds, stage); break;
+    case KC_I8: tile_body<KC_I8, T>(pr, b0, b1, p, lds, stage); break;
+    case KC_I16: tile_body<KC_I16, T>(pr, b0, b1, p, lds, stage); break;
+    case KC_I32: tile_body<KC_I32, T>(pr, b0, b1, p, lds, stage); break;
+    case KC_I64: tile_body<KC_I64, T>(pr, b0, b1, p, lds, stage); break;
+    default: tile_body<KC_U8, T>(pr, b0, b1, p, lds, stage); break;
   }
 }
 
-// What the workgroup found of a pair goes to the pair's accumulators (nothing
-// if every element was equal).  Once per run of tiles of one pair, not per
-// tile: the atomics of all workgroups on one pair meet at the same addresses
-// and cost about 0.1 us each there (a 250 MiB pair with one element in 10,000
-// off, flushed per 64 KiB tile: 0.70 ms for a 0.31 ms pass).  Leaves lds clear.
-__device__ __forceinline__ void end_pair(const Partial& p, unsigned long long* acc, TileLds& lds) {
+// Word w of a report (61 of 8 bytes, one per lane) comes from this word of the
+// pair's accumulators; -1: from none of them.
+__device__ __forceinline__ int acc_of_word(uint32_t w) {
+  if (w >= 10u && w < 10u + kBins) return (int)(w - 10u + kAccHist);
+  switch (w) {
+    case 1: return kAccMisElems;
+    case 2: return kAccMisBytes;
+    case 3: return kAccFirstInv;
+    case 4: return kAccNanBoth;
+    case 5: return kAccNanCand;
+    case 6: return kAccNanGold;
+    case 7: return kAccOverTol;
+    case 8: return kAccMaxAbs;
+    case 9: return kAccMaxRel;
+    case 59: return kAccNotClose;
+    default: return -1;
+  }
+}
+static_assert(sizeof(kc_cmp_result) == 61 * 8, "report layout");
+
+// One wave writes a pair's report; x: the accumulator word acc_of_word(lane).
+__device__ __forceinline__ void write_report(uint64_t n_elems, uint32_t dtype, uint64_t x, kc_cmp_result* r) {
+  const uint32_t lane = threadIdx.x % kWave;
+  const uint64_t rest = wave_sum_u64(lane > 10u && lane < 10u + kBins ? x : 0ull);  // counted at a distance above 0
+  const uint64_t mis = __shfl(x, 1, 64), nb = __shfl(x, 4, 64), nc = __shfl(x, 5, 64), ng = __shfl(x, 6, 64);
+  const uint64_t over = __shfl(x, 7, 64), not_close = __shfl(x, 59, 64);
+  const bool raw = dtype == KC_U8, no_nan = (nc | ng) == 0ull;
+  if (lane == 0u) x = n_elems;
+  if (lane == 3u) x = ~x;  // the accumulator holds the complement
+  if (lane == 10u) x = raw ? 0ull : n_elems - nb - nc - ng - rest;
+  if (lane == 58u) x = (raw ? mis == 0ull : over == 0ull && no_nan) ? 1u : 0u;  // pass, and status 0 above it
+  if (lane == 60u) x = (raw ? mis == 0ull : not_close == 0ull && no_nan) ? 1u : 0u;
+  if (lane < 61u) reinterpret_cast<uint64_t*>(r)[lane] = x;
+}
+
+// The accumulator words of a pair as the workgroup found them (totals summed).
+__device__ __forceinline__ uint64_t found_word(const TileLds& lds, int i) {
+  if (i < 0) return 0ull;
+  if (i >= (int)kAccHist) return lds.bins[i - (int)kAccHist];
+  if (i == kAccMaxAbs) return lds.max_abs;
+  if (i == kAccMaxRel) return lds.max_rel;
+  if (i == kAccFirstInv) return ~lds.first;
+  return lds.cnt[i == kAccNotClose ? kCntNotClose : i];
+}
+
+// Ends a workgroup's work on a pair; leaves lds clear.  DIRECT: it was the
+// whole pair, and the workgroup writes the report.  Else what it found goes to
+// the pair's accumulators (nothing if every element was equal): once per run of
+// tiles of one pair, not per tile, since the atomics of all workgroups on one
+// pair meet at the same addresses and cost about 0.1 us each there (a 250 MiB
+// pair with one element in 10,000 off, flushed per 64 KiB tile: 0.70 ms for a
+// 0.31 ms pass).
+template <bool DIRECT>
+__device__ __forceinline__ void end_pair(const CmpPairDev& pr, const Partial& p, unsigned long long* acc,
+                                         kc_cmp_result* res, TileLds& lds) {
   const uint32_t tid = threadIdx.x, lane = tid & 63u;
-  if (!__syncthreads_or(p.any)) return;  // nothing but equal elements, none NaN
+  if (!__syncthreads_or(p.any)) {  // nothing but equal elements, none NaN
+    if (DIRECT && tid < kWave) write_report(pr.n_elems, pr.dtype, 0ull, res);
+    return;
+  }
   const uint32_t v0 = wave_reduce_sum(p.mis_elems), v1 = wave_reduce_sum(p.mis_bytes);
   const uint32_t v2 = wave_reduce_sum(p.over), v3 = wave_reduce_sum(p.not_close);
   if (lane == 0) {
@@ -496,7 +543,6 @@ __device__ __forceinline__ void end_pair(const Partial& p, unsigned long long* a
     atomicAdd(&lds.cnt[kCntOver], v2);
     atomicAdd(&lds.cnt[kCntNotClose], v3);
   }
-  __syncthreads();
   // four threads per bin sum its copies (eight words each)
   for (uint32_t i = tid; i < kBins * 4u; i += blockDim.x) {
     const uint4* h = reinterpret_cast<const uint4*>(lds.hist + i * 8u);
@@ -504,15 +550,13 @@ __device__ __forceinline__ void end_pair(const Partial& p, unsigned long long* a
     uint32_t n = x.x + x.y + x.z + x.w + y.x + y.y + y.z + y.w;
     n += __shfl_xor(n, 1, 64);
     n += __shfl_xor(n, 2, 64);
-    if ((i & 3u) == 0u && n != 0u) atomicAdd(&acc[kAccHist + i / 4u], (unsigned long long)n);
+    if ((i & 3u) == 0u) lds.bins[i / 4u] = n;
   }
-  if (tid < 10u) {  // thread i flushes accumulator word i
-    unsigned long long x = 0;
-    if (tid == kAccMaxAbs) x = lds.max_abs;
-    else if (tid == kAccMaxRel) x = lds.max_rel;
-    else if (tid == kAccFirstInv) x = ~lds.first;
-    else if (tid == kAccNotClose) x = lds.cnt[kCntNotClose];
-    else x = lds.cnt[tid];
+  __syncthreads();
+  if (DIRECT) {
+    if (tid < kWave) write_report(pr.n_elems, pr.dtype, found_word(lds, acc_of_word(lane)), res);
+  } else if (tid < kAccHist + kBins) {  // thread i flushes accumulator word i
+    const unsigned long long x = tid <= kAccNotClose || tid >= kAccHist ? found_word(lds, (int)tid) : 0ull;
     if (x != 0ull) {
       if (tid >= kAccMaxAbs && tid <= kAccFirstInv) atomicMax(&acc[tid], x);
       else atomicAdd(&acc[tid], x);
@@ -522,7 +566,6 @@ __device__ __forceinline__ void end_pair(const Partial& p, unsigned long long* a
   clear_tile_lds(lds);
   __syncthreads();
 }
-
 // A table entry at an address that is the same in every lane, through the
 // scalar cache (the tables are not written while the kernel runs).
 template <typename S> __device__ __forceinline__ S const_load(const S* p) {
@@ -540,13 +583,20 @@ template <typename S> __device__ __forceinline__ S const_load(const S* p) {
 // the loads of one tile's first round are in flight while the last one's is
 // worked on), in pieces whose offsets fit 32 bits.
 constexpr uint64_t kMaxRun = 1ull << 30;
+template <uint32_t T, bool DIRECT>
 __device__ __forceinline__ void compare_tiles(const CmpPairDev& pr, uint64_t idx, uint64_t n, uint32_t tile_bytes,
-                                              unsigned long long* acc, TileLds& lds, uint4* stage) {
-  Partial p = begin_pair(acc);
+                                              unsigned long long* acc, kc_cmp_result* res, TileLds& lds,
+                                              uint4* stage) {
+  // The pair's maxima so far are thresholds below which nothing needs to be recorded (they only grow).
+  Partial p{0, 0, 0, 0, false, 0.0, 0.0, 0.0};
+  if (!DIRECT) {
+    p.max_abs = bits_dbl(acc[kAccMaxAbs]);
+    p.max_rel = bits_dbl(acc[kAccMaxRel]);
+  }
   const uint64_t end = min((idx + n) * tile_bytes, pr.n_elems * pr.esize);
   for (uint64_t b0 = idx * tile_bytes; b0 < end; b0 += kMaxRun)
-    compare_bytes(pr, b0, min(b0 + kMaxRun, end), p, lds, stage);
-  end_pair(p, acc, lds);
+    compare_bytes<T>(pr, b0, min(b0 + kMaxRun, end), p, lds, stage);
+  end_pair<DIRECT>(pr, p, acc, res, lds);
 }
 
 // The tiles of workgroup b of a launch over n: consecutive ones, so that a
@@ -560,10 +610,15 @@ static_assert(kAccMisElems == kCntMis && kAccMisBytes == kCntBytes && kAccNanBot
                   kAccNanCand == kCntNanCand && kAccNanGold == kCntNanGold && kAccOverTol == kCntOver,
               "counter order");
 
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_compare(
+// T threads per workgroup: kThreads, or kWideThreads when the tiles are no more
+// than the CUs (a tile of 64 KiB is then one round).  DIRECT: every pair of the
+// launch is one tile.  (Decided per launch: with the choice made per pair, the
+// pass over 10,000 pairs of one to a thousand tiles took 2.59 ms, not 2.53.)
+template <uint32_t T, bool DIRECT>
+__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) void k_compare(
     const CmpPairDev* pairs, const CmpTileDev* tiles, uint32_t n_tiles, uint32_t tile_bytes,
-    unsigned long long* acc_all) {
-  __shared__ uint4 stage[2 * kUnroll * kThreads];
+    unsigned long long* acc_all, kc_cmp_result* res) {
+  __shared__ uint4 stage[2 * kUnroll * T];
   __shared__ __attribute__((aligned(16))) TileLds lds;
   clear_tile_lds(lds);
   __syncthreads();
@@ -572,16 +627,17 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
     const CmpTileDev tl = const_load(tiles + t);
     const CmpPairDev pr = const_load(pairs + tl.pair);
     const uint32_t n = min(end - t, pr.n_tiles - tl.idx);
-    compare_tiles(pr, tl.idx, n, tile_bytes, acc_all + (uint64_t)tl.pair * kAccWords, lds, stage);
+    compare_tiles<T, DIRECT>(pr, tl.idx, n, tile_bytes, acc_all + (uint64_t)tl.pair * kAccWords, res + tl.pair, lds, stage);
     t += n;
   }
 }
 
 // The same pass over the pairs carried in the kernel arguments: tile t
 // belongs to the first pair whose inclusive tile prefix exceeds t.
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_compare_args(
-    CmpArgPairs a, uint32_t tile_bytes, unsigned long long* acc_all) {
-  __shared__ uint4 stage[2 * kUnroll * kThreads];
+template <uint32_t T, bool DIRECT>
+__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) void k_compare_args(
+    CmpArgPairs a, uint32_t tile_bytes, unsigned long long* acc_all, kc_cmp_result* res) {
+  __shared__ uint4 stage[2 * kUnroll * T];
   __shared__ __attribute__((aligned(16))) TileLds lds;
   clear_tile_lds(lds);
   __syncthreads();
@@ -593,88 +649,81 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
       if (a.tile_end[mid] > t) hi = mid; else lo = mid + 1u;
     }
     const uint32_t start = lo == 0u ? 0u : a.tile_end[lo - 1u], n = min(end, a.tile_end[lo]) - t;
-    compare_tiles(a.pair[lo], t - start, n, tile_bytes, acc_all + (uint64_t)lo * kAccWords, lds, stage);
+    compare_tiles<T, DIRECT>(a.pair[lo], t - start, n, tile_bytes, acc_all + (uint64_t)lo * kAccWords, res + lo, lds,
+                             stage);
     t += n;
   }
 }
 
-// One pair's report from its accumulators, which are zeroed again.
-__device__ __forceinline__ void finalize_pair(const CmpPairDev& pr, unsigned long long* acc, kc_cmp_result* r) {
-  const uint64_t nb = acc[kAccNanBoth], ncand = acc[kAccNanCand], ngold = acc[kAccNanGold], over = acc[kAccOverTol];
-  r->n_elems = pr.n_elems;
-  r->n_mismatch_elems = acc[kAccMisElems];
-  r->n_mismatch_bytes = acc[kAccMisBytes];
-  r->first_mismatch = ~(uint64_t)acc[kAccFirstInv];
-  r->n_nan_both = nb;
-  r->n_nan_cand_only = ncand;
-  r->n_nan_gold_only = ngold;
-  r->n_over_tol = over;
-  r->max_abs = bits_dbl(acc[kAccMaxAbs]);
-  r->max_rel = bits_dbl(acc[kAccMaxRel]);
-  uint64_t rest = 0;
-  for (uint32_t b = 1; b < 48; ++b) {
-    const uint64_t h = b < kBins ? (uint64_t)acc[kAccHist + b] : 0ull;
-    r->ulp_hist[b] = h;
-    rest += h;
-  }
-  const uint64_t not_close = acc[kAccNotClose];
-  r->n_not_close = not_close;
-  if (pr.dtype == KC_U8) {
-    r->ulp_hist[0] = 0;
-    r->pass = r->n_mismatch_elems == 0 ? 1u : 0u;
-    r->pass_close = r->pass;
-  } else {
-    r->ulp_hist[0] = pr.n_elems - nb - ncand - ngold - rest;
-    r->pass = (over == 0 && ncand == 0 && ngold == 0) ? 1u : 0u;
-    r->pass_close = (not_close == 0 && ncand == 0 && ngold == 0) ? 1u : 0u;
-  }
-  r->status = 0u;
-  r->reserved = 0u;
-  for (uint32_t w = 0; w < kAccWords; ++w) acc[w] = 0ull;  // ready for the next call
+// One wave per pair turns its accumulators into the report and zeroes them for
+// the next call.
+__device__ __forceinline__ void finalize_pair(uint64_t n_elems, uint32_t dtype, unsigned long long* acc,
+                                              kc_cmp_result* r) {
+  const uint32_t lane = threadIdx.x % kWave;
+  const int i = acc_of_word(lane);
+  const uint64_t x = i >= 0 ? acc[i] : 0ull;
+  write_report(n_elems, dtype, x, r);
+  asm volatile("" ::: "memory");  // the lanes clear words that other lanes have read above
+  acc[lane] = 0ull;
 }
+static_assert(kAccWords == kWave, "one accumulator word per lane");
 
-// One thread per pair turns the accumulators into the report and zeroes them.
 __global__ __launch_bounds__(256) void k_compare_finalize(const CmpPairDev* pairs, uint32_t n_pairs,
                                                           unsigned long long* acc_all, kc_cmp_result* res) {
-  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+  const uint32_t i = __builtin_amdgcn_readfirstlane(blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave);
   if (i >= n_pairs) return;
-  finalize_pair(pairs[i], acc_all + (uint64_t)i * kAccWords, res + i);
+  const CmpPairDev pr = const_load(pairs + i);
+  finalize_pair(pr.n_elems, pr.dtype, acc_all + (uint64_t)i * kAccWords, res + i);
 }
 
 __global__ __launch_bounds__(64) void k_compare_args_finalize(CmpArgPairs a, unsigned long long* acc_all,
                                                               kc_cmp_result* res) {
-  const uint32_t i = threadIdx.x;
-  if (i >= a.n) return;
-  finalize_pair(a.pair[i], acc_all + (uint64_t)i * kAccWords, res + i);
+  const uint32_t i = blockIdx.x;
+  finalize_pair(a.pair[i].n_elems, a.pair[i].dtype, acc_all + (uint64_t)i * kAccWords, res + i);
 }
 
 }  // namespace
 
-hipError_t launch_compare(const CmpPairDev* pairs, const CmpTileDev* tiles, uint32_t n_tiles,
-                          uint32_t tile_bytes, unsigned long long* acc, uint32_t grid, hipStream_t s) {
+// The instantiation for a launch shape, called with T and DIRECT.
+#define KC_COMPARE_CASE(KERNEL, W, D, ...)                                                                      \
+  if (wide == W && direct == D) {                                                                               \
+    constexpr uint32_t kT = W ? kWideThreads : kThreads;                                                        \
+    hipLaunchKernelGGL((KERNEL<kT, D>), dim3(grid), dim3(kT), 0, s, __VA_ARGS__);                               \
+  }
+#define KC_COMPARE_LAUNCH(KERNEL, ...)              \
+  KC_COMPARE_CASE(KERNEL, true, true, __VA_ARGS__)  \
+  KC_COMPARE_CASE(KERNEL, true, false, __VA_ARGS__) \
+  KC_COMPARE_CASE(KERNEL, false, true, __VA_ARGS__) \
+  KC_COMPARE_CASE(KERNEL, false, false, __VA_ARGS__)
+
+hipError_t launch_compare(const CmpPairDev* pairs, const CmpTileDev* tiles, uint32_t n_tiles, uint32_t tile_bytes,
+                          unsigned long long* acc, kc_cmp_result* res, uint32_t grid, bool wide, bool direct,
+                          hipStream_t s) {
   if (n_tiles == 0) return hipSuccess;
   grid = grid < 1u ? 1u : (grid > n_tiles ? n_tiles : grid);
-  hipLaunchKernelGGL(k_compare, dim3(grid), dim3(kThreads), 0, s, pairs, tiles, n_tiles, tile_bytes, acc);
+  KC_COMPARE_LAUNCH(k_compare, pairs, tiles, n_tiles, tile_bytes, acc, res)
   return hipGetLastError();
 }
 
 hipError_t launch_compare_finalize(const CmpPairDev* pairs, uint32_t n_pairs, unsigned long long* acc,
                                    kc_cmp_result* res, hipStream_t s) {
   if (n_pairs == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_compare_finalize, dim3((n_pairs + 255) / 256), dim3(256), 0, s, pairs, n_pairs, acc, res);
+  hipLaunchKernelGGL(k_compare_finalize, dim3((n_pairs + 3) / 4), dim3(256), 0, s, pairs, n_pairs, acc, res);
   return hipGetLastError();
 }
 
 hipError_t launch_compare_args(const CmpArgPairs& a, uint32_t tile_bytes, unsigned long long* acc,
-                               kc_cmp_result* res, uint32_t grid, hipStream_t s) {
+                               kc_cmp_result* res, uint32_t grid, bool wide, hipStream_t s) {
   if (a.n == 0) return hipSuccess;
   grid = grid < 1u ? 1u : (grid > a.n_tiles ? a.n_tiles : grid);
-  hipLaunchKernelGGL(k_compare_args, dim3(grid), dim3(kThreads), 0, s, a, tile_bytes, acc);
+  const bool direct = a.n_tiles == a.n;  // every pair one tile: the pass writes the reports
+  KC_COMPARE_LAUNCH(k_compare_args, a, tile_bytes, acc, res)
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  static_assert(kArgPairs <= 64, "one finalize thread per pair");
-  hipLaunchKernelGGL(k_compare_args_finalize, dim3(1), dim3(64), 0, s, a, acc, res);
+  if (e != hipSuccess || direct) return e;
+  hipLaunchKernelGGL(k_compare_args_finalize, dim3(a.n), dim3(64), 0, s, a, acc, res);
   return hipGetLastError();
 }
+#undef KC_COMPARE_LAUNCH
+#undef KC_COMPARE_CASE
 
 }  // namespace kc

@@ -220,6 +220,12 @@ static_assert(sizeof(CmpArgPairs) <= 3072, "kernel arguments");
 // 0.47 / 0.39 / 0.35 / 0.35 ms.
 constexpr uint32_t kCompareGridPerCu = 8;
 
+// Tile of a small compare: when tiles of this size are no more than the CUs,
+// each gets a workgroup of 1024 threads, which reads it in one round (64 KiB a
+// side), and if no pair is larger the pass writes the reports itself.  16 pairs
+// of 64 KiB: 8.7 us a call, 10.5 in four 16 KiB tiles each and a second kernel.
+constexpr uint32_t kCompareWideTile = 64u << 10;
+
 constexpr uint32_t kAccWords = 64;  // per-pair accumulator words
 // accumulator word map
 enum : uint32_t {
@@ -267,19 +273,23 @@ hipError_t launch_region_diff(const Tile* tiles, uint32_t n_tiles, const RangeTa
 hipError_t launch_oob_emit(const Tile* tiles, uint32_t n_tiles, const ScanDev& sd,
                            const uint64_t* tile_prefix, const uint64_t* n_oob, kc_oob* oob,
                            uint64_t cap, kc_scan_result* res, uint64_t n_words, hipStream_t s);
-hipError_t launch_compare(const CmpPairDev* pairs, const CmpTileDev* tiles, uint32_t n_tiles,
-                          uint32_t tile_bytes, unsigned long long* acc, uint32_t grid, hipStream_t s);
+// wide: workgroups of 1024 threads.  direct: every pair is one tile and the pass writes the reports (else the
+// finalize does).
+hipError_t launch_compare(const CmpPairDev* pairs, const CmpTileDev* tiles, uint32_t n_tiles, uint32_t tile_bytes,
+                          unsigned long long* acc, kc_cmp_result* res, uint32_t grid, bool wide, bool direct,
+                          hipStream_t s);
 hipError_t launch_compare_finalize(const CmpPairDev* pairs, uint32_t n_pairs, unsigned long long* acc,
                                    kc_cmp_result* res, hipStream_t s);
 // The pass and the reports of the pairs in `a` (accumulators acc[pair * kAccWords ...], zero on entry and
 // zeroed again; reports res[0 .. a.n)).
 hipError_t launch_compare_args(const CmpArgPairs& a, uint32_t tile_bytes, unsigned long long* acc,
-                               kc_cmp_result* res, uint32_t grid, hipStream_t s);
+                               kc_cmp_result* res, uint32_t grid, bool wide, hipStream_t s);
 
 // ---- shared host helpers (kc_api.hip) ----------------------------------------
 uint32_t grid_for(const kc_ctx* c, uint32_t op, uint32_t fallback_per_cu);  // persistent grid of an op
 uint32_t elem_size(uint32_t dtype);                                         // bytes of one element
 uint32_t compare_tile_bytes(const kc_ctx* c, const kc_pair* pairs, uint32_t n_pairs);
+bool compare_wide(const kc_ctx* c, uint64_t n_tiles, uint32_t tile_bytes);  // whether 1024-thread workgroups fit it
 
 // ---- the compare that allocates nothing (kc_noalloc.hip) ---------------------
 // Looks up, once per device, the device address of the static scratch array

@@ -85,8 +85,11 @@ int kc_compare_noalloc(kc_ctx* c, const kc_pair* pairs, uint32_t n_pairs, kc_cmp
     return KC_EHIP;
   }
   const hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  // the accumulators this call uses start at zero whatever an earlier call left (fill kernel: capturable)
-  KC_HIP(launch_fill_u64(reinterpret_cast<uint64_t*>(acc), (uint64_t)n_pairs * kAccWords, 0, s));
+  // the accumulators this call uses start at zero whatever an earlier call left (fill kernel: capturable); a call
+  // whose pairs are all one tile uses none
+  bool multi = false;
+  for (uint32_t i = 0; i < n_pairs && !multi; ++i) multi = pairs[i].n_elems * elem_size(pairs[i].dtype) > tile_bytes;
+  if (multi) KC_HIP(launch_fill_u64(reinterpret_cast<uint64_t*>(acc), (uint64_t)n_pairs * kAccWords, 0, s));
   for (uint32_t b0 = 0; b0 < n_pairs; b0 += kArgPairs) {
     CmpArgPairs a{};
     a.n = std::min(kArgPairs, n_pairs - b0);
@@ -110,7 +113,8 @@ int kc_compare_noalloc(kc_ctx* c, const kc_pair* pairs, uint32_t n_pairs, kc_cmp
     }
     a.n_tiles = (uint32_t)t;
     const uint32_t grid = grid_for(c, KC_OP_COMPARE, kCompareGridPerCu);
-    KC_HIP(launch_compare_args(a, tile_bytes, acc + (uint64_t)b0 * kAccWords, res_d + b0, grid, s));
+    KC_HIP(launch_compare_args(a, tile_bytes, acc + (uint64_t)b0 * kAccWords, res_d + b0, grid,
+                               compare_wide(c, t, tile_bytes), s));
   }
   return KC_OK;
 }
