@@ -15,49 +15,41 @@ namespace {
 inline uint32_t blocks_for(uint64_t n, uint32_t per) { return (uint32_t)((n + per - 1) / per); }
 
 // Pointer graph: for every pointer-like word, set bit (source range, target
-// range).  Lanes of a wave that hit the same target share one atomicOr, and a
-// wave skips the target it set last.
-__device__ __forceinline__ void graph_emit(int32_t t, uint32_t lane, uint64_t* row, int32_t& last) {
-  uint64_t pending = __ballot(t >= 0);
-  while (pending) {
-    const int32_t leader = __ffsll((long long)pending) - 1;
-    const int32_t tb = __shfl(t, leader, 64);
-    pending &= ~__ballot(t == tb);
-    if (tb != last && (int32_t)lane == leader) atomicOr((unsigned long long*)&row[tb >> 6], 1ull << (tb & 63));
+// range).  When the lanes of a wave hit one target (a table of pointers into
+// one allocation), one lane sets it, unless the wave set it last.  Otherwise
+// each lane sets its own, unless the word already shows it: lanes on different
+// targets do not wait for each other, and a target met again costs a read.
+__device__ __forceinline__ void graph_emit(int32_t t, uint64_t* row, int32_t& last) {
+  if (t < 0) return;
+  const int32_t tb = __builtin_amdgcn_readfirstlane(t);  // of the lanes here
+  if (__ballot(t != tb) == 0ull) {
+    if (tb != last && __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)) ==
+                          (uint32_t)__builtin_ctzll(__ballot(1)))
+      atomicOr((unsigned long long*)&row[tb >> 6], 1ull << (tb & 63));
     last = tb;
+    return;
   }
+  const unsigned long long bit = 1ull << (t & 63);
+  unsigned long long* const word = (unsigned long long*)&row[t >> 6];
+  if ((__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bit) == 0ull) atomicOr(word, bit);
 }
 
 // Workgroups of kWideWaves independent waves share the wide range table.
 __global__ __launch_bounds__(kWideWaves * kWave) __attribute__((amdgpu_waves_per_eu(4))) void k_pointer_graph(
     const Tile* tiles, uint32_t n_tiles, uint64_t lo, uint64_t span, RangeTable rt, uint64_t* edge_bm,
     uint32_t row_words) {
-  const uint32_t lane = threadIdx.x % kWave, wpb = blockDim.x / kWave;
-  const uint32_t wave = blockIdx.x * wpb + threadIdx.x / kWave, n_waves = gridDim.x * wpb;
+  __shared__ uint64_t queue[kWideWaves][kPtrQueue];
+  const uint32_t wv = threadIdx.x / kWave, wpb = blockDim.x / kWave;
+  const uint32_t wave = blockIdx.x * wpb + wv, n_waves = gridDim.x * wpb;
   load_wide_fences(rt, threadIdx.x, blockDim.x);
   __syncthreads();
   for (uint32_t t = wave; t < n_tiles; t += n_waves) {
     const Tile tile = tiles[t];
     const int32_t src = wide_range_index(tile.va, rt);  // the tile's own range (always found)
-    uint64_t* row = edge_bm + (uint64_t)(src < 0 ? 0 : src) * row_words;
+    if (src < 0) continue;
+    uint64_t* const row = edge_bm + (uint64_t)src * row_words;
     int32_t last = -1;
-    const uint32_t nseg = tile.npages * 4u;
-    for (uint32_t s0 = 0; s0 < nseg; s0 += 8) {
-      uint4 x[8];
-#pragma unroll
-      for (uint32_t i = 0; i < 8; ++i)
-        x[i] = (s0 + i < nseg) ? ld16nt(tile.va + (uint64_t)(s0 + i) * 1024u + lane * 16u) : make_uint4(0, 0, 0, 0);
-#pragma unroll
-      for (uint32_t i = 0; i < 8; ++i) {
-        const uint4 v = seg_words(tile, s0 + i, lane, x[i]);  // words wholly inside the range only
-        const uint64_t w0 = ((uint64_t)v.y << 32) | v.x;
-        const uint64_t w1 = ((uint64_t)v.w << 32) | v.z;
-        const bool p0 = (w0 - lo) < span, p1 = (w1 - lo) < span;
-        if (__ballot(p0 || p1) == 0ull || src < 0) continue;  // no pointer-like word here
-        graph_emit(p0 ? wide_range_index(w0, rt) : -1, lane, row, last);
-        graph_emit(p1 ? wide_range_index(w1, rt) : -1, lane, row, last);
-      }
-    }
+    each_pointer(tile, lo, span, queue[wv], [&](uint64_t w) { graph_emit(wide_range_index(w, rt), row, last); });
   }
 }
 

@@ -585,52 +585,27 @@ __global__ __launch_bounds__(64) void k_restore_tail(RangeTable rt, const uint8_
 }
 
 // --------------------------------------------------------- closure scan ---
-__device__ __forceinline__ void closure_words(uint4 v, uint64_t lo, uint64_t span, const RangeTable& rt,
-                                              uint32_t& n_ptr, uint32_t& n_in, uint32_t& oob) {
-  const uint64_t w0 = ((uint64_t)v.y << 32) | v.x;
-  const uint64_t w1 = ((uint64_t)v.w << 32) | v.z;
-  const bool p0 = (w0 - lo) < span, p1 = (w1 - lo) < span;
-  if (__ballot(p0 || p1)) {
-    if (p0) {
-      ++n_ptr;
-      if (wide_range_index(w0, rt) >= 0) ++n_in; else ++oob;
-    }
-    if (p1) {
-      ++n_ptr;
-      if (wide_range_index(w1, rt) >= 0) ++n_in; else ++oob;
-    }
-  }
-}
-
-// Standalone scan: a tile's 16 pages are read as 64 contiguous 1-KiB runs.
-// Workgroups of kWideWaves independent waves share the wide range table.
+// Standalone scan.  Workgroups of kWideWaves independent waves share the wide
+// range table.
 __global__ __launch_bounds__(kWideWaves * kWave) __attribute__((amdgpu_waves_per_eu(4))) void k_closure(
     const Tile* tiles, uint32_t n_tiles, uint32_t tile0, ScanDev sd) {
-  const uint32_t lane = threadIdx.x % kWave, wpb = blockDim.x / kWave;
-  const uint32_t wave = blockIdx.x * wpb + threadIdx.x / kWave, n_waves = gridDim.x * wpb;
+  __shared__ uint64_t queue[kWideWaves][kPtrQueue];
+  const uint32_t lane = threadIdx.x % kWave, wv = threadIdx.x / kWave, wpb = blockDim.x / kWave;
+  const uint32_t wave = blockIdx.x * wpb + wv, n_waves = gridDim.x * wpb;
   load_wide_fences(sd.rt, threadIdx.x, blockDim.x);
   __syncthreads();
-  uint32_t n_ptr = 0, n_in = 0;
+  uint32_t n_ptr = 0, n_in = 0;  // n_ptr: of the wave; n_in: of this lane
   for (uint32_t t = wave; t < n_tiles; t += n_waves) {
     const Tile tile = tiles[t];
-    const uint32_t nseg = tile.npages * 4u;
     uint32_t oob = 0;
-    for (uint32_t s0 = 0; s0 < nseg; s0 += 8) {
-      uint4 x[8];
-#pragma unroll
-      for (uint32_t i = 0; i < 8; ++i)
-        x[i] = (s0 + i < nseg) ? ld16nt(tile.va + (uint64_t)(s0 + i) * 1024u + lane * 16u) : make_uint4(0, 0, 0, 0);
-#pragma unroll
-      for (uint32_t i = 0; i < 8; ++i)
-        closure_words(seg_words(tile, s0 + i, lane, x[i]), sd.lo, sd.span, sd.rt, n_ptr, n_in, oob);
-    }
-    const uint32_t o = wave_sum_u32(oob);
+    n_ptr += each_pointer(tile, sd.lo, sd.span, queue[wv], [&](uint64_t w) {
+      if (wide_range_index(w, sd.rt) >= 0) ++n_in; else ++oob;
+    });
+    const uint32_t o = __ballot(oob != 0u) ? wave_sum_u32(oob) : 0u;
     if (lane == 0) sd.tile_oob[tile0 + t] = o;
   }
-  const uint32_t a = wave_sum_u32(n_ptr), b = wave_sum_u32(n_in);
-  if (lane == 0) {
-    add_scan_counts(sd.counts, wave, a, b);
-  }
+  const uint32_t b = wave_sum_u32(n_in);
+  if (lane == 0) add_scan_counts(sd.counts, wave, n_ptr, b);
 }
 
 // Writes the out-of-range words of each tile at its prefix position, in
