@@ -42,27 +42,26 @@ struct PerturbArgs {
 };
 
 // The buffers of one materialisation launch: golden sources, destinations in
-// the arena, and the inclusive prefix of their 16-byte vectors.
+// the arena, and the inclusive prefix of their 16-byte vectors, or of their
+// pieces of kPieceVecs vectors (k_materialize_runs).
 constexpr uint32_t kMatBufs = 56;  // buffers per launch (kernel arguments stay below 4 KiB)
 struct MatArgs {
   uint64_t src[kMatBufs];       // golden buffer (16-byte aligned)
   uint64_t dst[kMatBufs];       // its place in the arena (16-byte aligned)
   uint64_t len[kMatBufs];       // elements
-  uint64_t vend[kMatBufs];      // inclusive prefix of 16-byte vectors
+  uint64_t vend[kMatBufs];      // inclusive prefix of 16-byte vectors, or of pieces
   uint32_t seed[kMatBufs];      // already reduced to 31 bits
-  uint64_t total;               // vectors in this launch
+  uint64_t total;               // vectors, or pieces, in this launch
   uint64_t block;
   uint32_t n, kmax;
   PerturbFmt f;
 };
 static_assert(sizeof(MatArgs) <= 3584, "kernel arguments");
 
-__device__ __forceinline__ uint64_t mix32(uint64_t x) {
-  constexpr uint64_t m = 0xFFFFFFFFull;
-  x &= m;
-  x = (((x >> 16) ^ x) * 0x45D9F3Bull) & m;
-  x = (((x >> 16) ^ x) * 0x45D9F3Bull) & m;
-  return ((x >> 16) ^ x) & m;
+__device__ __forceinline__ uint32_t mix32(uint32_t x) {
+  x = ((x >> 16) ^ x) * 0x45D9F3Bu;
+  x = ((x >> 16) ^ x) * 0x45D9F3Bu;
+  return (x >> 16) ^ x;
 }
 
 __device__ __forceinline__ uint64_t load_elem(uint64_t addr, uint32_t width) {
@@ -109,11 +108,11 @@ __device__ __forceinline__ uint64_t step_bits(uint64_t b, int64_t k, const Pertu
 // moves inside the buffer, and its signed step.
 __device__ __forceinline__ void block_move(uint64_t sd, uint64_t j, uint64_t block, uint32_t kmax, uint64_t& pos,
                                            int64_t& k) {
-  const uint64_t h1 = mix32(sd * 0x9E37ull + j * 0x85EBull + 1ull);
-  const uint64_t h2 = mix32(h1 + sd + 0x27D4EB2Full);
-  pos = j * block + h1 % block;
+  const uint32_t h1 = mix32((uint32_t)(sd * 0x9E37ull + j * 0x85EBull + 1ull));
+  const uint32_t h2 = mix32((uint32_t)(h1 + sd + 0x27D4EB2Full));
+  pos = j * block + ((block >> 32) != 0ull ? h1 : h1 % (uint32_t)block);
   k = 1 + (int64_t)(h2 % kmax);
-  if ((h2 >> 20) & 1ull) k = -k;
+  if ((h2 >> 20) & 1u) k = -k;
 }
 
 __global__ __launch_bounds__(kPerturbThreads) void k_perturb(uint8_t* arena, PerturbArgs a) {
@@ -174,9 +173,86 @@ __device__ __forceinline__ void vec_set(uint32_t (&x)[4], uint32_t e, uint32_t w
   }
 }
 
-// Candidates in one pass: each thread copies 16-byte vectors of the goldens
-// into their places in the arena and applies the moves of the (at most two)
-// blocks each vector overlaps, so the arena equals a plain copy followed by
+// Candidates in one pass, for blocks that span at least kRunBlockBytes: a wave
+// copies one piece of a buffer (8 KiB, all its loads in flight before the first
+// store), the pieces of a launch in order over its waves as a plain copy would
+// take them.  The moves are worked out once per piece, lane l for the l-th block
+// that overlaps it, and those that land in the piece (about one in 10,000
+// elements) are applied in the registers of the lane that holds the element.
+// What bounds it: memory.  The form below looks up the buffer and divides by
+// the block for every 16-byte vector.  Measured on 32 goldens of 4 KiB to 256
+// MiB (847 MB read and written, three element types): 0.31 ms (5.4 TB/s)
+// against 0.36.
+constexpr uint32_t kPieceUnroll = 8, kPieceVecs = kPieceUnroll * kWave;
+constexpr uint32_t kPieceBytes = kPieceVecs * 16u;
+// From this many bytes per block a piece overlaps at most kPieceBytes / 256 + 2 = 34 blocks: one lane each.
+constexpr uint32_t kRunBlockBytes = 256;
+static_assert(kPieceBytes / kRunBlockBytes + 2 <= kWave, "a lane per block of a piece");
+constexpr uint64_t kMaxPieces = (1ull << 26) - 4;  // per launch: 2^32 threads less a workgroup (512 GiB)
+
+__global__ __launch_bounds__(kPerturbThreads) void k_materialize_runs(MatArgs a) {
+  const uint32_t lane = threadIdx.x % kWave;
+  const uint64_t piece = blockIdx.x * (uint64_t)(kPerturbThreads / kWave) +
+                         __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  if (piece >= a.total) return;
+  uint32_t lo = 0, hi = a.n - 1u;  // first buffer whose prefix exceeds the piece
+  while (lo < hi) {
+    const uint32_t mid = (lo + hi) >> 1;
+    if (a.vend[mid] > piece) hi = mid; else lo = mid + 1u;
+  }
+  const uint32_t w = a.f.width, epv = 16u / w;
+  const uint64_t v0 = (piece - (lo == 0u ? 0ull : a.vend[lo - 1u])) * kPieceVecs;  // first vector in the buffer
+  const uint64_t len = a.len[lo], src = a.src[lo] + v0 * 16u, dst = a.dst[lo] + v0 * 16u;
+  const uint64_t e0 = v0 * epv, whole = len / epv - min(len / epv, v0);  // whole vectors from the piece's first
+  const uint32_t n = (uint32_t)min<uint64_t>(whole, kPieceVecs);         // in the piece
+  const uint32_t short_n = n < kPieceVecs ? (uint32_t)(len - (v0 + n) * epv) : 0u;  // elements of a short one after
+  uint4 x[kPieceUnroll];
+#pragma unroll
+  for (uint32_t u = 0; u < kPieceUnroll; ++u)
+    x[u] = n != 0u ? ld16(src + (uint64_t)min(u * kWave + lane, n - 1u) * 16u) : make_uint4(0, 0, 0, 0);
+  // this lane's block: where its move lands, counted from the piece's first element
+  const uint64_t elems = (uint64_t)n * epv + short_n;
+  const uint64_t j = e0 / a.block + lane;
+  uint64_t pos = 0;
+  int64_t k = 0;
+  bool in = j < len / a.block;
+  if (in) {
+    block_move(a.seed[lo], j, a.block, a.kmax, pos, k);
+    in = pos >= e0 && pos - e0 < elems;
+    pos -= e0;
+  }
+  for (uint64_t m = __ballot(in); m != 0ull; m &= m - 1ull) {
+    const int32_t L = (int32_t)__builtin_ctzll(m);
+    const uint32_t at = __shfl((uint32_t)pos, L, 64);
+    const int64_t step = __shfl((long long)k, L, 64);
+    const uint32_t v = at / epv, e = at % epv;
+#pragma unroll
+    for (uint32_t u = 0; u < kPieceUnroll; ++u) {
+      if (u * kWave + lane == v && v < n) {
+        uint32_t y[4] = {x[u].x, x[u].y, x[u].z, x[u].w};
+        vec_set(y, e, w, step_bits(vec_get(y, e, w), step, a.f));
+        x[u] = make_uint4(y[0], y[1], y[2], y[3]);
+      }
+    }
+  }
+#pragma unroll
+  for (uint32_t u = 0; u < kPieceUnroll; ++u)
+    if (u * kWave + lane < n) st16(dst + (u * kWave + lane) * 16u, x[u]);
+  // the elements of a short last vector, one per lane: nothing past either buffer is touched
+  uint64_t b = 0;
+  if (lane < short_n) b = load_elem(src + n * 16u + lane * w, w);
+  for (uint64_t m = __ballot(in && pos >= (uint64_t)n * epv); m != 0ull; m &= m - 1ull) {
+    const int32_t L = (int32_t)__builtin_ctzll(m);
+    const uint32_t at = __shfl((uint32_t)pos, L, 64);
+    const int64_t step = __shfl((long long)k, L, 64);
+    if (n * epv + lane == at) b = step_bits(b, step, a.f);
+  }
+  if (lane < short_n) store_elem(dst + n * 16u + lane * w, w, b);
+}
+
+// The same for shorter blocks: each thread copies 16-byte vectors of the goldens
+// into their places in the arena and applies the moves of the blocks each vector
+// overlaps, so the arena equals a plain copy followed by
 // k_perturb.  A buffer whose byte length is not a multiple of 16 ends in a
 // short vector, read and written element by element, so nothing outside the
 // golden is read and nothing outside the buffer's place is written.  The
@@ -316,6 +392,7 @@ int kc_materialize(kc_ctx* c, void* arena_d, uint64_t arena_elems, uint32_t dtyp
   const hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   a.block = block;
   a.kmax = kmax;
+  const bool runs = block >= kRunBlockBytes / w;
   for (uint32_t b0 = 0; b0 < n_bufs;) {
     a.n = 0;
     a.total = 0;
@@ -323,15 +400,25 @@ int kc_materialize(kc_ctx* c, void* arena_d, uint64_t arena_elems, uint32_t dtyp
       const kc_materialize_buf& m = bufs[b0];
       const uint64_t vecs = (m.length * w + 15u) / 16u;
       if (vecs == 0) continue;
+      const uint64_t pieces = (vecs + kPieceVecs - 1) / kPieceVecs;
+      // a launch's grid covers all its pieces: at most kMaxPieces of them, the rest of the list in the next one
+      if (runs && a.n > 0 && a.total + pieces > kMaxPieces) break;
       a.src[a.n] = reinterpret_cast<uint64_t>(m.src_d);
       a.dst[a.n] = reinterpret_cast<uint64_t>(arena_d) + m.offset * w;
       a.len[a.n] = m.length;
       a.seed[a.n] = m.seed & 0x7FFFFFFFu;
-      a.total += vecs;
+      a.total += runs ? pieces : vecs;
       a.vend[a.n] = a.total;
       ++a.n;
     }
     if (a.total == 0) continue;
+    if (runs) {
+      const uint32_t per_wg = kPerturbThreads / kWave;
+      hipLaunchKernelGGL(k_materialize_runs, dim3((uint32_t)((a.total + per_wg - 1) / per_wg)), dim3(kPerturbThreads),
+                         0, s, a);
+      KC_HIP(hipGetLastError());
+      continue;
+    }
     const uint64_t want = (a.total + kPerturbThreads * kMatUnroll - 1) / (kPerturbThreads * kMatUnroll);
     const uint32_t grid = (uint32_t)std::min<uint64_t>(want, 8ull * c->n_cu);
     hipLaunchKernelGGL(k_materialize, dim3(grid), dim3(kPerturbThreads), 0, s, a);
