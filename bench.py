@@ -62,7 +62,8 @@ def log(msg: str) -> None:
 
 # Sources the step's kernels are compiled from (kernels, their device helpers
 # and the shared definitions); the counter values below belong to one version.
-STEP_KERNEL_SOURCES = ("kc_compare.hip", "kc_device.h", "kc_internal.h", "kc_snapshot.hip", "kc_xxh64.h")
+STEP_KERNEL_SOURCES = ("kc_compare.hip", "kc_device.h", "kc_hash.hip", "kc_internal.h", "kc_snapshot.hip",
+                       "kc_xxh64.h")
 
 
 def code_tokens(text: str) -> str:

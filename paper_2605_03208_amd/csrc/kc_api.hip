@@ -264,11 +264,9 @@ int kc_rangeset_create_unit(kc_ctx* c, const kc_range* ranges, uint32_t n, uint6
   // Tiles of up to per_tile units of one range; a range's last unit holds
   // what is left of its size.  Returns the number of units.
   auto build_tiles = [&](uint32_t shift, uint32_t per_tile, std::vector<Tile>& tiles,
-                         std::vector<uint32_t>& range_tile, std::vector<uint32_t>* ragged,
-                         std::vector<uint32_t>* ragged_of) {
+                         std::vector<uint32_t>& range_tile) {
     const uint64_t u = 1ull << shift;
     range_tile.assign(n + 1, 0);
-    if (ragged_of) ragged_of->assign(n, UINT32_MAX);
     uint64_t g0 = 0;
     for (uint32_t i = 0; i < n; ++i) {
       range_tile[i] = (uint32_t)tiles.size();
@@ -283,49 +281,36 @@ int kc_rangeset_create_unit(kc_ctx* c, const kc_range* ranges, uint32_t n, uint6
         tiles.push_back(t);
       }
       g0 += units;
-      if (ragged && tail != u) {  // the range's last tile holds a partial unit
-        (*ragged_of)[i] = (uint32_t)ragged->size();
-        ragged->push_back((uint32_t)tiles.size() - 1u);
-      }
     }
     range_tile[n] = (uint32_t)tiles.size();
     return g0;
   };
   std::vector<Tile> tiles, scan_tiles;
-  std::vector<uint32_t> ragged;
-  // Units above 4 KiB: when 16-unit tiles would leave fewer than two waves per SIMD for the pipelined hashing
-  // pass, tiles of 8 units give twice the waves (each with half its quads busy), and two waves per SIMD cover
-  // each other's instruction latencies (2 MiB units of a 30 GiB pool: 11.4-12.6 ms against 16.5-17.2 ms).
-  // That pass takes tiles of 32 units up to 256 KiB units (each lane quad hashes two units in turn) when those
-  // still give two waves per SIMD: the skew of its quads then idles them for a smaller share of its rounds.
-  // Measured at 64 KiB units on the 30 GiB pool, averages of three rounds in one process: 11.95 ms against
-  // 12.68 at one unit per quad and 12.53 at four (128 KiB: 12.35 / 12.47 / 12.38).
-  uint32_t per_tile = kTilePages, deep_per_tile = kTilePages;
+  // Tiles of 16 units; of 8 when the units are large and few (each tile is a long run of bytes for one wave).
   if (ushift > kMinUnitShift) {
-    auto n_tiles_of = [&](uint64_t per) {
-      uint64_t t = 0;
-      for (uint32_t i = 0; i < n; ++i) t += (((ranges[i].size + (1ull << ushift) - 1) >> ushift) + per - 1) / per;
-      return t;
-    };
-    const uint64_t want = 8ull * c->n_cu;
-    if (n_tiles_of(kTilePages) < want) per_tile = kTilePages / 2;
-    deep_per_tile = per_tile;
-    for (uint32_t u = ushift <= 18 ? 2u : 1u; u > 1u; u /= 2u)
-      if (n_tiles_of(kTilePages * u) >= want) {
-        deep_per_tile = kTilePages * u;
-        break;
-      }
+    uint64_t t = 0;
+    for (uint32_t i = 0; i < n; ++i)
+      t += (((ranges[i].size + (1ull << ushift) - 1) >> ushift) + kTilePages - 1) / kTilePages;
+    if (t < 8ull * c->n_cu) rs->per_tile = kTilePages / 2;
   }
-  const uint64_t n_units = build_tiles(ushift, per_tile, tiles, rs->range_tile, &ragged, &rs->ragged_of);
-  std::vector<Tile> deep_tiles;
-  if (deep_per_tile != per_tile) build_tiles(ushift, deep_per_tile, deep_tiles, rs->deep_range_tile, nullptr, nullptr);
-  else rs->deep_range_tile = rs->range_tile;
+  const uint32_t per_tile = rs->per_tile;
+  const uint64_t n_units = build_tiles(ushift, per_tile, tiles, rs->range_tile);
   if (ushift != kMinUnitShift)
-    build_tiles(kMinUnitShift, kTilePages, scan_tiles, rs->scan_range_tile, nullptr, nullptr);
+    build_tiles(kMinUnitShift, kTilePages, scan_tiles, rs->scan_range_tile);
   else rs->scan_range_tile = rs->range_tile;
+  // The scan tile (64 KiB of a range, from its base) holding each tile's first byte: tiles of units above 4 KiB
+  // start a multiple of 64 KiB into their range.
+  std::vector<uint32_t> scan0;
+  if (ushift != kMinUnitShift) {
+    scan0.resize(tiles.size());
+    for (uint32_t i = 0; i < n; ++i)
+      for (uint32_t t = rs->range_tile[i]; t < rs->range_tile[i + 1]; ++t)
+        scan0[t] = rs->scan_range_tile[i] + (uint32_t)((tiles[t].va - ranges[i].base) / (kTilePages * kPage));
+  }
   std::vector<uint64_t> bases(n), ends(n);
   for (uint32_t i = 0; i < n; ++i) {
     rs->n_scan_words += ranges[i].size / 8;
+    rs->n_ragged += (ranges[i].size & (unit - 1)) != 0 ? 1u : 0u;
     bases[i] = ranges[i].base;
     ends[i] = ranges[i].base + ranges[i].size;
   }
@@ -333,12 +318,10 @@ int kc_rangeset_create_unit(kc_ctx* c, const kc_range* ranges, uint32_t n, uint6
   rs->n_words = (n_units + 63) / 64;
   rs->n_tiles = (uint32_t)tiles.size();
   rs->n_scan_tiles = ushift != kMinUnitShift ? (uint32_t)scan_tiles.size() : rs->n_tiles;
-  rs->n_deep_tiles = deep_per_tile != per_tile ? (uint32_t)deep_tiles.size() : rs->n_tiles;
 
   const uint64_t nb_words = (rs->n_words + 2047) / 2048, nb_tiles = ((uint64_t)rs->n_scan_tiles + 2047) / 2048;
   const size_t sz_tiles = align_up(sizeof(Tile) * std::max<size_t>(1, tiles.size()), 256);
   const size_t sz_st = align_up(sizeof(Tile) * scan_tiles.size(), 256);  // 4 KiB page tiles of the scans
-  const size_t sz_dt = align_up(sizeof(Tile) * deep_tiles.size(), 256);  // tiles of the pipelined pass
   const size_t sz_r = align_up(8 * std::max<size_t>(1, n), 256);
   const size_t sz_oob = align_up(4 * std::max<size_t>(1, rs->n_scan_tiles), 256);
   const size_t sz_tp = align_up(8 * std::max<size_t>(1, rs->n_scan_tiles), 256);
@@ -346,8 +329,8 @@ int kc_rangeset_create_unit(kc_ctx* c, const kc_range* ranges, uint32_t n, uint6
   const size_t sz_bs = align_up(8 * std::max<uint64_t>(1, std::max(nb_words, nb_tiles)), 256);
   const size_t sz_misc = 256 + align_up(8 * kScanCountWords, 256);
   const size_t sz_bk = 2 * align_up(sizeof(uint16_t) * kBuckets, 256);  // bucket index of each fence table
-  const size_t sz_rg = align_up(4 * std::max<size_t>(1, ragged.size()), 256);
-  const size_t total = sz_tiles + sz_st + sz_dt + 2 * sz_r + sz_oob + sz_tp + sz_wp + sz_bs + sz_misc + sz_bk + sz_rg;
+  const size_t sz_s0 = align_up(4 * scan0.size(), 256);
+  const size_t total = sz_tiles + sz_st + 2 * sz_r + sz_oob + sz_tp + sz_wp + sz_bs + sz_misc + sz_bk + sz_s0;
   hipError_t e = hipMalloc(&rs->dev, total);
   if (e != hipSuccess) {
     set_error("hipMalloc(rangeset)", e);
@@ -357,7 +340,6 @@ int kc_rangeset_create_unit(kc_ctx* c, const kc_range* ranges, uint32_t n, uint6
   uint8_t* p = static_cast<uint8_t*>(rs->dev);
   rs->tiles = reinterpret_cast<Tile*>(p); p += sz_tiles;
   rs->scan_tiles = ushift != kMinUnitShift ? reinterpret_cast<Tile*>(p) : rs->tiles; p += sz_st;
-  rs->deep_tiles = deep_tiles.empty() ? rs->tiles : reinterpret_cast<Tile*>(p); p += sz_dt;
   rs->bases = reinterpret_cast<uint64_t*>(p); p += sz_r;
   rs->ends = reinterpret_cast<uint64_t*>(p); p += sz_r;
   rs->tile_oob = reinterpret_cast<uint32_t*>(p); p += sz_oob;
@@ -371,8 +353,7 @@ int kc_rangeset_create_unit(kc_ctx* c, const kc_range* ranges, uint32_t n, uint6
   uint16_t* bucket_d = reinterpret_cast<uint16_t*>(p);
   uint16_t* bucket_w_d = reinterpret_cast<uint16_t*>(p + sz_bk / 2);
   p += sz_bk;
-  rs->ragged = reinterpret_cast<uint32_t*>(p);
-  rs->n_ragged = (uint32_t)ragged.size();
+  rs->hash_scan0 = scan0.empty() ? nullptr : reinterpret_cast<uint32_t*>(p);
   // Bucket index over [lowest base, highest end): the last fence at or below
   // each bucket's first address, for a table of every stride-th range.
   const uint64_t lo = n ? ranges[0].base : 0, span = n ? ranges[n - 1].base + ranges[n - 1].size - lo : 0;
@@ -405,9 +386,6 @@ int kc_rangeset_create_unit(kc_ctx* c, const kc_range* ranges, uint32_t n, uint6
   if (!scan_tiles.empty() && (e = hipMemcpy(rs->scan_tiles, scan_tiles.data(), sizeof(Tile) * scan_tiles.size(),
                                             hipMemcpyHostToDevice)) != hipSuccess)
     return fail("hipMemcpy(scan tiles)", e);
-  if (!deep_tiles.empty() && (e = hipMemcpy(rs->deep_tiles, deep_tiles.data(), sizeof(Tile) * deep_tiles.size(),
-                                            hipMemcpyHostToDevice)) != hipSuccess)
-    return fail("hipMemcpy(pipelined pass tiles)", e);
   if (n > 0) {
     if ((e = hipMemcpy(rs->bases, bases.data(), 8 * n, hipMemcpyHostToDevice)) != hipSuccess)
       return fail("hipMemcpy(bases)", e);
@@ -420,9 +398,9 @@ int kc_rangeset_create_unit(kc_ctx* c, const kc_range* ranges, uint32_t n, uint6
   if ((e = hipMemcpy(bucket_w_d, bucket_w.data(), sizeof(uint16_t) * kBuckets, hipMemcpyHostToDevice)) !=
       hipSuccess)
     return fail("hipMemcpy(bucket index)", e);
-  if (!ragged.empty() &&
-      (e = hipMemcpy(rs->ragged, ragged.data(), 4 * ragged.size(), hipMemcpyHostToDevice)) != hipSuccess)
-    return fail("hipMemcpy(ragged tiles)", e);
+  if (!scan0.empty() &&
+      (e = hipMemcpy(rs->hash_scan0, scan0.data(), 4 * scan0.size(), hipMemcpyHostToDevice)) != hipSuccess)
+    return fail("hipMemcpy(scan tile of each tile)", e);
   rs->rt.base = rs->bases;
   rs->rt.end = rs->ends;
   rs->rt.bucket = bucket_d;
@@ -464,42 +442,61 @@ static int run_closure(kc_rangeset* rs, const ScanDev& sd, hipStream_t s) {
   return KC_OK;
 }
 
+// Units per wave of the hashing pass: 16 use every lane; fewer give more waves and fewer rounds per unit.  Measured
+// (pass time, 16 / 8 / 4 units per wave; snapshots without a scan unless said):
+//   4 KiB pages, snapshot: 30 GiB 11.6 / 10.7 / 10.6 ms, 1 GiB 391 / 351 / 339 us, with a scan 365 / 339 / 363, 64 MiB
+//     with a scan 43 / 38 / 37, 16 MiB 20 / 17 / 19, 4 MiB 19 / 16 / 15: 8, and 4 for the smallest;
+//   4 KiB pages, hash only: 30 GiB 4.9 / 5.2 / 6.7 ms, 64 MiB 21.6 / 23.2 / 27.1 us, 16 MiB 14.5 / 13.0 / 14.4, 4 MiB
+//     14.0 / 12.3 / 11.8: 16 from 1024 tiles on;
+//   64 KiB units: 30 GiB 10.9 / 11.9 / 11.6 ms, 1 GiB 483 / 455 / 465 us, 64 MiB 131 / 109 / 98;
+//   2 MiB units: 30 GiB 14.9 / 11.3 / 12.7 ms, 8 GiB 4.5 / 3.9 / 5.3, 4 GiB 4.0 / 3.6 / 2.9.
+// (Before, with 16 or 8 units per wave, 512-byte chunks and for larger units skewed rows: 11.4 ms for the 30 GiB of
+// pages, 13.3 and 13.0 ms for 64 KiB and 2 MiB units.)
+static uint32_t hash_rows(const kc_rangeset* rs, bool gather) {
+  const uint32_t n_cu = rs->ctx->n_cu;
+  if (rs->ushift > kMinUnitShift) {
+    if (rs->per_tile == kTilePages) return kTilePages;
+    return rs->n_tiles >= 2u * n_cu ? 8u : 4u;
+  }
+  if (rs->n_tiles < n_cu / 2u) return 4u;
+  return gather || rs->n_tiles < 4u * n_cu ? 8u : kTilePages;
+}
+
 // Launch the page-hash kernel over all tiles, or once per range.
 static int run_hash(kc_rangeset* rs, HashParams hp, bool gather, bool prior, bool scan, uint32_t op,
                     hipStream_t s) {
   kc_ctx* c = rs->ctx;
   KernelTimer timer(c, op, s);
-  // read-only hashing runs best with twice the waves of the fused snapshot (which also writes and scans)
-  uint32_t grid = grid_for(c, op, op == KC_OP_PAGE_HASH ? 8 : 4);
-  uint32_t depth = c->tune[op].depth;
-  if (depth == 0u && rs->ushift > kMinUnitShift) depth = 2u;
-  if (scan) depth = 1u;
-  // the pipelined pass walks its own tiles
-  const bool deep = depth > 1u;
-  Tile* const tiles = deep ? rs->deep_tiles : rs->tiles;
-  const std::vector<uint32_t>& range_tile = deep ? rs->deep_range_tile : rs->range_tile;
-  // large units give few tiles, each a long serial chain: one wave per tile rather than two tiles on some
-  // waves, each wave keeping two chunks in flight in the skewed pass (three or four measured no faster)
-  if (rs->ushift > kMinUnitShift) grid = std::max(grid, std::min(deep ? rs->n_deep_tiles : rs->n_tiles, 16u * c->n_cu));
+  // built-in: a wave per part of a tile, in address order (the waves in flight then cover one compact, advancing
+  // window of the data and of the packed slots)
+  const uint32_t grid = c->tune[op].grid_per_cu ? grid_for(c, op, 0) : 0u;
+  const uint32_t rows = hash_rows(rs, gather);
   hp.ushift = rs->ushift;
+  while ((rows << hp.sub_shift) < rs->per_tile) ++hp.sub_shift;
+  hp.tiles = rs->tiles;
+  hp.scan0 = rs->hash_scan0;
   if (!c->tune[op].per_item) {
-    hp.tiles = tiles;
-    hp.n_tiles = deep ? rs->n_deep_tiles : rs->n_tiles;
-    hp.tile0 = 0;
-    hp.ragged = rs->ragged;
-    hp.n_ragged = rs->n_ragged;
-    KC_HIP(launch_page_hash(hp, gather, prior, scan, depth, grid, c->n_cu, s));
+    hp.n_tiles = rs->n_tiles;
+    KC_HIP(launch_page_hash(hp, gather, prior, scan, rows, grid, c->n_cu, s));
     return KC_OK;
   }
   for (uint32_t r = 0; r < rs->n_ranges; ++r) {
-    hp.tile0 = range_tile[r];
-    hp.tiles = tiles + hp.tile0;
-    hp.n_tiles = range_tile[r + 1] - hp.tile0;
-    const bool rg = rs->ragged_of[r] != UINT32_MAX;
-    hp.ragged = rg ? rs->ragged + rs->ragged_of[r] : nullptr;
-    hp.n_ragged = rg ? 1u : 0u;
-    KC_HIP(launch_page_hash(hp, gather, prior, scan, depth, grid, c->n_cu, s));
+    hp.tile0 = rs->range_tile[r];
+    hp.tiles = rs->tiles + hp.tile0;
+    hp.scan0 = rs->hash_scan0 ? rs->hash_scan0 + hp.tile0 : nullptr;
+    hp.n_tiles = rs->range_tile[r + 1] - hp.tile0;
+    KC_HIP(launch_page_hash(hp, gather, prior, scan, rows, grid, c->n_cu, s));
   }
+  return KC_OK;
+}
+
+// What a hashing pass adds to and so must find clear: its bitmaps, and for a
+// scan the totals and the counts per scan tile.
+static int clear_for_hash(kc_rangeset* rs, uint64_t* zero_bm_d, uint64_t* changed_bm_d, bool scan, hipStream_t s) {
+  KC_HIP(launch_zero4(zero_bm_d, rs->n_words, changed_bm_d, changed_bm_d ? rs->n_words : 0,
+                      reinterpret_cast<uint64_t*>(rs->counts), scan ? kScanCountWords : 0,
+                      reinterpret_cast<uint64_t*>(rs->tile_oob),
+                      scan ? ((uint64_t)rs->n_scan_tiles + 1) / 2 : 0, s));
   return KC_OK;
 }
 
@@ -517,8 +514,8 @@ int kc_page_hash(kc_ctx* c, const kc_rangeset* crs, uint64_t seed, const uint64_
   DeviceGuard g(c->device);
   if (!g.ok) return KC_EHIP;
   const hipStream_t s = as_stream(stream);
-  KC_HIP(launch_zero3(zero_bm_d, rs->n_words, changed_bm_d, prior_hash_d ? rs->n_words : 0,
-                      reinterpret_cast<uint64_t*>(rs->counts), scan ? kScanCountWords : 0, s));
+  int st = clear_for_hash(rs, zero_bm_d, prior_hash_d ? changed_bm_d : nullptr, scan != nullptr, s);
+  if (st != KC_OK) return st;
   HashParams hp{};
   hp.seed = seed;
   hp.prior = prior_hash_d;
@@ -526,10 +523,8 @@ int kc_page_hash(kc_ctx* c, const kc_rangeset* crs, uint64_t seed, const uint64_
   hp.zero_bm = zero_bm_d;
   hp.changed_bm = changed_bm_d;
   hp.scan = sd;
-  const bool fused = scan != nullptr && rs->ushift == kMinUnitShift;  // the scan rides on 4 KiB page tiles
-  int st = run_hash(rs, hp, false, prior_hash_d != nullptr, fused, KC_OP_PAGE_HASH, s);
+  st = run_hash(rs, hp, false, prior_hash_d != nullptr, scan != nullptr, KC_OP_PAGE_HASH, s);
   if (st != KC_OK) return st;
-  if (scan && !fused && (st = run_closure(rs, sd, s)) != KC_OK) return st;
   if (scan) return finish_scan(rs, scan, sd, s);
   return KC_OK;
 }
@@ -586,8 +581,8 @@ int kc_snapshot(kc_ctx* c, const kc_rangeset* crs, uint64_t seed, const uint64_t
   DeviceGuard g(c->device);
   if (!g.ok) return KC_EHIP;
   const hipStream_t s = as_stream(stream);
-  KC_HIP(launch_zero3(zero_bm_d, rs->n_words, nullptr, 0, reinterpret_cast<uint64_t*>(rs->counts),
-                      scan ? kScanCountWords : 0, s));
+  int st = clear_for_hash(rs, zero_bm_d, nullptr, scan != nullptr, s);
+  if (st != KC_OK) return st;
   KC_HIP(launch_probe_zero(rs->tiles, rs->n_tiles, zero_bm_d, rs->ushift, grid_for(c, KC_OP_SNAPSHOT, 8), s));
   ScanSrc src{};
   src.kind = kSrcKeepBits;
@@ -604,10 +599,8 @@ int kc_snapshot(kc_ctx* c, const kc_rangeset* crs, uint64_t seed, const uint64_t
   hp.page_va = page_va_d;
   hp.cap_pages = cap_pages;
   hp.scan = sd;
-  const bool fused = scan != nullptr && rs->ushift == kMinUnitShift;  // the scan rides on 4 KiB page tiles
-  int st = run_hash(rs, hp, true, false, fused, KC_OP_SNAPSHOT, s);
+  st = run_hash(rs, hp, true, false, scan != nullptr, KC_OP_SNAPSHOT, s);
   if (st != KC_OK) return st;
-  if (scan && !fused && (st = run_closure(rs, sd, s)) != KC_OK) return st;
   if (scan) return finish_scan(rs, scan, sd, s);
   return KC_OK;
 }

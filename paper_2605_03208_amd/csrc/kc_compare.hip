@@ -566,19 +566,6 @@ __device__ __forceinline__ void end_pair(const CmpPairDev& pr, const Partial& p,
   clear_tile_lds(lds);
   __syncthreads();
 }
-// A table entry at an address that is the same in every lane, through the
-// scalar cache (the tables are not written while the kernel runs).
-template <typename S> __device__ __forceinline__ S const_load(const S* p) {
-  static_assert(sizeof(S) % 8 == 0, "whole words");
-  S out;
-  const KC_CONST uint64_t* w = (const KC_CONST uint64_t*)p;
-  uint64_t v[sizeof(S) / 8];
-#pragma unroll
-  for (uint32_t i = 0; i < sizeof(S) / 8; ++i) v[i] = w[i];
-  __builtin_memcpy(&out, v, sizeof(S));
-  return out;
-}
-
 // n consecutive tiles of a pair from tile `idx`, as one run of bytes (so that
 // the loads of one tile's first round are in flight while the last one's is
 // worked on), in pieces whose offsets fit 32 bits.

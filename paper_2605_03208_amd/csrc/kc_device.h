@@ -79,6 +79,20 @@ __device__ __forceinline__ int32_t search_fences(uint64_t w, const uint64_t* fba
 // gives the fences (every stride-th range) to search, then the ranges of that
 // fence are searched.  Returns the range index (or -1) and its base and end.
 #define KC_CONST __attribute__((address_space(4)))
+// A table entry at an address that is the same in every lane, through the
+// scalar cache (the tables are not written while the kernel runs).
+template <typename S> __device__ __forceinline__ S const_load(const S* p) {
+  static_assert(sizeof(S) % 8 == 0, "whole words");
+  S out;
+  const KC_CONST uint64_t* w = (const KC_CONST uint64_t*)p;
+  uint64_t v[sizeof(S) / 8];
+#pragma unroll
+  for (uint32_t i = 0; i < sizeof(S) / 8; ++i) v[i] = w[i];
+  __builtin_memcpy(&out, v, sizeof(S));
+  return out;
+}
+__device__ __forceinline__ uint32_t const_load32(const uint32_t* p) { return *(const KC_CONST uint32_t*)p; }
+
 struct RangeHit {
   int32_t a;
   uint64_t base, end;
@@ -164,27 +178,32 @@ __device__ __forceinline__ void wave_lds_order() { asm volatile("" ::: "memory")
 // searched at once, one per lane: at 1 % of the words a 1 KiB load holds one or
 // two, and searching those alone ran three dependent LDS reads and a branch per
 // load for one or two lanes (2 GiB in 4096 ranges: closure scan 0.77 -> 0.36 ms,
-// pointer graph 0.93 -> 0.38, 5.9 and 5.6 TB/s read).  q: kPtrQueue words of LDS of this wave; n is the same in every
-// lane.
+// pointer graph 0.93 -> 0.38, 5.9 and 5.6 TB/s read).  q (and tags): kPtrQueue
+// entries of LDS of this wave; n is the same in every lane.
 constexpr uint32_t kPtrQueue = 192;  // below 64 left over, and up to 128 of one load
 struct PtrQueue {
   uint64_t* q;
+  uint16_t* tags;  // where each word was found, as f needs it; null: not kept
   uint32_t n = 0;
-  __device__ __forceinline__ void push(bool p, uint64_t w) {
+  __device__ __forceinline__ void push(bool p, uint64_t w, uint32_t tag) {
     const uint64_t b = __ballot(p);
-    if (p) q[n + __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u))] = w;
+    if (p) {
+      const uint32_t i = n + __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
+      q[i] = w;
+      if (tags) tags[i] = (uint16_t)tag;
+    }
     n += (uint32_t)__popcll(b);
   }
-  // f(word) in the lanes that have one: every whole 64, or all.
+  // f(word, tag) in the lanes that have one: every whole 64, or all.
   template <typename F> __device__ __forceinline__ void drain(bool all, F f) {
     const uint32_t lane = threadIdx.x % kWave;
     wave_lds_order();
     while (n >= kWave) {
       n -= kWave;
-      f(q[n + lane]);
+      f(q[n + lane], tags ? tags[n + lane] : 0u);
     }
     if (all && n != 0u) {
-      if (lane < n) f(q[lane]);
+      if (lane < n) f(q[lane], tags ? tags[lane] : 0u);
       n = 0;
     }
     wave_lds_order();
@@ -199,7 +218,7 @@ __device__ __forceinline__ uint32_t each_pointer(const Tile& tile, uint64_t lo, 
   const uint32_t lane = threadIdx.x % kWave;
   const uint32_t nseg = tile.npages * 4u;
   const uint64_t base = tile.va + lane * 16u;
-  PtrQueue queue{q};
+  PtrQueue queue{q, nullptr};
   uint32_t total = 0;
   uint4 x[8];
   auto load = [&](uint32_t s0) {  // runs past the tile are read as its last one and not looked at
@@ -221,8 +240,8 @@ __device__ __forceinline__ uint32_t each_pointer(const Tile& tile, uint64_t lo, 
       const bool p0 = (w0 - lo) < span, p1 = (w1 - lo) < span;
       if (__ballot(p0 || p1) == 0ull) continue;
       const uint32_t before = queue.n;
-      queue.push(p0, w0);
-      queue.push(p1, w1);
+      queue.push(p0, w0, 0u);
+      queue.push(p1, w1, 0u);
       total += queue.n - before;
       if (queue.n >= kWave) queue.drain(false, f);
     }

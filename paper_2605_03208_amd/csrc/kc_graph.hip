@@ -49,7 +49,7 @@ __global__ __launch_bounds__(kWideWaves * kWave) __attribute__((amdgpu_waves_per
     if (src < 0) continue;
     uint64_t* const row = edge_bm + (uint64_t)src * row_words;
     int32_t last = -1;
-    each_pointer(tile, lo, span, queue[wv], [&](uint64_t w) { graph_emit(wide_range_index(w, rt), row, last); });
+    each_pointer(tile, lo, span, queue[wv], [&](uint64_t w, uint32_t) { graph_emit(wide_range_index(w, rt), row, last); });
   }
 }
 

@@ -14,8 +14,6 @@ namespace kc {
 constexpr uint32_t kPage = 4096;
 constexpr uint32_t kWave = 64;
 constexpr uint32_t kTilePages = 16;     // pages per wave tile (one lane quad per page)
-constexpr uint32_t kChunk = 512;        // bytes of each page staged per step
-constexpr uint32_t kStageStride = kChunk + 32;  // padded LDS row: quads land in distinct banks
 constexpr uint32_t kFences = 256;       // range-table entries held in LDS by one-wave workgroups
 constexpr uint32_t kWideFences = 4096;  // the same, shared by the waves of a multi-wave workgroup
 constexpr uint32_t kBuckets = 1024;     // entries of the LDS bucket index over the ranges
@@ -63,7 +61,7 @@ constexpr uint32_t kMinUnitShift = 12, kMaxUnitShift = 21;
 struct Tile {
   uint64_t va;              // VA of the first unit
   uint32_t g;               // global index of the first unit
-  uint32_t npages : 8;      // 1..16 units (1..64 in the tiles of the pipelined hashing pass)
+  uint32_t npages : 8;      // 1..16 units
   uint32_t last_len : 24;   // 1..unit bytes
 };
 static_assert(sizeof(Tile) == 16, "tile layout");
@@ -160,8 +158,8 @@ struct HashParams {
   const Tile* tiles;
   uint32_t n_tiles;
   uint32_t tile0;          // index of tiles[0] in the rangeset's tile list
-  const uint32_t* ragged;  // indices (in the rangeset's list) of tiles with a partial last page
-  uint32_t n_ragged;
+  uint32_t sub_shift;      // 1 << sub_shift parts per tile, each a wave's work
+  const uint32_t* scan0;   // per tile: the scan tile of its first byte (null: 4 KiB units, the tile itself)
   uint64_t seed;
   const uint64_t* prior;   // nullable
   uint64_t* hash;
@@ -235,15 +233,11 @@ enum : uint32_t {
 
 // ---- launchers (kc_kernels.hip) ------------------------------------------
 hipError_t launch_fill_u64(uint64_t* p, uint64_t n, uint64_t v, hipStream_t s);
-hipError_t launch_zero3(uint64_t* a, uint64_t na, uint64_t* b, uint64_t nb, uint64_t* c, uint64_t nc,
-                        hipStream_t s);
-// depth 2 to 4: the pipelined pass of large units with that many chunks in flight per wave (few tiles, about one
-// wave per SIMD); not with scan.  0 or 1: the pass with one chunk in flight.
-hipError_t launch_page_hash(const HashParams& p, bool gather, bool prior, bool scan, uint32_t depth,
-                            uint32_t grid, uint32_t n_cu, hipStream_t s);
-// The pipelined pass of units above 4 KiB (kc_units.hip), depth 2 to 4, on a launch shape already chosen.
-hipError_t launch_page_hash_deep(const HashParams& p, bool gather, bool prior, uint32_t depth, uint32_t blocks,
-                                 uint32_t waves_per_block, hipStream_t s);
+hipError_t launch_zero4(uint64_t* a, uint64_t na, uint64_t* b, uint64_t nb, uint64_t* c, uint64_t nc, uint64_t* d,
+                        uint64_t nd, hipStream_t s);
+// The hashing pass (kc_hash.hip); rows: most units per wave (16, 8 or 4); grid: waves (0: one per part of a tile).
+hipError_t launch_page_hash(const HashParams& p, bool gather, bool prior, bool scan, uint32_t rows, uint32_t grid,
+                            uint32_t n_cu, hipStream_t s);
 hipError_t launch_probe_zero(const Tile* tiles, uint32_t n_tiles, uint64_t* zero_bm, uint32_t ushift,
                              uint32_t grid, hipStream_t s);
 hipError_t launch_scan(const ScanSrc& src, uint64_t* out, uint64_t* block_sums,
@@ -358,9 +352,7 @@ struct kc_rangeset {
   uint32_t ushift = 12;              // log2 of the hash unit; n_pages, n_words and the tiles count units
   uint64_t n_pages = 0, n_words = 0;
   uint64_t n_scan_words = 0;         // 8-byte words wholly inside the ranges
-  uint32_t n_ragged = 0;             // tiles with a partial last page (at most one per range)
-  uint32_t* ragged = nullptr;        // their indices, ascending (device)
-  std::vector<uint32_t> ragged_of;   // per range: its entry in ragged, or UINT32_MAX
+  uint32_t n_ragged = 0;             // ranges whose last unit is partial
   std::vector<uint32_t> range_tile;  // first tile of each range (n + 1)
   uint64_t win_lo = 0, win_hi = 0;   // default pointer window
   std::vector<kc_range> host_ranges;
@@ -369,12 +361,8 @@ struct kc_rangeset {
   uint32_t n_scan_tiles = 0;
   std::vector<uint32_t> scan_range_tile;
   kc::Tile* scan_tiles = nullptr;
-  // tiles of the pipelined hashing pass of large units: up to 32 units of one
-  // range, each lane quad hashing up to two of them in turn (the same list as
-  // `tiles` when a quad takes one unit)
-  uint32_t n_deep_tiles = 0;
-  std::vector<uint32_t> deep_range_tile;
-  kc::Tile* deep_tiles = nullptr;
+  uint32_t per_tile = 16;            // most units of a tile in `tiles`
+  uint32_t* hash_scan0 = nullptr;    // units above 4 KiB: the scan tile of each tile's first byte (device)
   void* dev = nullptr;
   kc::Tile* tiles = nullptr;
   uint64_t* bases = nullptr;

@@ -1,12 +1,12 @@
-// kc_snapshot.hip -- gfx950 kernels of the snapshot, restore and closure scan.
+// kc_snapshot.hip -- gfx950 kernels of the snapshot around the hashing pass
+// (kc_hash.hip), of the restore and of the closure scan.
 //
 // Memory-bound streaming kernels: persistent grids of 64-lane waves striding
 // over a tile list (16 pages of one range per tile).  Most workgroups are one
-// wave; the hash pass and the standalone scan put several independent waves in
-// a workgroup to share one range table, and the out-of-range emission uses one
-// wave per page of a tile.  Global traffic is 16-byte loads / stores that
-// cover whole 512-byte or 1-KiB runs; the XXH64 lanes read their words from a
-// padded LDS stage.
+// wave; the standalone scan puts several independent waves in a workgroup to
+// share one range table, and the out-of-range emission uses one wave per page
+// of a tile.  Global traffic is 16-byte loads / stores that cover whole 1-KiB
+// runs.
 #include <algorithm>
 
 #include "kc_device.h"
@@ -23,189 +23,16 @@ __global__ void k_fill_u64(uint64_t* p, uint64_t n, uint64_t v) {
     p[i] = v;
 }
 
-// Zero up to three arrays in one launch (index space = their concatenation).
-__global__ void k_zero3(uint64_t* a, uint64_t na, uint64_t* b, uint64_t nb, uint64_t* c, uint64_t nc) {
-  const uint64_t n = na + nb + nc;
+// Zero up to four arrays in one launch (index space = their concatenation).
+__global__ void k_zero4(uint64_t* a, uint64_t na, uint64_t* b, uint64_t nb, uint64_t* c, uint64_t nc, uint64_t* d,
+                        uint64_t nd) {
+  const uint64_t n = na + nb + nc + nd;
   for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n;
        i += (uint64_t)gridDim.x * blockDim.x) {
     if (i < na) a[i] = 0;
     else if (i < na + nb) b[i - na] = 0;
-    else c[i - na - nb] = 0;
-  }
-}
-
-// ---------------------------------------------------------- page hash -----
-// One wave hashes a tile of up to 16 pages: lane quad q owns page q, lane k of
-// the quad runs XXH64 accumulator k over the words 8k + 32s of each stripe s.
-// The wave streams the tile in 8 chunks of 512 bytes per page: 8 loads of
-// 16 bytes per lane (instruction j covers pages 2j and 2j+1 with 32 lanes
-// each), the chunk goes to a padded LDS stage, and the quad lanes read their
-// 16 words of the chunk from there.  While chunk c is hashed, the loads of
-// chunk c+1 are in flight.
-//
-// GATHER: zero bits come from the probe, zero pages are not read (their hash
-// is computed from zeros), kept pages are also stored to their packed slot.
-// RAGGED = false: every tile whose pages are all whole (the hot path); RAGGED =
-// true: only the tiles listed in p.ragged, whose last page is partial (at most
-// one per range), with the bytes past the range's end masked out.
-//
-// A workgroup holds up to kHashWaves independent waves, each with its own
-// stage; with the closure scan they share one wide range table in dynamic LDS.
-template <bool GATHER, bool PRIOR, bool SCAN, bool RAGGED>
-__global__ __launch_bounds__(kHashWaves * kWave) __attribute__((amdgpu_waves_per_eu(RAGGED ? 1 : (SCAN ? 3 : 4)))) void k_page_hash(
-    HashParams p) {
-  __shared__ __attribute__((aligned(16))) uint8_t stage_all[kHashWaves][kTilePages * kStageStride];
-  __shared__ uint64_t tail_all[kHashWaves][kTilePages][4];  // a partial page's bytes past its last whole stripe
-  const uint32_t lane = threadIdx.x % kWave, wv = threadIdx.x / kWave, wpb = blockDim.x / kWave;
-  uint8_t* const stage = stage_all[wv];
-  uint64_t(*const tail_lds)[4] = tail_all[wv];
-  const uint32_t q = lane >> 2, k = lane & 3u;
-  const uint32_t half = lane >> 5, off16 = (lane & 31u) * 16u;
-  const uint64_t scan_lo = p.scan.lo, scan_span = p.scan.span;
-  const uint32_t ushift = p.ushift, unit = 1u << ushift;  // hash unit: 4 KiB .. 2 MiB
-  const uint32_t n_chunks = unit / kChunk;
-  if (SCAN) {
-    load_wide_fences(p.scan.rt, threadIdx.x, blockDim.x);
-    __syncthreads();  // the only workgroup barrier: the waves share nothing else
-  }
-  uint32_t n_ptr = 0, n_in = 0;
-
-  const uint32_t wave = blockIdx.x * wpb + wv, n_waves = gridDim.x * wpb;
-  const uint32_t n_items = RAGGED ? p.n_ragged : p.n_tiles;
-  for (uint32_t it = wave; it < n_items; it += n_waves) {
-    const uint32_t t = RAGGED ? p.ragged[it] - p.tile0 : it;
-    const Tile tile = p.tiles[t];
-    if (!RAGGED && tile.last_len != unit) continue;  // left to the ragged launch
-    const uint32_t np = tile.npages;
-    const uint64_t va = tile.va;
-    const uint32_t last_pg = np - 1u, last_len = RAGGED ? (uint32_t)tile.last_len : unit;  // only the last unit can be partial
-    uint32_t keep = (1u << np) - 1u;
-    uint64_t slot_j[8];
-    if (GATHER) {
-      uint64_t slot = 0;
-      bool kept = false;
-      if (lane < np) {
-        const uint64_t g = (uint64_t)tile.g + lane;
-        const uint64_t zw = p.zero_bm[g >> 6];
-        kept = ((zw >> (g & 63u)) & 1ull) == 0ull;
-        slot = p.word_prefix[g >> 6] + (uint64_t)__popcll(~zw & ((1ull << (g & 63u)) - 1ull));
-      }
-      keep = (uint32_t)__ballot(kept);
-#pragma unroll
-      for (uint32_t j = 0; j < 8; ++j) slot_j[j] = __shfl(slot, 2 * j + half, 64);
-      if (kept && slot < p.cap_pages) p.page_va[slot] = va + ((uint64_t)lane << ushift);
-    }
-    uint32_t nonzero = 0, oob = 0;
-    uint64_t acc = acc_init(p.seed, k);
-
-    uint4 cur[8];
-#pragma unroll
-    for (uint32_t j = 0; j < 8; ++j) {
-      const uint32_t pg = 2 * j + half;
-      if (RAGGED) {
-        const uint32_t len = pg == last_pg ? last_len : unit;
-        cur[j] = ((keep >> pg) & 1u) && off16 < len
-                     ? clip16(ld16nt(va + ((uint64_t)pg << ushift) + off16), off16, len)
-                     : make_uint4(0, 0, 0, 0);
-      } else {
-        cur[j] = ((keep >> pg) & 1u) ? ld16nt(va + ((uint64_t)pg << ushift) + off16) : make_uint4(0, 0, 0, 0);
-      }
-    }
-    // this lane's quad: stripes of its unit, and the bytes past the last stripe
-    const uint32_t qlen = RAGGED && q == last_pg ? last_len : unit;
-    const uint32_t lim = qlen / 32u, rem = qlen & 31u;
-#pragma unroll 1
-    for (uint32_t c = 0; c < n_chunks; ++c) {
-      uint32_t ptr_mask = 0;  // bit 2j+h: word h of this lane's 16 bytes of load j is pointer-like
-#pragma unroll
-      for (uint32_t j = 0; j < 8; ++j) {
-        const uint32_t pg = 2 * j + half;
-        const uint4 v = cur[j];
-        if (!GATHER) {
-          const uint64_t b = __ballot(nz16(v));
-          nonzero |= ((uint32_t)((uint32_t)b != 0u) << (2 * j)) | ((uint32_t)((b >> 32) != 0ull) << (2 * j + 1));
-        }
-        if (SCAN) {  // pointer-like words are only marked here; the range search runs once per chunk
-          const uint64_t w0 = ((uint64_t)v.y << 32) | v.x;
-          const uint64_t w1 = ((uint64_t)v.w << 32) | v.z;
-          uint32_t p0 = (w0 - scan_lo) < scan_span ? 1u : 0u;
-          uint32_t p1 = (w1 - scan_lo) < scan_span ? 1u : 0u;
-          if (RAGGED) {  // words wholly inside the range only
-            const uint32_t o = c * kChunk + off16, len = pg == last_pg ? last_len : unit;
-            p0 = o + 8u <= len ? p0 : 0u;
-            p1 = o + 16u <= len ? p1 : 0u;
-          }
-          ptr_mask |= (p0 << (2 * j)) | (p1 << (2 * j + 1));
-        }
-        if (GATHER) {
-          if (((keep >> pg) & 1u) && slot_j[j] < p.cap_pages)
-            st16nt((uint64_t)p.packed + (slot_j[j] << ushift) + c * kChunk + off16, v);
-        }
-        *reinterpret_cast<uint4*>(stage + pg * kStageStride + off16) = v;
-      }
-      wave_lds_order();
-      // loads of the next chunk overlap the hashing of this one
-      const uint32_t cn = c + 1 < n_chunks ? c + 1 : c;
-      const uint32_t more = c + 1 < n_chunks ? keep : 0u;
-#pragma unroll
-      for (uint32_t j = 0; j < 8; ++j) {
-        const uint32_t pg = 2 * j + half, o = cn * kChunk + off16;
-        if (RAGGED) {
-          const uint32_t len = pg == last_pg ? last_len : unit;
-          cur[j] = ((more >> pg) & 1u) && o < len ? clip16(ld16nt(va + ((uint64_t)pg << ushift) + o), o, len)
-                                                  : make_uint4(0, 0, 0, 0);
-        } else {
-          cur[j] = ((more >> pg) & 1u) ? ld16nt(va + ((uint64_t)pg << ushift) + o) : make_uint4(0, 0, 0, 0);
-        }
-      }
-      if (SCAN && __ballot(ptr_mask != 0u)) {
-        // the marked words, read back from the stage: one search chain per lane per chunk
-        n_ptr += (uint32_t)__popc(ptr_mask);
-        for (uint32_t m = ptr_mask; m != 0u; m &= m - 1u) {
-          const uint32_t bit = (uint32_t)__builtin_ctz(m);
-          const uint64_t w = *reinterpret_cast<const uint64_t*>(stage + (2u * (bit >> 1) + half) * kStageStride +
-                                                                 off16 + (bit & 1u) * 8u);
-          if (wide_range_index(w, p.scan.rt) >= 0) ++n_in; else ++oob;
-        }
-      }
-      const uint8_t* row = stage + q * kStageStride + k * 8u;
-#pragma unroll
-      for (uint32_t s = 0; s < kChunk / 32; ++s)
-        if (!RAGGED || c * (kChunk / 32) + s < lim) acc = xround(acc, *reinterpret_cast<const uint64_t*>(row + s * 32u));
-      if (RAGGED && rem != 0u && c == lim / (kChunk / 32))  // the partial page's last bytes are in this chunk
-        tail_lds[q][k] = *reinterpret_cast<const uint64_t*>(stage + q * kStageStride + (lim * 32u - c * kChunk) + 8u * k);
-      wave_lds_order();
-    }
-
-    const uint64_t merged = xxh64_merge4(acc, k);  // every lane of the quad takes part
-    uint64_t h = (lim > 0u ? merged : p.seed + kP5) + qlen;
-    if (RAGGED && rem != 0u) {
-      const uint64_t tail[4] = {tail_lds[q][0], tail_lds[q][1], tail_lds[q][2], tail_lds[q][3]};
-      h = xxh64_tail(h, tail, rem);
-    }
-    h = xxh64_avalanche(h);
-    const bool mine = (k == 0u) && (q < np);
-    if (mine) p.hash[tile.g + q] = h;
-    const uint32_t valid = (1u << np) - 1u;
-    if (!GATHER) {
-      const uint32_t zero = ~nonzero & valid;
-      if (lane == 0) or_page_bits(p.zero_bm, tile.g, np, zero);
-    }
-    if (PRIOR) {
-      const bool ch = mine && (h != p.prior[tile.g + q]);
-      const uint32_t cb = quad_bits(__ballot(ch));
-      if (lane == 0) or_page_bits(p.changed_bm, tile.g, np, cb);
-    }
-    if (SCAN) {
-      const uint32_t o = wave_sum_u32(oob);
-      if (lane == 0) p.scan.tile_oob[p.tile0 + t] = o;
-    }
-  }
-  if (SCAN) {
-    const uint32_t a = wave_sum_u32(n_ptr), b = wave_sum_u32(n_in);
-    if (lane == 0) {
-      add_scan_counts(p.scan.counts, wave, a, b);
-    }
+    else if (i < na + nb + nc) c[i - na - nb] = 0;
+    else d[i - na - nb - nc] = 0;
   }
 }
 
@@ -598,7 +425,7 @@ __global__ __launch_bounds__(kWideWaves * kWave) __attribute__((amdgpu_waves_per
   for (uint32_t t = wave; t < n_tiles; t += n_waves) {
     const Tile tile = tiles[t];
     uint32_t oob = 0;
-    n_ptr += each_pointer(tile, sd.lo, sd.span, queue[wv], [&](uint64_t w) {
+    n_ptr += each_pointer(tile, sd.lo, sd.span, queue[wv], [&](uint64_t w, uint32_t) {
       if (wide_range_index(w, sd.rt) >= 0) ++n_in; else ++oob;
     });
     const uint32_t o = __ballot(oob != 0u) ? wave_sum_u32(oob) : 0u;
@@ -708,12 +535,12 @@ inline uint32_t blocks_for(uint64_t n, uint32_t per) { return (uint32_t)((n + pe
 }  // namespace
 
 // ------------------------------------------------------------- launchers --
-hipError_t launch_zero3(uint64_t* a, uint64_t na, uint64_t* b, uint64_t nb, uint64_t* c, uint64_t nc,
-                        hipStream_t s) {
-  const uint64_t n = na + nb + nc;
+hipError_t launch_zero4(uint64_t* a, uint64_t na, uint64_t* b, uint64_t nb, uint64_t* c, uint64_t nc, uint64_t* d,
+                        uint64_t nd, hipStream_t s) {
+  const uint64_t n = na + nb + nc + nd;
   if (n == 0) return hipSuccess;
   const uint64_t nbk = blocks_for(n, 256);
-  hipLaunchKernelGGL(k_zero3, dim3((uint32_t)(nbk < 4096 ? nbk : 4096)), dim3(256), 0, s, a, na, b, nb, c, nc);
+  hipLaunchKernelGGL(k_zero4, dim3((uint32_t)(nbk < 4096 ? nbk : 4096)), dim3(256), 0, s, a, na, b, nb, c, nc, d, nd);
   return hipGetLastError();
 }
 
@@ -723,33 +550,6 @@ hipError_t launch_fill_u64(uint64_t* p, uint64_t n, uint64_t v, hipStream_t s) {
   const uint32_t grid = (uint32_t)(nb < 4096 ? nb : 4096);
   hipLaunchKernelGGL(k_fill_u64, dim3(grid), dim3(256), 0, s, p, n, v);
   return hipGetLastError();
-}
-
-hipError_t launch_page_hash(const HashParams& p, bool gather, bool prior, bool scan, uint32_t depth, uint32_t grid,
-                            uint32_t n_cu, hipStream_t s) {
-  if (p.n_tiles == 0) return hipSuccess;
-  uint32_t blocks = 1, wpb = 1, blocks_r = 1, wpb_r = 1;  // grid counts waves
-  wide_shape(std::min(grid, p.n_tiles), n_cu, &blocks, &wpb, kHashWaves);
-  wide_shape(std::min(grid, std::max(1u, p.n_ragged)), n_cu, &blocks_r, &wpb_r, kHashWaves);
-  const size_t lds = scan ? wide_lds_bytes(p.scan.rt) : 0;
-  if (depth > 1u && !scan)  // every tile, partial last units included, through the pipelined pass
-    return launch_page_hash_deep(p, gather, prior, depth, blocks, wpb, s);
-#define KC_HASH_CASE(G, P, S)                                                                              \
-  if (gather == G && prior == P && scan == S) {                                                           \
-    hipLaunchKernelGGL((k_page_hash<G, P, S, false>), dim3(blocks), dim3(wpb * kWave), lds, s, p);        \
-    hipError_t e = hipGetLastError();                                                                     \
-    if (e != hipSuccess || p.n_ragged == 0) return e;                                                     \
-    hipLaunchKernelGGL((k_page_hash<G, P, S, true>), dim3(blocks_r), dim3(wpb_r * kWave), lds, s, p);     \
-    return hipGetLastError();                                                                             \
-  }
-  KC_HASH_CASE(false, false, false)
-  KC_HASH_CASE(false, false, true)
-  KC_HASH_CASE(false, true, false)
-  KC_HASH_CASE(false, true, true)
-  KC_HASH_CASE(true, false, false)
-  KC_HASH_CASE(true, false, true)
-#undef KC_HASH_CASE
-  return hipErrorInvalidValue;
 }
 
 hipError_t launch_probe_zero(const Tile* tiles, uint32_t n_tiles, uint64_t* zero_bm, uint32_t ushift, uint32_t grid,

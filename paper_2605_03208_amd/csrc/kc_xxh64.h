@@ -22,9 +22,12 @@ __device__ __forceinline__ uint64_t rotl64(uint64_t x, uint32_t r) {
 }
 
 __device__ __forceinline__ uint64_t xround(uint64_t acc, uint64_t in) {
-  acc += in * kP2;
-  acc = rotl64(acc, 31);
-  return acc * kP1;
+  uint64_t x = in * kP2;
+  asm("" : "+v"(x));  // the product is ready before the accumulator is: not one multiply-add that waits for it
+  x += acc;
+  const uint32_t lo = (uint32_t)x, hi = (uint32_t)(x >> 32);
+  x = ((uint64_t)__builtin_amdgcn_alignbit(hi, lo, 1) << 32) | __builtin_amdgcn_alignbit(lo, hi, 1);  // rotate by 31
+  return x * kP1;
 }
 
 // 64-bit DPP move inside a lane quad (quad_perm control word).
@@ -105,7 +108,5 @@ __device__ __forceinline__ uint32_t quad_bits(uint64_t ballot) {
   for (uint32_t q = 0; q < 16; ++q) out |= (uint32_t)((ballot >> (4u * q)) & 1ull) << q;
   return out;
 }
-
-constexpr uint32_t kHashWaves = 4;  // most waves per workgroup of a hashing pass
 
 }  // namespace kc
