@@ -319,6 +319,11 @@ int kc_rangeset_create_unit(kc_ctx* c, const kc_range* ranges, uint32_t n, uint6
   rs->n_tiles = (uint32_t)tiles.size();
   rs->n_scan_tiles = ushift != kMinUnitShift ? (uint32_t)scan_tiles.size() : rs->n_tiles;
 
+  std::vector<uint32_t> word_tile(rs->n_words);
+  for (uint32_t t = 0; t < rs->n_tiles; ++t)  // a tile has at most 16 units, so it holds at most one word's first
+    if ((tiles[t].g & 63u) == 0u || (tiles[t].g >> 6) != ((tiles[t].g + tiles[t].npages - 1u) >> 6))
+      word_tile[(tiles[t].g + tiles[t].npages - 1u) >> 6] = t;
+
   const uint64_t nb_words = (rs->n_words + 2047) / 2048, nb_tiles = ((uint64_t)rs->n_scan_tiles + 2047) / 2048;
   const size_t sz_tiles = align_up(sizeof(Tile) * std::max<size_t>(1, tiles.size()), 256);
   const size_t sz_st = align_up(sizeof(Tile) * scan_tiles.size(), 256);  // 4 KiB page tiles of the scans
@@ -330,7 +335,9 @@ int kc_rangeset_create_unit(kc_ctx* c, const kc_range* ranges, uint32_t n, uint6
   const size_t sz_misc = 256 + align_up(8 * kScanCountWords, 256);
   const size_t sz_bk = 2 * align_up(sizeof(uint16_t) * kBuckets, 256);  // bucket index of each fence table
   const size_t sz_s0 = align_up(4 * scan0.size(), 256);
-  const size_t total = sz_tiles + sz_st + 2 * sz_r + sz_oob + sz_tp + sz_wp + sz_bs + sz_misc + sz_bk + sz_s0;
+  const size_t sz_wt = align_up(4 * word_tile.size(), 256);
+  const size_t total =
+      sz_tiles + sz_st + 2 * sz_r + sz_oob + sz_tp + sz_wp + sz_bs + sz_misc + sz_bk + sz_s0 + sz_wt;
   hipError_t e = hipMalloc(&rs->dev, total);
   if (e != hipSuccess) {
     set_error("hipMalloc(rangeset)", e);
@@ -354,6 +361,8 @@ int kc_rangeset_create_unit(kc_ctx* c, const kc_range* ranges, uint32_t n, uint6
   uint16_t* bucket_w_d = reinterpret_cast<uint16_t*>(p + sz_bk / 2);
   p += sz_bk;
   rs->hash_scan0 = scan0.empty() ? nullptr : reinterpret_cast<uint32_t*>(p);
+  p += sz_s0;
+  rs->word_tile = reinterpret_cast<uint32_t*>(p);
   // Bucket index over [lowest base, highest end): the last fence at or below
   // each bucket's first address, for a table of every stride-th range.
   const uint64_t lo = n ? ranges[0].base : 0, span = n ? ranges[n - 1].base + ranges[n - 1].size - lo : 0;
@@ -401,6 +410,9 @@ int kc_rangeset_create_unit(kc_ctx* c, const kc_range* ranges, uint32_t n, uint6
   if (!scan0.empty() &&
       (e = hipMemcpy(rs->hash_scan0, scan0.data(), 4 * scan0.size(), hipMemcpyHostToDevice)) != hipSuccess)
     return fail("hipMemcpy(scan tile of each tile)", e);
+  if (!word_tile.empty() &&
+      (e = hipMemcpy(rs->word_tile, word_tile.data(), 4 * word_tile.size(), hipMemcpyHostToDevice)) != hipSuccess)
+    return fail("hipMemcpy(tile of each bitmap word)", e);
   rs->rt.base = rs->bases;
   rs->rt.end = rs->ends;
   rs->rt.bucket = bucket_d;
@@ -581,9 +593,20 @@ int kc_snapshot(kc_ctx* c, const kc_rangeset* crs, uint64_t seed, const uint64_t
   DeviceGuard g(c->device);
   if (!g.ok) return KC_EHIP;
   const hipStream_t s = as_stream(stream);
-  int st = clear_for_hash(rs, zero_bm_d, nullptr, scan != nullptr, s);
-  if (st != KC_OK) return st;
-  KC_HIP(launch_probe_zero(rs->tiles, rs->n_tiles, zero_bm_d, rs->ushift, grid_for(c, KC_OP_SNAPSHOT, 8), s));
+  ProbeParams pp{};
+  pp.tiles = rs->tiles;
+  pp.n_tiles = rs->n_tiles;
+  pp.word_tile = rs->word_tile;
+  pp.n_units = rs->n_pages;
+  pp.zero_bm = zero_bm_d;
+  pp.ushift = rs->ushift;
+  if (scan) {  // what the hashing pass adds to
+    pp.clear_a = reinterpret_cast<uint64_t*>(rs->counts);
+    pp.n_clear_a = kScanCountWords;
+    pp.clear_b = reinterpret_cast<uint64_t*>(rs->tile_oob);
+    pp.n_clear_b = ((uint64_t)rs->n_scan_tiles + 1) / 2;
+  }
+  KC_HIP(launch_probe_zero(pp, rs->n_words, c->n_cu, s));
   ScanSrc src{};
   src.kind = kSrcKeepBits;
   src.zero_bm = zero_bm_d;
@@ -599,7 +622,7 @@ int kc_snapshot(kc_ctx* c, const kc_rangeset* crs, uint64_t seed, const uint64_t
   hp.page_va = page_va_d;
   hp.cap_pages = cap_pages;
   hp.scan = sd;
-  st = run_hash(rs, hp, true, false, scan != nullptr, KC_OP_SNAPSHOT, s);
+  const int st = run_hash(rs, hp, true, false, scan != nullptr, KC_OP_SNAPSHOT, s);
   if (st != KC_OK) return st;
   if (scan) return finish_scan(rs, scan, sd, s);
   return KC_OK;

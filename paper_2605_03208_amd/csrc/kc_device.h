@@ -26,6 +26,17 @@ __device__ __forceinline__ void add_scan_counts(unsigned long long* counts, uint
   if (n_in) atomicAdd(c + 1, (unsigned long long)n_in);
 }
 
+// Buffer resource over [base, base + bytes) (gfx9 raw buffer, no stride):
+// loads outside it return zeros and stores outside it are dropped.  base and
+// bytes must be the same in every lane of the wave.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t raw_rsrc(uint64_t base, uint32_t bytes) {
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)base);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(base >> 32));
+  return __builtin_amdgcn_make_buffer_rsrc((void*)(((uint64_t)hi << 32) | lo), (short)0,
+                                           (int)__builtin_amdgcn_readfirstlane(bytes), 0x00020000);
+}
+constexpr int kNt = 2;  // cache policy of buffer accesses: non-temporal
+
 // ---------------------------------------------------------- range search --
 struct FenceLds {
   uint64_t base[kFences];

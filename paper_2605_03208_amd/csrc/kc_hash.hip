@@ -10,17 +10,7 @@
 namespace kc {
 namespace {
 
-// Buffer resource over [base, base + bytes) (gfx9 raw buffer, no stride):
-// loads outside it return zeros and stores outside it are dropped.  base and
-// bytes must be the same in every lane of the wave.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t raw_rsrc(uint64_t base, uint32_t bytes) {
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)base);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(base >> 32));
-  return __builtin_amdgcn_make_buffer_rsrc((void*)(((uint64_t)hi << 32) | lo), (short)0,
-                                           (int)__builtin_amdgcn_readfirstlane(bytes), 0x00020000);
-}
 constexpr uint32_t kOutside = 0x80000000u;  // an offset beyond any resource made here (tiles are below 64 MiB)
-constexpr int kNt = 2;                      // cache policy: non-temporal
 
 constexpr uint32_t kRoundLoads = 16;        // 1 KiB runs a wave loads per round
 constexpr uint32_t kHashWaves = 8;          // most waves per workgroup

@@ -173,6 +173,19 @@ struct HashParams {
   ScanDev scan;
 };
 
+struct ProbeParams {
+  const Tile* tiles;
+  uint32_t n_tiles;
+  const uint32_t* word_tile;  // tile of each bitmap word's first unit
+  uint64_t n_units;
+  uint64_t* zero_bm;
+  uint64_t *clear_a, *clear_b;  // arrays to clear on the side
+  uint64_t n_clear_a, n_clear_b;
+  uint32_t ushift;
+  uint32_t gshift;  // log2 of the units per group (6 or 4; set by the launcher, as n_groups)
+  uint64_t n_groups;
+};
+
 // Exclusive-scan sources.
 enum ScanSrcKind : uint32_t { kSrcKeepBits = 0, kSrcCounts = 1 };
 struct ScanSrc {
@@ -238,8 +251,7 @@ hipError_t launch_zero4(uint64_t* a, uint64_t na, uint64_t* b, uint64_t nb, uint
 // The hashing pass (kc_hash.hip); rows: most units per wave (16, 8 or 4); grid: waves (0: one per part of a tile).
 hipError_t launch_page_hash(const HashParams& p, bool gather, bool prior, bool scan, uint32_t rows, uint32_t grid,
                             uint32_t n_cu, hipStream_t s);
-hipError_t launch_probe_zero(const Tile* tiles, uint32_t n_tiles, uint64_t* zero_bm, uint32_t ushift,
-                             uint32_t grid, hipStream_t s);
+hipError_t launch_probe_zero(ProbeParams p, uint64_t n_words, uint32_t n_cu, hipStream_t s);
 hipError_t launch_scan(const ScanSrc& src, uint64_t* out, uint64_t* block_sums,
                        uint64_t* total_out, hipStream_t s);
 hipError_t launch_gather(const Tile* tiles, uint32_t n_tiles, const uint64_t* zero_bm,
@@ -362,6 +374,7 @@ struct kc_rangeset {
   std::vector<uint32_t> scan_range_tile;
   kc::Tile* scan_tiles = nullptr;
   uint32_t per_tile = 16;            // most units of a tile in `tiles`
+  uint32_t* word_tile = nullptr;     // tile of each bitmap word's first unit (device)
   uint32_t* hash_scan0 = nullptr;    // units above 4 KiB: the scan tile of each tile's first byte (device)
   void* dev = nullptr;
   kc::Tile* tiles = nullptr;

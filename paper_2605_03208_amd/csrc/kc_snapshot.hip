@@ -37,76 +37,103 @@ __global__ void k_zero4(uint64_t* a, uint64_t na, uint64_t* b, uint64_t nb, uint
 }
 
 // ------------------------------------------------------------ zero probe --
-// Exact zero bitmap.  A wave takes four tiles at a time, one lane per unit:
-// each lane reads the first 16 bytes of its unit; a unit whose first 16 bytes
-// are zero is then read by the whole wave (four such units at a time, 4 KiB of
-// each per round) until a non-zero byte shows or the unit ends.
-__global__ __launch_bounds__(64) void k_probe_zero(const Tile* tiles, uint32_t n_tiles,
-                                                   uint64_t* zero_bm, uint32_t ushift) {
-  const uint32_t lane = threadIdx.x, sub = lane >> 4, pl = lane & 15u;
-  const uint32_t unit = 1u << ushift, nsub = unit / kPage;
-  for (uint32_t t0 = blockIdx.x * 4u; t0 < n_tiles; t0 += gridDim.x * 4u) {
-    const uint32_t t = t0 + sub;
-    Tile tile{0, 0, 0};
-    if (t < n_tiles) tile = tiles[t];
-    const bool valid = pl < tile.npages;
-    const uint32_t len = valid ? unit_bytes(tile, pl, unit) : 0u;  // a partial unit is tested over its bytes only
-    const uint64_t unit_va = tile.va + ((uint64_t)pl << ushift);
-    const uint4 v = valid ? clip16(ld16(unit_va), 0u, len) : make_uint4(0, 0, 0, 0);
-    const bool cand = valid && !nz16(v);
-    uint64_t maybe = __ballot(cand && len == unit);
-    uint64_t maybe_part = __ballot(cand && len != unit);
-    uint64_t zero = 0;
-    while (maybe) {  // whole units, four at a time
-      uint32_t ln[4];
-      uint64_t pva[4];
-      uint32_t cnt = 0;
+// Exact zero bitmap of the units, written whole (nothing to clear first).  A
+// workgroup takes a group of 64 or 16 consecutive units: its first wave reads
+// the first 16 bytes of each, one lane per unit, and lists the units that begin
+// with zeros; the listed units' 4 KiB blocks are then shared out to the waves,
+// four blocks (16 KiB in flight) at a time, until a non-zero byte shows in the
+// unit or it ends.  A unit's tile is found from the tile of its bitmap word's
+// first unit: each lane holds one of the 64 tiles from there on, and every lane
+// searches them for its unit's.
+//
+// What bounds it: with most units non-zero, the one line of each unit that is
+// read, and a chain of four dependent loads per group, so there are as many
+// groups in flight as fit; with many zero units, their bytes.  Measured against
+// persistent waves of four tiles each (8 per CU), all the units of a tile run
+// through by one wave: 64 MiB with 30 % zero pages 23.5 -> 8.3 us, 1 MiB 5.9
+// -> 4.5, 8 GiB in units of 64 KiB 59 -> 50; 30 GiB of pages with 2.7 % zero 400
+// -> 373 us (7.8 million lines a page apart and 0.8 GiB of zeros).
+//
+// It also clears the two arrays that a closure scan accumulates into.
+constexpr uint32_t kProbeWaves = 16;
+
+__global__ __launch_bounds__(kProbeWaves * kWave) void k_probe_zero(ProbeParams p) {
+  __shared__ uint64_t unit_va[kWave];
+  __shared__ uint32_t unit_len[kWave], unit_at[kWave];  // of the listed units: bytes, place in the group
+  __shared__ unsigned long long listed, nonzero;
+  const uint32_t lane = threadIdx.x % kWave, wpb = blockDim.x / kWave;
+  const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const uint32_t unit = 1u << p.ushift, bshift = p.ushift - 12u, group = 1u << p.gshift;
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < p.n_clear_a + p.n_clear_b;
+       i += (uint64_t)gridDim.x * blockDim.x) {
+    if (i < p.n_clear_a) p.clear_a[i] = 0;
+    else p.clear_b[i - p.n_clear_a] = 0;
+  }
+  for (uint64_t gr = blockIdx.x; gr < p.n_groups; gr += gridDim.x) {
+    const uint64_t u0 = gr << p.gshift;
+    if (wv == 0) {
+      const uint32_t n = u0 < p.n_units ? (uint32_t)min(p.n_units - u0, (uint64_t)group) : 0u;
+      const uint32_t t0 = const_load32(p.word_tile + (u0 >> 6)), t = t0 + lane;
+      Tile tile{0, 0xFFFFFFFFu, 0, 0};
+      if (t < p.n_tiles) tile = p.tiles[t];
+      const uint32_t shape = (tile.npages << 24) | tile.last_len;  // npages 16 at most, last_len up to 2 MiB
+      const uint32_t u = (uint32_t)u0 + lane;
+      uint32_t at = 0;  // the last of the 64 tiles that starts at or before unit u
+#pragma unroll
+      for (uint32_t d = 32; d >= 1u; d >>= 1) at += (uint32_t)__shfl(tile.g, at + d, 64) <= u ? d : 0u;
+      const uint32_t j = u - (uint32_t)__shfl(tile.g, at, 64), sh = __shfl(shape, at, 64);
+      const uint64_t va = __shfl((unsigned long long)tile.va, at, 64) + ((uint64_t)j << p.ushift);
+      const bool valid = lane < n;
+      const uint32_t len = j + 1u == sh >> 24 ? sh & 0xFFFFFFu : unit;  // a partial unit is tested over its bytes only
+      const bool zeros = valid && !nz16(clip16(valid ? ld16(va) : make_uint4(0, 0, 0, 0), 0u, len));
+      const uint64_t m = __ballot(zeros);
+      if (zeros) {
+        const uint32_t i = (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+        unit_va[i] = va;
+        unit_len[i] = len;
+        unit_at[i] = lane;
+      }
+      if (lane == 0) {
+        listed = m;
+        nonzero = 0;
+      }
+    }
+    __syncthreads();
+    const uint32_t n_listed = (uint32_t)__popcll(listed), n_blocks = n_listed << bshift;
+    for (uint32_t b0 = wv * 4u; b0 < n_blocks; b0 += wpb * 4u) {
+      const uint64_t seen = *(volatile unsigned long long*)&nonzero;  // blocks of units known not to be zero: skipped
+      uint4 x[16];
+      uint32_t place[4], bytes[4];
 #pragma unroll
       for (uint32_t i = 0; i < 4; ++i) {
-        ln[i] = maybe ? (uint32_t)__builtin_ctzll(maybe) : 0u;
-        pva[i] = __shfl(unit_va, ln[i], 64);
-        if (maybe) {
-          maybe &= maybe - 1ull;
-          ++cnt;
-        }
-      }
-      uint32_t alive = (1u << cnt) - 1u;  // units with no non-zero byte seen yet
-      for (uint32_t b = 0; b < nsub && alive != 0u; ++b) {
-        uint4 x[16];
-#pragma unroll
-        for (uint32_t i = 0; i < 4; ++i)
-#pragma unroll
-          for (uint32_t j = 0; j < 4; ++j)
-            x[i * 4 + j] = ((alive >> i) & 1u) ? ld16nt(pva[i] + (uint64_t)b * kPage + j * 1024u + lane * 16u)
-                                               : make_uint4(0, 0, 0, 0);
-#pragma unroll
-        for (uint32_t i = 0; i < 4; ++i) {
-          const bool nzl = nz16(x[i * 4]) || nz16(x[i * 4 + 1]) || nz16(x[i * 4 + 2]) || nz16(x[i * 4 + 3]);
-          if (__ballot(nzl) != 0ull) alive &= ~(1u << i);
-        }
-      }
-#pragma unroll
-      for (uint32_t i = 0; i < 4; ++i)
-        if ((alive >> i) & 1u) zero |= 1ull << ln[i];
-    }
-    while (maybe_part) {  // partial last units (one per range at most), one at a time over their bytes
-      const uint32_t L = (uint32_t)__builtin_ctzll(maybe_part);
-      maybe_part &= maybe_part - 1ull;
-      const uint64_t pva = __shfl(unit_va, L, 64);
-      const uint32_t plen = __shfl(len, L, 64);
-      bool nzw = false;
-      for (uint32_t o0 = 0; o0 < plen && !nzw; o0 += kPage) {
-        bool nzl = false;
+        const uint32_t b = b0 + i, c = min(b >> bshift, n_listed - 1u), off = (b & ((1u << bshift) - 1u)) * kPage;
+        place[i] = unit_at[c];
+        const bool skip = b >= n_blocks || ((seen >> place[i]) & 1ull) != 0ull || off >= unit_len[c];
+        bytes[i] = skip ? 0u : min(unit_len[c] - off, kPage);
+        const __amdgpu_buffer_rsrc_t src = raw_rsrc(unit_va[c] + off, (bytes[i] + 15u) & ~15u);
 #pragma unroll
         for (uint32_t j = 0; j < 4; ++j) {
-          const uint32_t o = o0 + j * 1024u + lane * 16u;
-          if (o < plen) nzl = nzl || nz16(clip16(ld16nt(pva + o), o, plen));
+          const v4u v = __builtin_amdgcn_raw_buffer_load_b128(src, j * 1024u + lane * 16u, 0, kNt);
+          x[i * 4 + j] = make_uint4(v[0], v[1], v[2], v[3]);
         }
-        nzw = __ballot(nzl) != 0ull;
       }
-      if (!nzw) zero |= 1ull << L;
+      uint64_t found = 0;
+#pragma unroll
+      for (uint32_t i = 0; i < 4; ++i) {
+        bool nz = false;
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j) nz = nz || nz16(clip16(x[i * 4 + j], j * 1024u + lane * 16u, bytes[i]));
+        if (__ballot(nz) != 0ull) found |= 1ull << place[i];
+      }
+      if (found != 0ull && lane == 0) atomicOr(&nonzero, (unsigned long long)found);
     }
-    if (pl == 0 && t < n_tiles) or_page_bits(zero_bm, tile.g, tile.npages, (uint32_t)((zero >> (16u * sub)) & 0xFFFFull));
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      const uint64_t zero = listed & ~nonzero;
+      if (p.gshift == 6u) p.zero_bm[gr] = zero;
+      else reinterpret_cast<uint16_t*>(p.zero_bm)[gr] = (uint16_t)zero;
+    }
+    __syncthreads();  // the list is rewritten for the next group
   }
 }
 
@@ -552,11 +579,17 @@ hipError_t launch_fill_u64(uint64_t* p, uint64_t n, uint64_t v, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_probe_zero(const Tile* tiles, uint32_t n_tiles, uint64_t* zero_bm, uint32_t ushift, uint32_t grid,
-                             hipStream_t s) {
-  if (n_tiles == 0) return hipSuccess;
-  grid = std::max(1u, std::min(grid, n_tiles));
-  hipLaunchKernelGGL(k_probe_zero, dim3(grid), dim3(64), 0, s, tiles, n_tiles, zero_bm, ushift);
+hipError_t launch_probe_zero(ProbeParams p, uint64_t n_words, uint32_t n_cu, hipStream_t s) {
+  // Groups of 64 pages, or of 16 larger units (more groups: few units can be many bytes).
+  p.gshift = p.ushift == kMinUnitShift ? 6u : 4u;
+  p.n_groups = n_words << (6u - p.gshift);
+  if (p.n_groups == 0 && p.n_clear_a + p.n_clear_b == 0) return hipSuccess;
+  // Waves per group: so many that the chip has 16 per CU and that no wave has more than 256 KiB of zeros to read.
+  const uint64_t fill = 16ull * n_cu / std::max<uint64_t>(1, p.n_groups), zeros = 1ull << (p.gshift + p.ushift);
+  uint32_t wpb = 1;
+  while (wpb < kProbeWaves && (wpb < fill || (uint64_t)wpb << 18 < zeros)) wpb *= 2u;
+  const uint32_t grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(p.n_groups, 1u << 21));
+  hipLaunchKernelGGL(k_probe_zero, dim3(grid), dim3(wpb * kWave), 0, s, p);
   return hipGetLastError();
 }
 
