@@ -104,16 +104,19 @@ int make_scan(const kc_rangeset* rs, const kc_scan_args* sa, ScanDev* sd) {
   return KC_OK;
 }
 
-// Count-scan the per-tile out-of-range totals, emit the ordered list, write
+// Emit the ordered list of out-of-range words from the per-tile counts, write
 // the result struct.
 int finish_scan(kc_rangeset* rs, const kc_scan_args* sa, const ScanDev& sd, hipStream_t s) {
-  ScanSrc src{};
-  src.kind = kSrcCounts;
-  src.counts = rs->tile_oob;
-  src.n_items = rs->n_scan_tiles;
-  KC_HIP(launch_scan(src, rs->tile_prefix, rs->block_sums, rs->n_oob, s));
-  KC_HIP(launch_oob_emit(rs->scan_tiles, rs->n_scan_tiles, sd, rs->tile_prefix, rs->n_oob, sa->oob_d, sa->oob_cap,
-                         sa->res_d, rs->n_scan_words, s));
+  const bool in_line = rs->n_scan_tiles <= kInlineTiles;
+  if (!in_line) {
+    ScanSrc src{};
+    src.kind = kSrcCounts;
+    src.counts = rs->tile_oob;
+    src.n_items = rs->n_scan_tiles;
+    KC_HIP(launch_scan(src, rs->tile_prefix, rs->block_sums, rs->n_oob, s));
+  }
+  KC_HIP(launch_oob_emit(rs->scan_tiles, rs->n_scan_tiles, sd, in_line ? nullptr : rs->tile_prefix, sa->oob_d,
+                         sa->oob_cap, sa->res_d, rs->n_scan_words, s));
   return KC_OK;
 }
 
@@ -607,17 +610,22 @@ int kc_snapshot(kc_ctx* c, const kc_rangeset* crs, uint64_t seed, const uint64_t
     pp.n_clear_b = ((uint64_t)rs->n_scan_tiles + 1) / 2;
   }
   KC_HIP(launch_probe_zero(pp, rs->n_words, c->n_cu, s));
-  ScanSrc src{};
-  src.kind = kSrcKeepBits;
-  src.zero_bm = zero_bm_d;
-  src.n_pages = rs->n_pages;
-  src.n_items = rs->n_words;
-  KC_HIP(launch_scan(src, rs->word_prefix, rs->block_sums, n_kept_d, s));
+  const bool in_line = rs->n_words <= kInlineWords && rs->n_tiles > 0;
+  if (!in_line) {
+    ScanSrc src{};
+    src.kind = kSrcKeepBits;
+    src.zero_bm = zero_bm_d;
+    src.n_pages = rs->n_pages;
+    src.n_items = rs->n_words;
+    KC_HIP(launch_scan(src, rs->word_prefix, rs->block_sums, n_kept_d, s));
+  }
   HashParams hp{};
   hp.seed = seed;
   hp.hash = hash_d;
   hp.zero_bm = zero_bm_d;
-  hp.word_prefix = rs->word_prefix;
+  hp.word_prefix = in_line ? nullptr : rs->word_prefix;
+  hp.n_units = rs->n_pages;
+  hp.n_kept = n_kept_d;
   hp.packed = static_cast<uint8_t*>(packed_d);
   hp.page_va = page_va_d;
   hp.cap_pages = cap_pages;

@@ -25,6 +25,24 @@ __device__ __forceinline__ void mark_high(uint32_t& marks, uint32_t d, uint32_t 
       : "vcc");
 }
 
+// Units kept (zero bit clear) among the first n, at most 64 * kInlineWords: all words loaded at once.
+__device__ __forceinline__ uint32_t kept_before(const uint64_t* zero_bm, uint32_t n, uint32_t lane) {
+  constexpr uint32_t kEach = kInlineWords / kWave;
+  typedef unsigned int v2u __attribute__((ext_vector_type(2)));
+  const __amdgpu_buffer_rsrc_t src = raw_rsrc((uint64_t)zero_bm, (n + 63u) / 64u * 8u);
+  v2u w[kEach];
+#pragma unroll
+  for (uint32_t i = 0; i < kEach; ++i) w[i] = __builtin_amdgcn_raw_buffer_load_b64(src, (i * kWave + lane) * 8u, 0, 0);
+  uint32_t kept = 0;
+#pragma unroll
+  for (uint32_t i = 0; i < kEach; ++i) {
+    const uint32_t u = (i * kWave + lane) * 64u;  // the word's first unit
+    const uint64_t mine = u >= n ? 0ull : n - u >= 64u ? ~0ull : (1ull << (n - u)) - 1ull;
+    kept += (uint32_t)__popcll(~(((uint64_t)w[i][1] << 32) | w[i][0]) & mine);
+  }
+  return wave_sum_u32(kept);
+}
+
 // One wave hashes up to ROWS units of a tile: lane quad q takes unit (row) q,
 // lane k of the quad runs XXH64 accumulator k over the words 8k + 32s of each
 // stripe s (the four accumulators are serial over a unit, so a unit never takes
@@ -90,10 +108,12 @@ __global__ __launch_bounds__(kHashWaves * kWave) __attribute__((amdgpu_waves_per
   const uint32_t k = lane & 3u, lane16 = lane * 16u;
   const uint32_t q = min(lane >> 2, ROWS - 1u);  // this lane's row
   const uint32_t ushift = p.ushift, unit = 1u << ushift;
-  if (SCAN) {
+  bool table_in = false;  // the same in every wave at the barrier: each gets there once, whether it has items or not
+  auto load_table = [&] {
     load_wide_fences(p.scan.rt, threadIdx.x, blockDim.x);
     __syncthreads();  // the only workgroup barrier: the waves share nothing else
-  }
+    table_in = true;
+  };
   uint32_t n_ptr = 0, n_in = 0;  // of this lane
   // the window's upper halves: a word whose upper half is not among them is not pointer-like
   const uint32_t win_hi = (uint32_t)(p.scan.lo >> 32);
@@ -119,7 +139,10 @@ __global__ __launch_bounds__(kHashWaves * kWave) __attribute__((amdgpu_waves_per
         const uint64_t g = (uint64_t)g0 + lane;
         const uint64_t zw = p.zero_bm[g >> 6];
         kept = ((zw >> (g & 63u)) & 1ull) == 0ull;
-        slot = p.word_prefix[g >> 6] + (uint64_t)__popcll(~zw & ((1ull << (g & 63u)) - 1ull));
+        if (p.word_prefix) slot = p.word_prefix[g >> 6] + (uint64_t)__popcll(~zw & ((1ull << (g & 63u)) - 1ull));
+      }
+      if (!p.word_prefix) {  // few words: their kept units are counted here
+        slot = kept_before(p.zero_bm, g0, lane) + (uint32_t)__popcll(__ballot(kept) & ((1ull << lane) - 1ull));
       }
       keep = (uint32_t)__ballot(kept);
       if (kept && slot < p.cap_pages) p.page_va[slot] = va + ((uint64_t)lane << ushift);
@@ -166,6 +189,7 @@ __global__ __launch_bounds__(kHashWaves * kWave) __attribute__((amdgpu_waves_per
       else atomicAdd(&p.scan.tile_oob[scan0 + tag], 1u);
     };
     load(0u);
+    if (SCAN && !table_in) load_table();  // while the first loads are under way: 8 GiB 2.77 ms, table first 2.81
 #pragma unroll 1
     for (uint32_t c = 0; c < n_rounds; ++c) {
       uint32_t marks = 0;  // bit 31 - (2i + h): word h of this lane's 16 bytes of run i may be pointer-like
@@ -262,7 +286,12 @@ __global__ __launch_bounds__(kHashWaves * kWave) __attribute__((amdgpu_waves_per
       if (lane == 0) or_page_bits(p.changed_bm, g0, np, ch);
     }
   }
+  if (GATHER && !p.word_prefix && blockIdx.x == 0 && wv == 0) {  // with the prefixes goes the total
+    const uint32_t n = kept_before(p.zero_bm, (uint32_t)p.n_units, lane);
+    if (lane == 0) *p.n_kept = n;
+  }
   if (SCAN) {
+    if (!table_in) load_table();
     const uint32_t a = wave_sum_u32(n_ptr), b = wave_sum_u32(n_in);
     if (lane == 0) add_scan_counts(p.scan.counts, blockIdx.x * wpb + wv, a, b);
   }

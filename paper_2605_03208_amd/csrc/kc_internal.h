@@ -165,7 +165,9 @@ struct HashParams {
   uint64_t* hash;
   uint64_t* zero_bm;       // output, or input when gathering
   uint64_t* changed_bm;
-  const uint64_t* word_prefix;  // keep prefix per bitmap word (gathering)
+  const uint64_t* word_prefix;  // keep prefix per bitmap word (gathering; null: counted by each wave, with n_kept)
+  uint64_t n_units;
+  uint64_t* n_kept;
   uint8_t* packed;
   uint64_t* page_va;
   uint64_t cap_pages;
@@ -185,6 +187,14 @@ struct ProbeParams {
   uint32_t gshift;  // log2 of the units per group (6 or 4; set by the launcher, as n_groups)
   uint64_t n_groups;
 };
+
+// Up to this many bitmap words, the waves of a gathering hash pass count the kept units before theirs themselves.
+// 64 MiB: the pass takes 1.3 us more, the launch that is saved took 4.2 and a gap; each wave loads all words at once.
+constexpr uint64_t kInlineWords = 512;
+// Up to this many tiles, the blocks that list out-of-range words count those before theirs themselves.
+// 8 GiB: 9.8 us; with a prefix per tile 9.0, and three launches of 4.6 us to make it.  Every block with entries reads
+// all the counts before its run, so beyond 12 GiB the three launches do it.
+constexpr uint32_t kInlineTiles = 3u << 16;
 
 // Exclusive-scan sources.
 enum ScanSrcKind : uint32_t { kSrcKeepBits = 0, kSrcCounts = 1 };
@@ -277,8 +287,8 @@ hipError_t launch_region_diff(const Tile* tiles, uint32_t n_tiles, const RangeTa
                               const uint64_t* gold_n_kept, uint64_t cap, const uint8_t* gold_packed,
                               kc_region_diff_result* res, uint32_t ushift, uint32_t grid, hipStream_t s);
 hipError_t launch_oob_emit(const Tile* tiles, uint32_t n_tiles, const ScanDev& sd,
-                           const uint64_t* tile_prefix, const uint64_t* n_oob, kc_oob* oob,
-                           uint64_t cap, kc_scan_result* res, uint64_t n_words, hipStream_t s);
+                           const uint64_t* tile_prefix, kc_oob* oob, uint64_t cap, kc_scan_result* res,
+                           uint64_t n_words, hipStream_t s);
 // wide: workgroups of 1024 threads.  direct: every pair is one tile and the pass writes the reports (else the
 // finalize does).
 hipError_t launch_compare(const CmpPairDev* pairs, const CmpTileDev* tiles, uint32_t n_tiles, uint32_t tile_bytes,
