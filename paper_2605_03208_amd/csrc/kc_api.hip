@@ -313,7 +313,6 @@ int kc_rangeset_create_unit(kc_ctx* c, const kc_range* ranges, uint32_t n, uint6
   std::vector<uint64_t> bases(n), ends(n);
   for (uint32_t i = 0; i < n; ++i) {
     rs->n_scan_words += ranges[i].size / 8;
-    rs->n_ragged += (ranges[i].size & (unit - 1)) != 0 ? 1u : 0u;
     bases[i] = ranges[i].base;
     ends[i] = ranges[i].base + ranges[i].size;
   }
@@ -651,7 +650,7 @@ int kc_restore(kc_ctx* c, const kc_rangeset* crs, const uint64_t* zero_bm_d, con
   KC_HIP(launch_restore_zero(rs->tiles, rs->n_tiles, zero_bm_d, changed_bm_d, bad, rs->ushift, grid, s));
   KernelTimer timer(c, KC_OP_RESTORE, s);
   KC_HIP(launch_restore_scatter(rs->rt, static_cast<const uint8_t*>(packed_d), page_va_d, n_kept_d, cap_pages,
-                                bad, rs->n_ragged > 0, changed_bm_d != nullptr, rs->ushift, grid, s));
+                                bad, changed_bm_d != nullptr, rs->ushift, s));
   return KC_OK;
 }
 

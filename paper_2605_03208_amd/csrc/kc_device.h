@@ -143,9 +143,6 @@ __device__ __forceinline__ int32_t range_index(uint64_t w, const FenceLds& f, co
 }
 
 // True iff w lies in [base_r, end_r) for some range r.
-__device__ __forceinline__ bool in_ranges(uint64_t w, const FenceLds& f, const RangeTable& rt) {
-  return range_index(w, f, rt) >= 0;
-}
 
 // ------------------------------------------------------------ wide table --
 // Kernels whose workgroups hold several independent waves share one copy of

@@ -274,7 +274,7 @@ hipError_t launch_restore_zero(const Tile* tiles, uint32_t n_tiles, const uint64
 hipError_t launch_restore_scatter(const RangeTable& rt, const uint8_t* packed,
                                   const uint64_t* page_va, const uint64_t* n_kept,
                                   uint64_t cap_pages, unsigned long long* n_bad,
-                                  bool ragged, bool delta, uint32_t ushift, uint32_t grid, hipStream_t s);
+                                  bool delta, uint32_t ushift, hipStream_t s);
 hipError_t launch_closure(const Tile* tiles, uint32_t n_tiles, uint32_t tile0,
                           const ScanDev& sd, uint32_t grid, uint32_t n_cu, hipStream_t s);
 hipError_t launch_pointer_graph(const Tile* tiles, uint32_t n_tiles, uint64_t lo, uint64_t span,
@@ -374,7 +374,6 @@ struct kc_rangeset {
   uint32_t ushift = 12;              // log2 of the hash unit; n_pages, n_words and the tiles count units
   uint64_t n_pages = 0, n_words = 0;
   uint64_t n_scan_words = 0;         // 8-byte words wholly inside the ranges
-  uint32_t n_ragged = 0;             // ranges whose last unit is partial
   std::vector<uint32_t> range_tile;  // first tile of each range (n + 1)
   uint64_t win_lo = 0, win_hi = 0;   // default pointer window
   std::vector<kc_range> host_ranges;

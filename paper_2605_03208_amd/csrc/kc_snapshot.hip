@@ -357,9 +357,11 @@ __global__ __launch_bounds__(64) void k_restore_zero(const Tile* tiles, uint32_t
 // belongs to slot b >> (ushift - 12); the wave reads that slot's page-VA entry
 // (one scalar load for the whole wave), validates it (4 KiB aligned, inside a
 // range, the start of a unit of that range) with a scalar search of the range
-// set's arrays, and copies the block, if it lies wholly inside the range, with
-// four 16-byte loads and stores per lane.  Workgroups are dispatched in block order, so the waves in flight cover
-// one compact, advancing window of both buffers: against a persistent grid
+// set's arrays, and copies the block with four 16-byte loads and stores per
+// lane; of the last block of a range, only the bytes inside it (a second pass
+// over the slots for these took 41 of 760 us on 2 GiB in 4096 ranges).
+// Workgroups are dispatched in block order, so the waves in flight cover one
+// compact, advancing window of both buffers: against a persistent grid
 // striding four-block groups over the snapshot (with a range table loaded into
 // LDS per workgroup) the one-wave form runs at the speed of a plain copy
 // kernel between the same buffers.  Four-wave workgroups copy a full snapshot
@@ -382,9 +384,18 @@ __global__ __launch_bounds__(WAVES * kWave) void k_restore_scatter(RangeTable rt
     bool good = false, ok = false;
     if ((va & (kPage - 1)) == 0) {
       const RangeHit r = range_find_uniform(va, rt);
-      if (r.a >= 0) {  // of a range's partial last unit, the bytes past its last whole block go to k_restore_tail
+      if (r.a >= 0) {
         good = ((va - r.base) & (unit - 1ull)) == 0ull;
-        ok = good && va + (sub << 12) + kPage <= r.end;
+        const uint64_t at = va + (sub << 12);
+        ok = good && at + kPage <= r.end;
+        if (good && !ok && at < r.end) {  // the last bytes of a range, never past its end
+          const uint32_t len = (uint32_t)(r.end - at);
+#pragma unroll
+          for (uint32_t j = 0; j < 4; ++j) {
+            const uint32_t o = j * 1024u + lane * 16u;
+            if (o < len) st_bytes(at + o, ld16nt((uint64_t)packed + blk * kPage + o), len - o);
+          }
+        }
       }
     }
     if (!good && sub == 0 && lane == 0) atomicAdd(n_bad, 1ull);  // counted once per slot
@@ -395,46 +406,6 @@ __global__ __launch_bounds__(WAVES * kWave) void k_restore_scatter(RangeTable rt
     for (uint32_t j = 0; j < 4; ++j) x[j] = ld16nt(src + j * 1024u);
 #pragma unroll
     for (uint32_t j = 0; j < 4; ++j) st16nt(dst + j * 1024u, x[j]);
-  }
-}
-
-// Packed units bound for a range's partial last unit: the restore scatter
-// copies its whole 4 KiB blocks; here only its last bytes past them are
-// written, never past the range's end.  One lane per slot finds such units;
-// the wave copies each one's remainder (under 4 KiB).
-__global__ __launch_bounds__(64) void k_restore_tail(RangeTable rt, const uint8_t* packed, const uint64_t* page_va,
-                                                     const uint64_t* n_kept, uint64_t cap, uint32_t ushift) {
-  __shared__ FenceLds fences;
-  const uint32_t lane = threadIdx.x;
-  const uint64_t unit = 1ull << ushift;
-  load_fences(fences, rt, lane, kWave);
-  __syncthreads();
-  const uint64_t n = min(*n_kept, cap);
-  for (uint64_t s0 = (uint64_t)blockIdx.x * 64u; s0 < n; s0 += (uint64_t)gridDim.x * 64u) {
-    uint64_t va = 0;
-    uint32_t len = 0;
-    if (s0 + lane < n) {
-      va = page_va[s0 + lane];
-      const int32_t a = (va & (kPage - 1)) == 0 ? range_index(va, fences, rt) : -1;
-      if (a >= 0) {
-        const uint64_t base = rt.stride == 1u ? fences.base[a] : ld8g(rt.base + a);
-        const uint64_t end = rt.stride == 1u ? fences.end[a] : ld8g(rt.end + a);
-        if (((va - base) & (unit - 1ull)) == 0ull && va + unit > end && ((end - va) & (kPage - 1)) != 0ull)
-          len = (uint32_t)(end - va);
-      }
-    }
-    for (uint64_t m = __ballot(len != 0u); m != 0ull; m &= m - 1ull) {
-      const int32_t L = __ffsll((long long)m) - 1;
-      const uint64_t dva = __shfl((unsigned long long)va, L, 64);
-      const uint32_t dlen = __shfl(len, L, 64);
-      const uint64_t src = (uint64_t)packed + ((s0 + (uint64_t)L) << ushift);
-      const uint32_t o0 = dlen & ~(kPage - 1u);  // the bytes before it went with the scatter's whole blocks
-#pragma unroll
-      for (uint32_t j = 0; j < 4; ++j) {
-        const uint32_t o = o0 + j * 1024u + lane * 16u;
-        if (o < dlen) st_bytes(dva + o, ld16nt(src + o), dlen - o);  // never past the range's end
-      }
-    }
   }
 }
 
@@ -708,17 +679,12 @@ void launch_scatter_waves(const RangeTable& rt, const uint8_t* packed, const uin
 
 hipError_t launch_restore_scatter(const RangeTable& rt, const uint8_t* packed, const uint64_t* page_va,
                                   const uint64_t* n_kept, uint64_t cap_pages, unsigned long long* n_bad,
-                                  bool ragged, bool delta, uint32_t ushift, uint32_t grid, hipStream_t s) {
+                                  bool delta, uint32_t ushift, hipStream_t s) {
   if (cap_pages == 0) return hipSuccess;
   if (delta)
     launch_scatter_waves<4>(rt, packed, page_va, n_kept, cap_pages, n_bad, ushift, s);
   else
     launch_scatter_waves<1>(rt, packed, page_va, n_kept, cap_pages, n_bad, ushift, s);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || !ragged) return e;
-  const uint64_t groups64 = (cap_pages + 63) / 64;
-  const uint32_t grid_t = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(groups64, 1024));
-  hipLaunchKernelGGL(k_restore_tail, dim3(grid_t), dim3(64), 0, s, rt, packed, page_va, n_kept, cap_pages, ushift);
   return hipGetLastError();
 }
 
