@@ -13,7 +13,7 @@ namespace {
 constexpr uint32_t kOutside = 0x80000000u;  // an offset beyond any resource made here (tiles are below 64 MiB)
 
 constexpr uint32_t kRoundLoads = 16;        // 1 KiB runs a wave loads per round
-constexpr uint32_t kHashWaves = 8;          // most waves per workgroup
+constexpr uint32_t kHashWaves = 4;          // most waves per workgroup
 constexpr uint32_t kLdsBytes = 160u << 10;  // of a CU
 constexpr uint64_t kMaxThreads = (1ull << 32) - 1;  // of a launch
 
@@ -82,7 +82,7 @@ __device__ __forceinline__ uint32_t kept_before(const uint64_t* zero_bm, uint32_
 // atomics.
 //
 // The waves of a workgroup are independent; with the closure scan they share
-// one wide range table.  LDS, all dynamic: the table, then per wave its stage,
+// one range table.  LDS, all dynamic: the table, then per wave its stage,
 // a partial unit's last bytes and the queue (hash_lds_per_wave).
 constexpr uint32_t kHashQueue = 128;  // below 64 left over, and up to 64 of one push
 __host__ __device__ constexpr uint32_t stage_stride(uint32_t rows) {
@@ -114,6 +114,7 @@ __global__ __launch_bounds__(kHashWaves * kWave) __attribute__((amdgpu_waves_per
     __syncthreads();  // the only workgroup barrier: the waves share nothing else
     table_in = true;
   };
+  if (SCAN && !GATHER) load_table();
   uint32_t n_ptr = 0, n_in = 0;  // of this lane
   // the window's upper halves: a word whose upper half is not among them is not pointer-like
   const uint32_t win_hi = (uint32_t)(p.scan.lo >> 32);
@@ -189,7 +190,9 @@ __global__ __launch_bounds__(kHashWaves * kWave) __attribute__((amdgpu_waves_per
       else atomicAdd(&p.scan.tile_oob[scan0 + tag], 1u);
     };
     load(0u);
-    if (SCAN && !table_in) load_table();  // while the first loads are under way: 8 GiB 2.77 ms, table first 2.81
+    // Snapshots load the table while the first loads are under way (8 GiB 2.78 ms, table first 2.85); for the others
+    // it goes first (1.39 ms, else 1.42).
+    if (SCAN && GATHER && !table_in) load_table();
 #pragma unroll 1
     for (uint32_t c = 0; c < n_rounds; ++c) {
       uint32_t marks = 0;  // bit 31 - (2i + h): word h of this lane's 16 bytes of run i may be pointer-like
@@ -299,25 +302,29 @@ __global__ __launch_bounds__(kHashWaves * kWave) __attribute__((amdgpu_waves_per
 
 }  // namespace
 
-hipError_t launch_page_hash(const HashParams& p, bool gather, bool prior, bool scan, uint32_t rows, uint32_t grid,
+hipError_t launch_page_hash(HashParams p, bool gather, bool prior, bool scan, uint32_t rows, uint32_t grid,
                             uint32_t n_cu, hipStream_t s) {
   const uint64_t n_items = (uint64_t)p.n_tiles << p.sub_shift;
   if (n_items == 0) return hipSuccess;
-  // Waves per workgroup: one while all fit on the chip at once (8 per CU; 520 waves of 512 KiB units: 0.73 ms, in
-  // pairs 0.92), else four (30 GiB of 4 KiB pages, hash only: 4.69 ms; one by one 4.82).  With a scan a workgroup
-  // shares one range table (2 KiB and 16 bytes a range, 66 KiB at most): four waves while two such workgroups fit a
-  // CU's LDS, else as many as fit beside one table (8 up to 800 ranges, 5 from 4096 on).
-  const uint32_t per = hash_lds_per_wave(rows, scan), table = scan ? (uint32_t)wide_lds_bytes(p.scan.rt) : 0u;
+  // The table of up to 256 fences (6 KiB at most) serves the scan: what a larger one saves in searches, it costs in
+  // waves per CU and in loading.  Hash only, 2 GiB in 4096 ranges, 1 % pointers 385 us, with 4096 fences 504; 2 GB in
+  // 1422 ranges, 0.1 % pointers 331 / 377; snapshots of the first 745 / 858.
+  RangeTable& rt = p.scan.rt;
+  rt.bucket_w = rt.bucket;
+  rt.stride_w = rt.stride;
+  rt.n_fence_w = rt.n_fence;
+  // Waves per workgroup: one while there are few, which spreads them over the SIMDs (1 GiB in 512 KiB units, 520 waves:
+  // 0.73 ms, in pairs 0.92; with a scan 0.82 / 1.01), else four (30 GiB of 4 KiB pages, hash only: 4.69 ms; one by one
+  // 4.82), which with a scan share the range table.
+  const uint32_t per = hash_lds_per_wave(rows, scan), table = scan ? (uint32_t)wide_lds_bytes(rt) : 0u;
   uint64_t waves = grid == 0u ? n_items : std::min<uint64_t>(grid, n_items);  // 0: one item per wave
   uint32_t wpb = 4;
-  if (scan && 2u * (table + wpb * per) > kLdsBytes) wpb = std::min(kHashWaves, (kLdsBytes - table) / per);
-  if (!scan && waves <= 8ull * n_cu) wpb = 1;
-  if (waves < (uint64_t)wpb * n_cu) wpb = (uint32_t)std::max<uint64_t>(1u, waves / n_cu);  // spread over the CUs
+  if (waves <= (scan ? 4ull : 8ull) * n_cu) wpb = 1;
   const size_t lds = table + (size_t)wpb * per;
-  // A large table is not loaded again for every workgroup's worth of tiles: the waves that fit on the chip stride over
-  // them (2 GiB in 4096 ranges: 0.85 ms, one item per wave 0.98).
-  if (grid == 0u && table > kLdsBytes / 10u)
-    waves = std::min(waves, (uint64_t)(kLdsBytes / lds) * wpb * n_cu);
+  // Hash only with a scan: the waves that fit on the chip stride over the tiles and load the table once (the 2 GiB
+  // above: 385 us, one item per wave 474; 1 GiB in 100 ranges 200 / 206).  Snapshots stay in address order (1 GiB
+  // 348 us, striding 401).
+  if (grid == 0u && scan && !gather) waves = std::min(waves, (uint64_t)(kLdsBytes / lds) * wpb * n_cu);
   const uint32_t blocks = (uint32_t)std::min<uint64_t>((waves + wpb - 1) / wpb, kMaxThreads / (wpb * kWave));
 #define KC_HASH_CASE(G, P, S, N)                                                                     \
   if (gather == G && prior == P && scan == S && rows == N) {                                         \

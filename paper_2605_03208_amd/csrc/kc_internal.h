@@ -259,7 +259,7 @@ hipError_t launch_fill_u64(uint64_t* p, uint64_t n, uint64_t v, hipStream_t s);
 hipError_t launch_zero4(uint64_t* a, uint64_t na, uint64_t* b, uint64_t nb, uint64_t* c, uint64_t nc, uint64_t* d,
                         uint64_t nd, hipStream_t s);
 // The hashing pass (kc_hash.hip); rows: most units per wave (16, 8 or 4); grid: waves (0: one per part of a tile).
-hipError_t launch_page_hash(const HashParams& p, bool gather, bool prior, bool scan, uint32_t rows, uint32_t grid,
+hipError_t launch_page_hash(HashParams p, bool gather, bool prior, bool scan, uint32_t rows, uint32_t grid,
                             uint32_t n_cu, hipStream_t s);
 hipError_t launch_probe_zero(ProbeParams p, uint64_t n_words, uint32_t n_cu, hipStream_t s);
 hipError_t launch_scan(const ScanSrc& src, uint64_t* out, uint64_t* block_sums,
