@@ -785,25 +785,32 @@ uint32_t elem_size(uint32_t dtype) {
 }
 
 // Tuned tile size, else 64 KiB, halved (down to 16 KiB) while the pairs would
-// give fewer than eight tiles per compute unit: small batches still spread
-// over the whole chip.  The smallest batches keep 64 KiB (kCompareWideTile).
+// give fewer than two tiles per compute unit: small batches still spread over
+// the chip, and no further, since every workgroup's end has its cost (11.3 % of
+// the elements off, tiles of 16 / 32 / 64 KiB: 16 pairs of 1 MiB 37 / 31 / 38 us,
+// 40 of 1 MiB of f32 43 / 36 / 35).  Small pairs keep 64 KiB (kCompareWideTile).
 uint32_t compare_tile_bytes(const kc_ctx* c, const kc_pair* pairs, uint32_t n_pairs) {
   if (c->tune[KC_OP_COMPARE].tile_bytes) return c->tune[KC_OP_COMPARE].tile_bytes;
-  uint64_t total = 0, wide_tiles = 0;
+  uint64_t total = 0, largest = 0;
   for (uint32_t i = 0; i < n_pairs; ++i) {
     if (pairs[i].dtype > KC_I64 || pairs[i].n_elems > (1ull << 60)) continue;  // refused later
     const uint64_t nb = pairs[i].n_elems * elem_size(pairs[i].dtype);
     total += nb;
-    wide_tiles += nb == 0 ? 1 : (nb + kCompareWideTile - 1) / kCompareWideTile;
+    largest = std::max(largest, nb);
   }
-  if (compare_wide(c, wide_tiles, kCompareWideTile)) return kCompareWideTile;
+  if (n_pairs <= c->n_cu && largest <= kCompareWideTile) return kCompareWideTile;
   uint32_t tb = 64u << 10;
-  while (tb > (16u << 10) && total / tb < 8ull * c->n_cu) tb >>= 1;
+  while (tb > (16u << 10) && total / tb < 2ull * c->n_cu) tb >>= 1;
   return tb;
 }
 
-bool compare_wide(const kc_ctx* c, uint64_t n_tiles, uint32_t tile_bytes) {
-  return n_tiles <= c->n_cu && tile_bytes >= kCompareWideTile;
+bool compare_wide(const kc_ctx* c, uint64_t n_pairs, uint64_t n_tiles, uint32_t tile_bytes) {
+  return n_pairs == n_tiles && n_tiles <= c->n_cu && tile_bytes >= kCompareWideTile;
+}
+
+uint32_t compare_grid(const kc_ctx* c, uint64_t n_tiles, uint32_t tile_bytes) {
+  const uint64_t per_cu = n_tiles * tile_bytes / std::max(1u, c->n_cu);
+  return grid_for(c, KC_OP_COMPARE, per_cu < kCompareFewBytes ? kCompareGridPerCu / 2u : kCompareGridPerCu);
 }
 
 }  // namespace kc
@@ -820,7 +827,7 @@ int plan_pairs(const kc_pair* pairs, uint32_t n_pairs, uint32_t tile_bytes, std:
     if (!(pr.atol >= 0.0) || !(pr.rtol >= 0.0)) return KC_EINVAL;  // negative or NaN tolerances
     if (pr.n_elems > 0) {
       if (pr.cand_d == nullptr || pr.gold_d == nullptr) return KC_EINVAL;
-      // element-aligned buffers; those not 16-byte aligned take the element-wise path
+      // element-aligned buffers
       if ((reinterpret_cast<uintptr_t>(pr.cand_d) | reinterpret_cast<uintptr_t>(pr.gold_d)) & (elem_size(pr.dtype) - 1u))
         return KC_EALIGN;
     }
@@ -864,7 +871,7 @@ void fill_pair_tables(const kc_pair* pairs, uint32_t n_pairs, const std::vector<
 int run_compare(kc_ctx* c, const CmpPairDev* dpairs, const CmpTileDev* dtiles, const std::vector<uint64_t>& tile_off,
                 uint32_t n_pairs, uint32_t tile_bytes, unsigned long long* dacc, uint64_t acc_words, bool* acc_dirty,
                 kc_cmp_result* res_d, hipStream_t s) {
-  const uint32_t grid = grid_for(c, KC_OP_COMPARE, kCompareGridPerCu);
+  const uint32_t grid = compare_grid(c, tile_off[n_pairs], tile_bytes);
   const bool direct = tile_off[n_pairs] == n_pairs;  // every pair one tile
   if (*acc_dirty) KC_HIP(launch_fill_u64(reinterpret_cast<uint64_t*>(dacc), acc_words, 0, s));
   *acc_dirty = true;
@@ -872,7 +879,7 @@ int run_compare(kc_ctx* c, const CmpPairDev* dpairs, const CmpTileDev* dtiles, c
     KernelTimer timer(c, KC_OP_COMPARE, s);
     if (!c->tune[KC_OP_COMPARE].per_item) {
       KC_HIP(launch_compare(dpairs, dtiles, (uint32_t)tile_off[n_pairs], tile_bytes, dacc, res_d, grid,
-                            compare_wide(c, tile_off[n_pairs], tile_bytes), direct, s));
+                            compare_wide(c, n_pairs, tile_off[n_pairs], tile_bytes), direct, s));
     } else {
       for (uint32_t i = 0; i < n_pairs; ++i)
         KC_HIP(launch_compare(dpairs, dtiles + tile_off[i], (uint32_t)(tile_off[i + 1] - tile_off[i]), tile_bytes,

@@ -679,7 +679,6 @@ __global__ __launch_bounds__(64) void k_compare_args_finalize(CmpArgPairs a, uns
   }
 #define KC_COMPARE_LAUNCH(KERNEL, ...)              \
   KC_COMPARE_CASE(KERNEL, true, true, __VA_ARGS__)  \
-  KC_COMPARE_CASE(KERNEL, true, false, __VA_ARGS__) \
   KC_COMPARE_CASE(KERNEL, false, true, __VA_ARGS__) \
   KC_COMPARE_CASE(KERNEL, false, false, __VA_ARGS__)
 

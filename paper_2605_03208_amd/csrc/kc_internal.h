@@ -238,13 +238,17 @@ static_assert(sizeof(CmpArgPairs) <= 3072, "kernel arguments");
 // one.  Each workgroup reads one run of consecutive tiles.  Measured at 2 / 4 /
 // 8 / 16 per CU: 10,000 uneven pairs of 8 GiB a side, 1e-4 of the elements off,
 // 2.48 / 2.52 / 2.54 / 2.57 ms; 768 MiB a side of mixed types with 11.3 % off
-// 0.47 / 0.39 / 0.35 / 0.35 ms.
+// 0.47 / 0.39 / 0.35 / 0.35 ms.  With less than 1 MiB of tiles per CU, half as
+// many: the end of a run, and the adds of all workgroups at one pair's
+// accumulators, weigh more (4 / 8 per CU, 11.3 % off: 1000 pairs of 128 KiB 76 /
+// 100 us, 5 pairs of 167 MiB in all 119 / 135; 417 pairs of 548 MiB 301 / 293).
 constexpr uint32_t kCompareGridPerCu = 8;
+constexpr uint64_t kCompareFewBytes = 1u << 20;
 
-// Tile of a small compare: when tiles of this size are no more than the CUs,
-// each gets a workgroup of 1024 threads, which reads it in one round (64 KiB a
-// side), and if no pair is larger the pass writes the reports itself.  16 pairs
-// of 64 KiB: 8.7 us a call, 10.5 in four 16 KiB tiles each and a second kernel.
+// Tile of a small compare: when the pairs are no more than the CUs and none is
+// larger than this, each gets a workgroup of 1024 threads, which reads it in one
+// round (64 KiB a side) and writes its report itself.  16 pairs of 64 KiB: 8.7 us
+// a call, 10.5 in four 16 KiB tiles each and a second kernel.
 constexpr uint32_t kCompareWideTile = 64u << 10;
 
 constexpr uint32_t kAccWords = 64;  // per-pair accumulator words
@@ -305,7 +309,8 @@ hipError_t launch_compare_args(const CmpArgPairs& a, uint32_t tile_bytes, unsign
 uint32_t grid_for(const kc_ctx* c, uint32_t op, uint32_t fallback_per_cu);  // persistent grid of an op
 uint32_t elem_size(uint32_t dtype);                                         // bytes of one element
 uint32_t compare_tile_bytes(const kc_ctx* c, const kc_pair* pairs, uint32_t n_pairs);
-bool compare_wide(const kc_ctx* c, uint64_t n_tiles, uint32_t tile_bytes);  // whether 1024-thread workgroups fit it
+bool compare_wide(const kc_ctx* c, uint64_t n_pairs, uint64_t n_tiles, uint32_t tile_bytes);  // 1024-thread workgroups
+uint32_t compare_grid(const kc_ctx* c, uint64_t n_tiles, uint32_t tile_bytes);
 
 // ---- the compare that allocates nothing (kc_noalloc.hip) ---------------------
 // Looks up, once per device, the device address of the static scratch array

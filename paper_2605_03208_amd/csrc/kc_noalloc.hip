@@ -68,7 +68,7 @@ int kc_compare_noalloc(kc_ctx* c, const kc_pair* pairs, uint32_t n_pairs, kc_cmp
     if (!(pr.atol >= 0.0) || !(pr.rtol >= 0.0)) return KC_EINVAL;
     if (pr.n_elems > 0) {
       if (pr.cand_d == nullptr || pr.gold_d == nullptr) return KC_EINVAL;
-      // element-aligned buffers; those not 16-byte aligned take the element-wise path
+      // element-aligned buffers
       if ((reinterpret_cast<uintptr_t>(pr.cand_d) | reinterpret_cast<uintptr_t>(pr.gold_d)) & (elem_size(pr.dtype) - 1u))
         return KC_EALIGN;
     }
@@ -112,9 +112,9 @@ int kc_compare_noalloc(kc_ctx* c, const kc_pair* pairs, uint32_t n_pairs, kc_cmp
       a.tile_end[j] = (uint32_t)t;
     }
     a.n_tiles = (uint32_t)t;
-    const uint32_t grid = grid_for(c, KC_OP_COMPARE, kCompareGridPerCu);
+    const uint32_t grid = compare_grid(c, t, tile_bytes);
     KC_HIP(launch_compare_args(a, tile_bytes, acc + (uint64_t)b0 * kAccWords, res_d + b0, grid,
-                               compare_wide(c, t, tile_bytes), s));
+                               compare_wide(c, a.n, t, tile_bytes), s));
   }
   return KC_OK;
 }
