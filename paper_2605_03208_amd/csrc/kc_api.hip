@@ -687,7 +687,7 @@ int kc_region_diff(kc_ctx* c, const kc_rangeset* crs, uint64_t seed, const uint6
   KernelTimer timer(c, KC_OP_REGION_DIFF, s);
   KC_HIP(launch_region_diff(rs->tiles, rs->n_tiles, rs->rt, changed_bm_d, gold_zero_bm_d, rs->word_prefix,
                             gold_page_va_d, gold_n_kept_d, cap_pages, static_cast<const uint8_t*>(gold_packed_d),
-                            res_d, rs->ushift, grid_for(c, KC_OP_REGION_DIFF, 8), s));
+                            res_d, rs->ushift, grid_for(c, KC_OP_REGION_DIFF, 16), c->n_cu, s));
   return KC_OK;
 }
 
