@@ -14,14 +14,14 @@
 // What bounds it: memory while few elements differ, the exact path's
 // instructions when many do.  So that path holds no division unless the
 // relative error is about to grow (see rel_may_grow), keeps the running maxima
-// and the first mismatch per workgroup in LDS (a lane writes only when it
-// exceeds them), and counts into a ULP histogram of kHistCopies copies, one
+// and the first mismatch per workgroup in LDS (a wave writes at most once a
+// round, when it exceeds them), and counts into a ULP histogram of kHistCopies copies, one
 // per LDS bank, so that lanes with the same distance do not queue on one bin.
 //
 // Measured (16 pairs of f16, bf16, f32 and fp8, 768 MiB a side, 11.3 % of the
-// elements off): 0.41 ms a call, 1.95 ms when every element of a run that
+// elements off): 0.39 ms a call, 1.95 ms when every element of a run that
 // differed took the exact path with its division; 10,000 uneven pairs of 8 GiB
-// a side with 1e-4 off: 2.60 ms (6.6 TB/s) against 3.16.
+// a side with 1e-4 off: 2.58 ms (6.7 TB/s) against 3.16.
 //
 // A workgroup's totals of a pair go to per-pair accumulators with integer
 // atomics (max of non-negative doubles via their bit patterns, first mismatch
@@ -185,8 +185,8 @@ enum : uint32_t { kCntMis = 0, kCntBytes, kCntNanBoth, kCntNanCand, kCntNanGold,
 struct Partial {
   uint32_t mis_elems, mis_bytes, over, not_close;  // of this thread
   bool any;                                        // this thread saw an element that differs or is NaN
-  double max_abs, max_rel, half_ulp;               // copies of the shared ones (never beyond them); half_ulp: half
-                                                   // the distance from max_rel to the next double
+  double max_abs, max_rel, half_ulp;               // of this thread and, as of the round's start, of all; half_ulp:
+                                                   // half the distance from max_rel to the next double
 };
 
 struct Tol {
@@ -233,7 +233,7 @@ template <typename B, uint32_t SIZE> __device__ __forceinline__ uint32_t byte_co
 }
 
 // Exact path of one marked element: it differs, or it is a NaN.  Straight-line
-// but for NaNs and for new maxima; the first mismatch is not looked for here.
+// but for NaNs and for new maxima of the relative error.
 template <uint32_t DT>
 __device__ __forceinline__ void element(typename Fmt<DT>::B c, typename Fmt<DT>::B g, const Tol& tol, Partial& p,
                                         TileLds& lds) {
@@ -267,22 +267,54 @@ __device__ __forceinline__ void element(typename Fmt<DT>::B c, typename Fmt<DT>:
     atomicAdd(&lds.hist[ulp_bin<D>(d) * kHistCopies + threadIdx.x % kHistCopies], 1u);
     const double vc = F::value(c), vg = F::value(g), ag = __builtin_fabs(vg);
     const double a = F::kind == 1 ? (double)d : __builtin_fabs(vc - vg);
-    if (a > p.max_abs) {
-      p.max_abs = a;
-      atomicMax(&lds.max_abs, (unsigned long long)dbl_bits(a));
-    }
+    p.max_abs = a > p.max_abs ? a : p.max_abs;
     if (vg != 0.0 && rel_may_grow(a, ag, p.max_rel, p.half_ulp)) {
       const double r = a / ag;
       if (r > p.max_rel) {
         p.max_rel = r;
         p.half_ulp = half_gap(r);
-        atomicMax(&lds.max_rel, (unsigned long long)dbl_bits(r));
       }
     }
     // tolerance test: an infinity is close only to an equal value, and these two differ
     const double bound = tol.atol + tol.rtol * ag;
     p.not_close += (a > bound || F::inf(c) || F::inf(g)) ? 1u : 0u;
   }
+}
+
+// Ends a round: the maxima that grew in it (from max_abs and max_rel) and the
+// lowest differing element (from round0; ~0: none) go to the shared ones: from
+// each lane that has some if they are few, else once per wave.  All lanes take
+// part.  (With an atomic per lane whatever their number, the first rounds' lanes
+// queued on these addresses: 1076 pairs of 920 bytes, 60 % off, 46 us, so 22; 214
+// pairs of 260 KB, 11.3 % off, 61 -> 45.  With a reduction whatever their number,
+// 16 pairs of 64 KiB, 0.1 % off, took 10.0 us a call, so 8.7.)
+constexpr int kFewLanes = 8;
+__device__ __forceinline__ void share_found(Partial& p, double max_abs, double max_rel, uint64_t round0, uint32_t low,
+                                            TileLds& lds) {
+  const bool grew = p.max_abs > max_abs || p.max_rel > max_rel;
+  unsigned long long a = dbl_bits(p.max_abs), r = dbl_bits(p.max_rel);  // not negative: ordered as their bits
+  const uint64_t growing = __ballot(grew);
+  bool tell = grew;
+  if (__popcll(growing) > kFewLanes) {
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+      a = max(a, __shfl_xor(a, d, 64));
+      r = max(r, __shfl_xor(r, d, 64));
+    }
+    tell = threadIdx.x % kWave == 0u;
+  }
+  if (tell) {
+    atomicMax(&lds.max_abs, a);
+    atomicMax(&lds.max_rel, r);
+  }
+  if (__ballot(round0 < lds.first) == 0ull) return;  // not one of the first rounds that differ
+  tell = low != ~0u;
+  if (__popcll(__ballot(tell)) > kFewLanes) {
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) low = min(low, (uint32_t)__shfl_xor(low, d, 64));
+    tell = threadIdx.x % kWave == 0u;
+  }
+  if (tell) atomicMin(&lds.first, (unsigned long long)(round0 + low));
 }
 
 // One element of `es` bytes at a naturally aligned address, zero-extended.
@@ -320,7 +352,10 @@ __device__ __forceinline__ void tile_body(const CmpPairDev& pr, uint64_t b0, uin
   constexpr uint32_t es = Fmt<DT>::size;
   constexpr uint32_t epv = 16u / es;  // elements per run
   const uint32_t tid = threadIdx.x;
-  const uint32_t nvec = (uint32_t)((b1 - b0) / 16u), per_round = T * kUnroll;
+  const uint32_t n_el = (uint32_t)((b1 - b0) / es), per_round = T * kUnroll;
+  // whole runs; none when every element can have a thread of its own, which spares one wave a chain of exact paths
+  // (230 pairs of 870 bytes with 60 % off: 15 us, 27 with runs)
+  const uint32_t nvec = n_el <= T ? 0u : (uint32_t)((b1 - b0) / 16u);
   const Tol tol{pr.tol, pr.atol, pr.rtol};
   const uint64_t ca = (uint64_t)pr.cand + b0, ga = (uint64_t)pr.gold + b0, e0 = b0 / es;
   uint4* const cs = stage + tid;                 // run u of this thread at cs[u * T]
@@ -410,31 +445,32 @@ __device__ __forceinline__ void tile_body(const CmpPairDev& pr, uint64_t b0, uin
       if (es == 2) return (B)*reinterpret_cast<const uint16_t*>(x);
       return *reinterpret_cast<const B*>(x);
     };
-    if (round0 < lds.first) {  // the first rounds that differ: look for the lowest differing element
-      uint32_t low = ~0u, at;
-      for (M m = mask; m != 0; m &= m - 1) {
-        const uint32_t o = place(m, at);
-        if (get(cs, o) != get(gs, o)) low = min(low, at);
-      }
-      if (low != ~0u) atomicMin(&lds.first, (unsigned long long)(round0 + low));
-    }
+    const double max_abs = p.max_abs, max_rel = p.max_rel;
+    uint32_t low = ~0u;
     for (; mask != 0; mask &= mask - 1) {
       uint32_t at;
       const uint32_t o = place(mask, at);
-      element<DT>(get(cs, o), get(gs, o), tol, p, lds);
+      const B cv = get(cs, o), gv = get(gs, o);
+      low = cv != gv ? min(low, at) : low;
+      element<DT>(cv, gv, tol, p, lds);
     }
+    share_found(p, max_abs, max_rel, round0, low, lds);
     asm volatile("" ::: "memory");
   }
-  // elements past the last whole run, one per thread
+  // elements past the last whole run (fewer than a run's, or all), one per thread
+  if (nvec * epv == n_el) return;
+  const double max_abs = p.max_abs, max_rel = p.max_rel;
   const uint32_t at = nvec * epv + tid;
-  if (at < (uint32_t)(b1 - b0) / es) {
+  uint32_t low = ~0u;
+  if (at < n_el) {
     const B cv = load_elem<B, es>((const uint8_t*)ca, at), gv = load_elem<B, es>((const uint8_t*)ga, at);
     if (cv != gv || Fmt<DT>::nan(gv)) {
       p.any = true;
-      if (cv != gv) atomicMin(&lds.first, (unsigned long long)(e0 + at));
+      if (cv != gv) low = at;
       element<DT>(cv, gv, tol, p, lds);
     }
   }
+  share_found(p, max_abs, max_rel, e0, low, lds);
 }
 
 
