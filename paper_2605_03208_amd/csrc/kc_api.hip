@@ -559,15 +559,15 @@ int kc_compact(kc_ctx* c, const kc_rangeset* crs, const uint64_t* zero_bm_d, con
   src.n_pages = rs->n_pages;
   src.n_items = rs->n_words;
   KC_HIP(launch_scan(src, rs->word_prefix, rs->block_sums, n_kept_d, s));
-  const uint32_t grid = grid_for(c, KC_OP_COMPACT, 8);
+  const uint32_t grid = c->tune[KC_OP_COMPACT].grid_per_cu ? grid_for(c, KC_OP_COMPACT, 0) : 0u;
   KernelTimer timer(c, KC_OP_COMPACT, s);
   if (!c->tune[KC_OP_COMPACT].per_item) {
-    KC_HIP(launch_gather(rs->tiles, rs->n_tiles, zero_bm_d, changed_bm_d, rs->word_prefix,
+    KC_HIP(launch_gather(rs->tiles, rs->n_tiles, rs->per_tile, zero_bm_d, changed_bm_d, rs->word_prefix,
                          static_cast<uint8_t*>(packed_d), page_va_d, cap_pages, rs->ushift, grid, s));
   } else {
     for (uint32_t r = 0; r < rs->n_ranges; ++r) {
       const uint32_t t0 = rs->range_tile[r];
-      KC_HIP(launch_gather(rs->tiles + t0, rs->range_tile[r + 1] - t0, zero_bm_d, changed_bm_d,
+      KC_HIP(launch_gather(rs->tiles + t0, rs->range_tile[r + 1] - t0, rs->per_tile, zero_bm_d, changed_bm_d,
                            rs->word_prefix, static_cast<uint8_t*>(packed_d), page_va_d, cap_pages, rs->ushift,
                            grid, s));
     }

@@ -268,7 +268,8 @@ hipError_t launch_page_hash(HashParams p, bool gather, bool prior, bool scan, ui
 hipError_t launch_probe_zero(ProbeParams p, uint64_t n_words, uint32_t n_cu, hipStream_t s);
 hipError_t launch_scan(const ScanSrc& src, uint64_t* out, uint64_t* block_sums,
                        uint64_t* total_out, hipStream_t s);
-hipError_t launch_gather(const Tile* tiles, uint32_t n_tiles, const uint64_t* zero_bm,
+// grid: waves (0: one per part of a tile)
+hipError_t launch_gather(const Tile* tiles, uint32_t n_tiles, uint32_t per_tile, const uint64_t* zero_bm,
                          const uint64_t* changed_bm, const uint64_t* word_prefix,
                          uint8_t* packed, uint64_t* page_va, uint64_t cap_pages, uint32_t ushift,
                          uint32_t grid, hipStream_t s);

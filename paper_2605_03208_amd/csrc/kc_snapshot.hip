@@ -250,69 +250,66 @@ __global__ __launch_bounds__(256) void k_scan_small(ScanSrc src, uint64_t* out, 
   if (threadIdx.x == 0 && total_out) *total_out = tot;
 }
 
-// ------------------------------------------------------ slots of a tile ---
-// Lane i < np: keep bit and packed slot of page i of the tile.
-__device__ __forceinline__ void tile_slots(const Tile& tile, const uint64_t* zero_bm,
-                                           const uint64_t* changed_bm, const uint64_t* word_prefix,
-                                           uint32_t lane, bool& kept, uint64_t& slot) {
-  kept = false;
-  slot = 0;
-  if (lane < tile.npages) {
-    const uint64_t g = (uint64_t)tile.g + lane;
-    uint64_t kw = ~zero_bm[g >> 6];
-    if (changed_bm) kw &= changed_bm[g >> 6];
-    kept = ((kw >> (g & 63u)) & 1ull) != 0ull;
-    slot = word_prefix[g >> 6] + (uint64_t)__popcll(kw & ((1ull << (g & 63u)) - 1ull));
-  }
-}
-
 // --------------------------------------------------------------- gather ---
-// Kept units of a tile, four at a time, copied to their packed slots 4 KiB of
-// each per round; a partial unit's slot is filled up with zeros.
-__global__ __launch_bounds__(64) void k_gather(const Tile* tiles, uint32_t n_tiles, const uint64_t* zero_bm,
-                                               const uint64_t* changed_bm, const uint64_t* word_prefix,
-                                               uint8_t* packed, uint64_t* page_va, uint64_t cap, uint32_t ushift) {
-  const uint32_t lane = threadIdx.x;
-  const uint32_t unit = 1u << ushift, nsub = unit / kPage;
-  for (uint32_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
-    const Tile tile = tiles[t];
-    bool kept;
-    uint64_t slot;
-    tile_slots(tile, zero_bm, changed_bm, word_prefix, lane, kept, slot);
-    const bool go = kept && slot < cap;
-    if (go) page_va[slot] = tile.va + ((uint64_t)lane << ushift);
+// Kept units copied to their packed slots.  A wave takes 64 KiB of a tile (a
+// whole tile of pages, a part of one of larger units): one lane per 4 KiB block
+// resolves whether its unit is kept and where its slot is, then the kept blocks
+// are copied four at a time, 16 KiB in flight; a partial unit's slot is filled up
+// with zeros.  The bytes moved bound it.  One such part per wave, in address
+// order (2 GiB in 4096 ranges, 5 % of the pages kept, 43 us, eight persistent
+// waves per CU 54; 8 GiB, all kept, 3.29 ms and 3.40; before, with whole tiles,
+// 60 us and 3.38 ms, and 2 GiB in units of 2 MiB 1.68 ms, now 0.77).
+constexpr uint32_t kGatherShift = 16;
+constexpr uint64_t kGatherPart = 1ull << kGatherShift;
+
+__global__ __launch_bounds__(64) void k_gather(const Tile* tiles, uint32_t n_tiles, uint32_t part_shift,
+                                               const uint64_t* zero_bm, const uint64_t* changed_bm,
+                                               const uint64_t* word_prefix, uint8_t* packed, uint64_t* page_va,
+                                               uint64_t cap, uint32_t ushift) {
+  const uint32_t lane = threadIdx.x, unit = 1u << ushift;
+  const uint64_t n_items = (uint64_t)n_tiles << part_shift;
+  for (uint64_t it = blockIdx.x; it < n_items; it += gridDim.x) {
+    const Tile tile = const_load(tiles + (it >> part_shift));
+    // this lane's block, of the 16 of the part: its unit and place in it
+    const uint32_t off = (((uint32_t)it & ((1u << part_shift) - 1u)) << kGatherShift) + lane * kPage;
+    const uint32_t j = off >> ushift, inside = off & (unit - 1u);
+    bool go = false;
+    uint64_t dst = 0;
+    if (lane < 16u && j < tile.npages) {
+      const uint64_t g = (uint64_t)tile.g + j;
+      uint64_t kw = ~zero_bm[g >> 6];
+      if (changed_bm) kw &= changed_bm[g >> 6];
+      const uint64_t slot = word_prefix[g >> 6] + (uint64_t)__popcll(kw & ((1ull << (g & 63u)) - 1ull));
+      go = ((kw >> (g & 63u)) & 1ull) != 0ull && slot < cap;
+      if (go && inside == 0u) page_va[slot] = tile.va + off;
+      dst = (uint64_t)packed + (slot << ushift) + inside;
+    }
+    const uint32_t bytes = j < tile.npages ? unit_bytes(tile, j, unit) : 0u;
+    const uint32_t len = bytes > inside ? min(bytes - inside, kPage) : 0u;  // of the block
     uint32_t mask = (uint32_t)__ballot(go);
     while (mask) {
-      uint32_t pg[4];
-      uint64_t dst[4];
-      uint32_t cnt = 0;
+      uint64_t from[4], to[4];
+      uint32_t cnt = 0, n[4];
 #pragma unroll
       for (uint32_t i = 0; i < 4; ++i) {
-        pg[i] = mask ? (uint32_t)__builtin_ctz(mask) : 0u;
-        dst[i] = __shfl(slot, pg[i], 64);
+        const uint32_t b = mask ? (uint32_t)__builtin_ctz(mask) : 0u;
+        from[i] = tile.va + __shfl(off, b, 64);
+        to[i] = __shfl((unsigned long long)dst, b, 64);
+        n[i] = __shfl(len, b, 64);
         if (mask) {
           mask &= mask - 1u;
           ++cnt;
         }
       }
-      for (uint32_t b = 0; b < nsub; ++b) {
-        uint4 x[16];
+      uint4 x[16];
 #pragma unroll
-        for (uint32_t i = 0; i < 4; ++i)
-#pragma unroll
-          for (uint32_t j = 0; j < 4; ++j) {
-            const uint32_t o = b * kPage + j * 1024u + lane * 16u, len = unit_bytes(tile, pg[i], unit);
-            if (i < cnt)
-              x[i * 4 + j] = o < len ? clip16(ld16nt(tile.va + ((uint64_t)pg[i] << ushift) + o), o, len)
-                                     : make_uint4(0, 0, 0, 0);  // a partial unit: zeros after its bytes
-          }
-#pragma unroll
-        for (uint32_t i = 0; i < 4; ++i)
-#pragma unroll
-          for (uint32_t j = 0; j < 4; ++j)
-            if (i < cnt)
-              st16nt((uint64_t)packed + (dst[i] << ushift) + b * kPage + j * 1024u + lane * 16u, x[i * 4 + j]);
+      for (uint32_t i = 0; i < 16; ++i) {
+        const uint32_t o = (i & 3u) * 1024u + lane * 16u;
+        if (i / 4u < cnt) x[i] = o < n[i / 4u] ? clip16(ld16nt(from[i / 4u] + o), o, n[i / 4u]) : make_uint4(0, 0, 0, 0);
       }
+#pragma unroll
+      for (uint32_t i = 0; i < 16; ++i)
+        if (i / 4u < cnt) st16nt(to[i / 4u] + (i & 3u) * 1024u + lane * 16u, x[i]);
     }
   }
 }
@@ -644,13 +641,16 @@ hipError_t launch_scan(const ScanSrc& src, uint64_t* out, uint64_t* block_sums, 
   return hipGetLastError();
 }
 
-hipError_t launch_gather(const Tile* tiles, uint32_t n_tiles, const uint64_t* zero_bm,
+hipError_t launch_gather(const Tile* tiles, uint32_t n_tiles, uint32_t per_tile, const uint64_t* zero_bm,
                          const uint64_t* changed_bm, const uint64_t* word_prefix, uint8_t* packed,
                          uint64_t* page_va, uint64_t cap_pages, uint32_t ushift, uint32_t grid, hipStream_t s) {
   if (n_tiles == 0) return hipSuccess;
-  grid = std::max(1u, std::min(grid, n_tiles));
-  hipLaunchKernelGGL(k_gather, dim3(grid), dim3(64), 0, s, tiles, n_tiles, zero_bm, changed_bm, word_prefix,
-                     packed, page_va, cap_pages, ushift);
+  uint32_t part_shift = 0;
+  while ((kGatherPart << part_shift) < (uint64_t)per_tile << ushift) ++part_shift;
+  const uint64_t n_items = (uint64_t)n_tiles << part_shift;
+  const uint32_t blocks = (uint32_t)std::min<uint64_t>(grid == 0u ? n_items : std::min<uint64_t>(grid, n_items), 1u << 25);
+  hipLaunchKernelGGL(k_gather, dim3(blocks), dim3(64), 0, s, tiles, n_tiles, part_shift, zero_bm, changed_bm,
+                     word_prefix, packed, page_va, cap_pages, ushift);
   return hipGetLastError();
 }
 
