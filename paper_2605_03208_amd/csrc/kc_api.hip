@@ -809,8 +809,10 @@ bool compare_wide(const kc_ctx* c, uint64_t n_pairs, uint64_t n_tiles, uint32_t 
 }
 
 uint32_t compare_grid(const kc_ctx* c, uint64_t n_tiles, uint32_t tile_bytes) {
-  const uint64_t per_cu = n_tiles * tile_bytes / std::max(1u, c->n_cu);
-  return grid_for(c, KC_OP_COMPARE, per_cu < kCompareFewBytes ? kCompareGridPerCu / 2u : kCompareGridPerCu);
+  const uint64_t bytes = n_tiles * tile_bytes, per_cu = bytes / std::max(1u, c->n_cu);
+  if (per_cu < kCompareFewBytes) return grid_for(c, KC_OP_COMPARE, kCompareGridPerCu / 2u);
+  if (c->tune[KC_OP_COMPARE].grid_per_cu) return grid_for(c, KC_OP_COMPARE, 0);
+  return std::max(c->n_cu * kCompareGridPerCu, (uint32_t)std::min<uint64_t>(bytes / kCompareRunBytes, 1u << 22));
 }
 
 }  // namespace kc

@@ -21,7 +21,8 @@
 // Measured (16 pairs of f16, bf16, f32 and fp8, 768 MiB a side, 11.3 % of the
 // elements off): 0.39 ms a call, 1.95 ms when every element of a run that
 // differed took the exact path with its division; 10,000 uneven pairs of 8 GiB
-// a side with 1e-4 off: 2.58 ms (6.7 TB/s) against 3.16.
+// a side with 1e-4 off: 2.53 ms (6.8 TB/s) against 3.16 (2.58 when the loads of
+// the next round were issued together, after the last run was looked at).
 //
 // A workgroup's totals of a pair go to per-pair accumulators with integer
 // atomics (max of non-negative doubles via their bit patterns, first mismatch
@@ -361,39 +362,31 @@ __device__ __forceinline__ void tile_body(const CmpPairDev& pr, uint64_t b0, uin
   uint4* const cs = stage + tid;                 // run u of this thread at cs[u * T]
   uint4* const gs = stage + per_round + tid;
   uint4 c[kUnroll], g[kUnroll];
-  auto load = [&](uint32_t v0) {  // runs past the end are read as the last one and not looked at
-#pragma unroll
-    for (uint32_t u = 0; u < kUnroll; ++u) {
-      const uint32_t o = min(v0 + u * T + tid, nvec - 1u) * 16u;
-      c[u] = ld_run<es>(ca + o);
-      g[u] = ld_run<es>(ga + o);
-    }
+  auto load = [&](uint32_t u, uint32_t v0) {  // runs past the end are read as the last one and not looked at
+    const uint32_t o = min(v0 + u * T + tid, nvec - 1u) * 16u;
+    c[u] = ld_run<es>(ca + o);
+    g[u] = ld_run<es>(ga + o);
   };
-  if (nvec != 0u) load(0u);
+  if (nvec != 0u) {
+#pragma unroll
+    for (uint32_t u = 0; u < kUnroll; ++u) load(u, 0u);
+  }
   for (uint32_t v0 = 0; v0 < nvec; v0 += per_round) {
-    // Does any lane of the wave hold a differing or NaN element?
-    uint32_t diff = 0u, nan = 0u;
+    // Marked elements: those that differ or are NaN.  Word j = 4 u + i of this lane's runs; 8-bit elements: byte k of
+    // word j is bit 8k + 7 - (j & 7) of half j >> 3; 16-bit: half-word k of word j is bit 16k + 15 - j; 32-bit: bit j;
+    // 64-bit: element e is bit e.
+    using M = typename Mask<es>::T;
+    uint32_t m[2] = {0u, 0u};
+    bool work = false;  // of the wave
 #pragma unroll
     for (uint32_t u = 0; u < kUnroll; ++u) {
       const uint32_t cw[4] = {c[u].x, c[u].y, c[u].z, c[u].w}, gw[4] = {g[u].x, g[u].y, g[u].z, g[u].w};
+      uint32_t any = 0u;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        diff |= cw[i] ^ gw[i];
-        nan |= nan_tops<DT>(gw, i);
-      }
-    }
-    const bool work = __ballot((diff | nan) != 0u) != 0ull;
-    // Marked elements.  Word j = 4 u + i of this lane's runs; 8-bit elements: byte k of word j is bit
-    // 8k + 7 - (j & 7) of half j >> 3; 16-bit: half-word k of word j is bit 16k + 15 - j; 32-bit: bit j; 64-bit:
-    // element e is bit e.
-    using M = typename Mask<es>::T;
-    M mask = 0u;
-    if (work) {
-      uint32_t m[2] = {0u, 0u};
-#pragma unroll
-      for (uint32_t u = 0; u < kUnroll; ++u) {
+      for (int i = 0; i < 4; ++i) any |= (cw[i] ^ gw[i]) | nan_tops<DT>(gw, i);
+      if (__ballot(any != 0u) != 0ull) {  // some lane's run holds one
+        work = true;
         const bool in = v0 + u * T + tid < nvec;
-        const uint32_t cw[4] = {c[u].x, c[u].y, c[u].z, c[u].w}, gw[4] = {g[u].x, g[u].y, g[u].z, g[u].w};
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const uint32_t j = 4u * u + (uint32_t)i;
@@ -411,10 +404,10 @@ __device__ __forceinline__ void tile_body(const CmpPairDev& pr, uint64_t b0, uin
         cs[u * T] = c[u];
         gs[u * T] = g[u];
       }
-      mask = es == 1 ? (M)(((uint64_t)m[1] << 32) | m[0]) : (M)m[0];
-      asm volatile("" ::: "memory");  // the runs are read back as elements of another type
+      load(u, v0 + per_round);  // the next round's, run by run (after the last round: its last run again)
     }
-    if (v0 + per_round < nvec) load(v0 + per_round);
+    M mask = es == 1 ? (M)(((uint64_t)m[1] << 32) | m[0]) : (M)m[0];
+    asm volatile("" ::: "memory");  // the runs are read back as elements of another type
     if (!work) continue;
     p.any = p.any || mask != 0;
     p.max_abs = fmax_pos(p.max_abs, lds.max_abs);

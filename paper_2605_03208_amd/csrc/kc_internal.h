@@ -243,7 +243,11 @@ static_assert(sizeof(CmpArgPairs) <= 3072, "kernel arguments");
 // accumulators, weigh more (4 / 8 per CU, 11.3 % off: 1000 pairs of 128 KiB 76 /
 // 100 us, 5 pairs of 167 MiB in all 119 / 135; 417 pairs of 548 MiB 301 / 293).
 constexpr uint32_t kCompareGridPerCu = 8;
+// Beyond 16 GiB a side, more, of 8 MiB each: the workgroups in flight then cover
+// a window of the buffers (200 pairs of 150 MiB, all equal, runs of 30 / 7.5 /
+// 0.5 MiB a side: 9.23 / 9.16 / 9.05 ms).
 constexpr uint64_t kCompareFewBytes = 1u << 20;
+constexpr uint64_t kCompareRunBytes = 8u << 20;
 
 // Tile of a small compare: when the pairs are no more than the CUs and none is
 // larger than this, each gets a workgroup of 1024 threads, which reads it in one
