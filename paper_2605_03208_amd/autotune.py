@@ -1,7 +1,8 @@
 """Launch-shape autotuner for the kc operations.
 
 For one operation on the caller's real inputs, every candidate launch shape
-(persistent waves per CU, and for compare workgroups per CU and the bytes per tile) is run,
+(waves per CU, and for compare workgroups per CU and the bytes per tile; 0: the library's
+own rule) is run,
 timed with the library's kernel events, and its outputs are digested; a
 candidate whose outputs differ from the first one's raises, so tuning can
 never change a result.  The fastest candidate is applied to the context and
@@ -25,15 +26,16 @@ from . import kc
 ARCH = "gfx950"
 
 CANDIDATES = {
-    kc.OP_PAGE_HASH: [dict(grid_per_cu=g) for g in (2, 3, 4, 6, 8, 12, 16, 24)],
-    kc.OP_SNAPSHOT: [dict(grid_per_cu=g) for g in (2, 3, 4, 6, 8, 12)],
-    kc.OP_COMPACT: [dict(grid_per_cu=g) for g in (4, 8, 16, 32, 48, 64, 96, 128, 192, 256)],
-    kc.OP_RESTORE: [dict(grid_per_cu=g) for g in (8, 12, 16, 24, 32, 48, 64, 96, 128)],
-    kc.OP_CLOSURE: [dict(grid_per_cu=g) for g in (4, 8, 16)],
-    kc.OP_COMPARE: [dict(grid_per_cu=g, tile_bytes=t) for g in (1, 2, 3, 4, 16, 64, 128, 256, 512, 1024)
-                    for t in (16 << 10, 32 << 10, 64 << 10, 128 << 10, 256 << 10, 512 << 10, 1 << 20)],
-    kc.OP_GRAPH: [dict(grid_per_cu=g) for g in (4, 8, 12, 16, 24, 32)],
-    kc.OP_REGION_DIFF: [dict(grid_per_cu=g) for g in (8, 12, 16, 20, 32, 48, 64)],
+    kc.OP_PAGE_HASH: [dict(grid_per_cu=g) for g in (0, 4, 8, 12, 16, 24)],
+    kc.OP_SNAPSHOT: [dict(grid_per_cu=g) for g in (0, 4, 6, 8, 12)],
+    kc.OP_COMPACT: [dict(grid_per_cu=g) for g in (0, 8, 16, 32, 48, 64, 96, 128, 192, 256)],
+    kc.OP_RESTORE: [dict(grid_per_cu=g) for g in (0, 8, 32, 64, 128)],
+    kc.OP_CLOSURE: [dict(grid_per_cu=g) for g in (0, 4, 8, 16)],
+    kc.OP_COMPARE: [dict(grid_per_cu=0, tile_bytes=0)] +
+                   [dict(grid_per_cu=g, tile_bytes=t) for g in (2, 4, 8, 16, 64, 256)
+                    for t in (16 << 10, 32 << 10, 64 << 10, 128 << 10, 256 << 10, 512 << 10)],
+    kc.OP_GRAPH: [dict(grid_per_cu=g) for g in (0, 4, 8, 12, 16, 24, 32)],
+    kc.OP_REGION_DIFF: [dict(grid_per_cu=g) for g in (0, 8, 12, 16, 20, 32, 48)],
 }
 
 OP_NAMES = {kc.OP_PAGE_HASH: "page_hash", kc.OP_SNAPSHOT: "snapshot", kc.OP_COMPACT: "compact",
