@@ -49,10 +49,10 @@ PAGE = 4096
 # device copy gives (fetch x2.0, write x1.0).  Valid only for the kernel
 # sources they were taken from.
 PMC_TRAFFIC = {
-    "source_sha256": "e1c6a004cddd500c648e60c69194f8845c910135b386660677fe57bc9c581063",
-    "snapshot": 62869523365,   # fetch 31385126181 + write 31484397184
-    "restore": 63687466317,    # fetch 32333170304 + write 31354296013
-    "compare": 64440925107,    # fetch 64440925107 + write 0
+    "source_sha256": "917568fabc86ba8fa148f9621927b3ad81b17f149c4f11d0cf59a8c42db25695",
+    "snapshot": 62934620777,  # fetch 31401060297 + write 31533560480
+    "restore": 63687210009,   # fetch 32333206195 + write 31354003814
+    "compare": 64428289434,   # fetch 64428289434 + write 0
 }
 
 

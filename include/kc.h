@@ -148,9 +148,7 @@ typedef struct {
 
 /* One candidate / golden pair for kc_compare.  Both buffers device memory of
  * n_elems elements of `dtype`, each aligned to the element size (else
- * KC_EALIGN).  Pairs whose buffers are both 16-byte aligned stream 16-byte
- * runs; others (views at odd element offsets) are read element by element,
- * with the same results. */
+ * KC_EALIGN); views at odd element offsets are read in 16-byte runs as well. */
 typedef struct {
   const void *cand_d;
   const void *gold_d;
@@ -197,14 +195,13 @@ typedef struct {
 
 /* Launch shape of one operation.  Zero fields keep the built-in choice. */
 typedef struct {
-  uint32_t grid_per_cu; /* persistent waves per compute unit (the compare:
-                           four-wave workgroups per compute unit)           */
+  uint32_t grid_per_cu; /* waves per compute unit (the compare: four-wave
+                           workgroups per compute unit), which stride over
+                           the work                                         */
   uint32_t tile_bytes;  /* compare: bytes of each side per work item        */
   uint32_t per_item;    /* 1 = one launch per range / pair (no batching)    */
-  uint32_t depth;       /* hashing pass without a fused scan: chunks in flight
-                           per wave, 1 to 4; 2 to 4 select the pipelined,
-                           skewed pass of units above 4 KiB; 0 = built-in
-                           choice (2 above 4 KiB, else 1)                    */
+  uint32_t depth;       /* 0 to 4; accepted, without effect (every hashing
+                           pass keeps sixteen 1 KiB loads in flight)        */
 } kc_tuning;
 
 enum {
