@@ -25,6 +25,14 @@ __device__ __forceinline__ void mark_high(uint32_t& marks, uint32_t d, uint32_t 
       : "vcc");
 }
 
+// The same of words: marks = 2 * marks + (d < span).
+__device__ __forceinline__ void mark_word(uint32_t& marks, uint64_t d, uint64_t span) {
+  asm("v_cmp_gt_u64_e32 vcc, %1, %2\n\tv_addc_co_u32_e32 %0, vcc, %0, %0, vcc"
+      : "+v"(marks)
+      : "s"(span), "v"(d)
+      : "vcc");
+}
+
 // Units kept (zero bit clear) among the first n, at most 64 * kInlineWords: all words loaded at once.
 __device__ __forceinline__ uint32_t kept_before(const uint64_t* zero_bm, uint32_t n, uint32_t lane) {
   constexpr uint32_t kEach = kInlineWords / kWave;
@@ -75,11 +83,15 @@ __device__ __forceinline__ uint32_t kept_before(const uint64_t* zero_bm, uint32_
 //
 // GATHER: zero bits come from the probe, zero units are not read (their hash
 // is computed from zeros), kept units are also stored to their packed slots.
-// SCAN: words whose upper half lies in the window's are marked (three
-// instructions a word); once a round is staged, the marked ones get the exact
-// test, and pointer-like words go to the wave's queue (PtrQueue) with the
+// SCAN (a closure scan rides on the pass), kScanHigh: words whose upper half lies
+// in the window's are marked (three instructions a word); once a round is
+// staged, the marked ones get the exact test, and pointer-like words go to the wave's queue (PtrQueue) with the
 // 4 KiB-page scan tile they lie in; out-of-range ones are counted there by
-// atomics.
+// atomics.  kScanWord, for windows that reach below 4 GiB: every zero and every
+// small integer has such an upper half, and the steps over those marks took more
+// than the pass (2 GiB of zeros, window from 4096: 590 us, 370 with the words
+// themselves marked).  For other windows that costs small snapshots (64 MiB: 50.9
+// -> 52.5 us).
 //
 // The waves of a workgroup are independent; with the closure scan they share
 // one range table.  LDS, all dynamic: the table, then per wave its stage,
@@ -92,7 +104,9 @@ __host__ __device__ constexpr uint32_t hash_lds_per_wave(uint32_t rows, bool sca
   return rows * (stage_stride(rows) + 32u) + (scan ? kHashQueue * 10u : 0u);
 }
 
-template <bool GATHER, bool PRIOR, bool SCAN, uint32_t ROWS>
+enum ScanKind : uint32_t { kNoScan = 0, kScanHigh = 1, kScanWord = 2 };
+
+template <bool GATHER, bool PRIOR, uint32_t SCAN, uint32_t ROWS>
 __global__ __launch_bounds__(kHashWaves * kWave) __attribute__((amdgpu_waves_per_eu(2))) void k_page_hash(
     HashParams p) {
   constexpr uint32_t kPer = kRoundLoads / ROWS;  // loads per row and round
@@ -101,7 +115,7 @@ __global__ __launch_bounds__(kHashWaves * kWave) __attribute__((amdgpu_waves_per
   const uint32_t lane = threadIdx.x % kWave, wpb = blockDim.x / kWave;
   const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const uint32_t table = SCAN ? 16u * p.scan.rt.n_fence_w + 2u * kBuckets : 0u;
-  uint8_t* const stage = reinterpret_cast<uint8_t*>(kc_wide_lds) + table + wv * hash_lds_per_wave(ROWS, SCAN);
+  uint8_t* const stage = reinterpret_cast<uint8_t*>(kc_wide_lds) + table + wv * hash_lds_per_wave(ROWS, SCAN != kNoScan);
   // a partial unit's bytes past its last whole stripe
   uint64_t(*const tail_lds)[4] = reinterpret_cast<uint64_t(*)[4]>(stage + ROWS * kStride);
   uint64_t* const queue_lds = reinterpret_cast<uint64_t*>(tail_lds + ROWS);
@@ -204,8 +218,13 @@ __global__ __launch_bounds__(kHashWaves * kWave) __attribute__((amdgpu_waves_per
         if (part) v = clip16(v, o + lane16, last_len);  // the partial unit's bytes past its end
         if (!GATHER && __ballot(nz16(v)) != 0ull) nonzero |= 1u << r;
         if (SCAN) {
-          mark_high(marks, v.y - win_hi, win_span);
-          mark_high(marks, v.w - win_hi, win_span);
+          if (SCAN == kScanWord) {
+            mark_word(marks, (((uint64_t)v.y << 32) | v.x) - p.scan.lo, p.scan.span);
+            mark_word(marks, (((uint64_t)v.w << 32) | v.z) - p.scan.lo, p.scan.span);
+          } else {
+            mark_high(marks, v.y - win_hi, win_span);
+            mark_high(marks, v.w - win_hi, win_span);
+          }
         }
         if (GATHER) {  // a partial unit's slot: zeros after its bytes
           const v4u x = {v.x, v.y, v.z, v.w};
@@ -326,18 +345,22 @@ hipError_t launch_page_hash(HashParams p, bool gather, bool prior, bool scan, ui
   // 348 us, striding 401).
   if (grid == 0u && scan && !gather) waves = std::min(waves, (uint64_t)(kLdsBytes / lds) * wpb * n_cu);
   const uint32_t blocks = (uint32_t)std::min<uint64_t>((waves + wpb - 1) / wpb, kMaxThreads / (wpb * kWave));
+  const uint32_t kind = !scan ? kNoScan : (p.scan.lo >> 32) != 0ull ? kScanHigh : kScanWord;
 #define KC_HASH_CASE(G, P, S, N)                                                                     \
-  if (gather == G && prior == P && scan == S && rows == N) {                                         \
+  if (gather == G && prior == P && kind == S && rows == N) {                                         \
     hipLaunchKernelGGL((k_page_hash<G, P, S, N>), dim3(blocks), dim3(wpb * kWave), lds, s, p);       \
     return hipGetLastError();                                                                        \
   }
-#define KC_HASH_CASES(N)              \
-  KC_HASH_CASE(false, false, false, N) \
-  KC_HASH_CASE(false, false, true, N)  \
-  KC_HASH_CASE(false, true, false, N)  \
-  KC_HASH_CASE(false, true, true, N)   \
-  KC_HASH_CASE(true, false, false, N)  \
-  KC_HASH_CASE(true, false, true, N)
+#define KC_HASH_CASES(N)                  \
+  KC_HASH_CASE(false, false, kNoScan, N)   \
+  KC_HASH_CASE(false, false, kScanHigh, N) \
+  KC_HASH_CASE(false, false, kScanWord, N) \
+  KC_HASH_CASE(false, true, kNoScan, N)    \
+  KC_HASH_CASE(false, true, kScanHigh, N)  \
+  KC_HASH_CASE(false, true, kScanWord, N)  \
+  KC_HASH_CASE(true, false, kNoScan, N)    \
+  KC_HASH_CASE(true, false, kScanHigh, N)  \
+  KC_HASH_CASE(true, false, kScanWord, N)
   KC_HASH_CASES(16u)
   KC_HASH_CASES(8u)
   KC_HASH_CASES(4u)
