@@ -86,8 +86,7 @@ __device__ __forceinline__ uint32_t kept_before(const uint64_t* zero_bm, uint32_
 // SCAN (a closure scan rides on the pass), kScanHigh: words whose upper half lies
 // in the window's are marked (three instructions a word); once a round is
 // staged, the marked ones get the exact test, and pointer-like words go to the wave's queue (PtrQueue) with the
-// 4 KiB-page scan tile they lie in; out-of-range ones are counted there by
-// atomics.  kScanWord, for windows that reach below 4 GiB: every zero and every
+// 4 KiB-page scan tile they lie in, where out-of-range ones are counted.  kScanWord, for windows that reach below 4 GiB: every zero and every
 // small integer has such an upper half, and the steps over those marks took more
 // than the pass (2 GiB of zeros, window from 4096: 590 us, 370 with the words
 // themselves marked).  For other windows that costs small snapshots (64 MiB: 50.9
@@ -199,9 +198,17 @@ __global__ __launch_bounds__(kHashWaves * kWave) __attribute__((amdgpu_waves_per
     // the scan tile of these units' first byte: with 4 KiB units the tile itself
     uint32_t scan0 = p.tile0 + t;
     if (SCAN && p.scan0) scan0 = const_load32(p.scan0 + t) + ((first << ushift) >> 16);
+    // Out-of-range words are added once per scan tile among the lanes (an atomic per word queued on the tile's address:
+    // 2 GiB of nothing but such words 33 ms, so 1.6).
     auto search = [&](uint64_t w, uint32_t tag) {
-      if (wide_range_index(w, p.scan.rt) >= 0) ++n_in;
-      else atomicAdd(&p.scan.tile_oob[scan0 + tag], 1u);
+      const bool out = wide_range_index(w, p.scan.rt) < 0;
+      n_in += out ? 0u : 1u;
+      for (uint64_t m = __ballot(out); m != 0ull;) {
+        const uint32_t leader = (uint32_t)__builtin_ctzll(m), its = __builtin_amdgcn_readlane(tag, leader);
+        const uint64_t same = __ballot(out && tag == its);
+        if (lane == leader) atomicAdd(&p.scan.tile_oob[scan0 + its], (uint32_t)__popcll(same));
+        m &= ~same;
+      }
     };
     load(0u);
     // Snapshots load the table while the first loads are under way (8 GiB 2.78 ms, table first 2.85); for the others

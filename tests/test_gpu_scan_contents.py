@@ -104,3 +104,47 @@ def test_windows_below_4gib_time(kc):
     assert us["low"] < 1.25 * us["default"]
     rs.close()
     ctx.close()
+
+
+@pytest.mark.parametrize("unit", [PAGE, 2 * PAGE, 8 * PAGE, 16 * PAGE, 64 * PAGE, 512 * PAGE])
+def test_memory_of_out_of_range_words(kc, unit):
+    """Every word, every word of some pages, and a few words are pointers past
+    the end of a range."""
+    rng = np.random.default_rng(7 + unit)
+    sizes = np.concatenate([rng.integers(1, 5, size=6) * unit, rng.integers(1, 40, size=12) * PAGE])
+    sizes -= rng.integers(0, PAGE, size=len(sizes))
+    lay = W.make_layout(rng, sizes, gap_pages=(1, 3))
+    arena = W.Arena(lay, "cuda")
+    ranges = lay.ranges(arena.va_base)
+    words_of = lay.arena_bytes // 8
+    past = np.array([b + s + 8 for b, s in ranges], dtype=np.uint64)[rng.integers(0, len(ranges), size=words_of)]
+    inside = np.array([b for b, _ in ranges], dtype=np.uint64)[rng.integers(0, len(ranges), size=words_of)]
+    ctx = kc.Context(0)
+    for name, share in (("every word", np.ones(words_of, dtype=bool)),
+                        ("every word of a third of the pages", (rng.random(words_of // 512 + 1) < 0.33).repeat(512)[:words_of]),
+                        ("one word in 50", rng.random(words_of) < 0.02)):
+        say(f"out-of-range words: unit {unit}, {name}")
+        host = np.zeros(lay.arena_bytes, dtype=np.uint8)
+        host[: words_of * 8].view(np.uint64)[:] = np.where(share, past, np.where(rng.random(words_of) < 0.1, inside, 5))
+        arena.buf.copy_(torch.from_numpy(host))
+        check_scans(kc, ctx, ranges, W.host_views(lay, host), unit, (0, 0))
+    ctx.close()
+
+
+@pytest.mark.parametrize("unit", [PAGE, 16 * PAGE])
+def test_memory_of_out_of_range_words_time(kc, unit):
+    buf, ranges = large()
+    words = buf[: buf.numel() // 8 * 8].view(torch.int64)
+    ctx = kc.Context(0)
+    rs = kc.RangeSet(ctx, ranges, unit=unit)
+    us = {}
+    for name, value in (("in range", ranges[3][0] + 64), ("out of range", ranges[3][0] + ranges[3][1] + 64)):
+        say(f"out-of-range words: time, unit {unit}, all words {name}")
+        words.fill_(value)
+        scan = kc.ScanOut("cuda", CAP)
+        out = kc.page_hash(ctx, rs, scan=scan)
+        us[name] = best_us(lambda: kc.page_hash(ctx, rs, scan=scan, out=out))
+    say(f"out-of-range words: {us}")
+    assert us["out of range"] < 2.0 * us["in range"]
+    rs.close()
+    ctx.close()
