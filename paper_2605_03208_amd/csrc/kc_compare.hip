@@ -170,18 +170,21 @@ template <uint32_t DT> __device__ __forceinline__ uint32_t nan_tops(const uint32
 }
 
 constexpr uint32_t kHistCopies = 32;
+// After the ULP bins, one for each NaN class: in both sides, in the candidate only, in the golden only.
+constexpr uint32_t kNanBins = kBins, kAllBins = kBins + 3u;
 
 // What a workgroup shares of the pair it is on.  The maxima and the first
 // mismatch live here rather than in registers: a lane compares with its own
 // copy of them, taken once per round, and writes only what exceeds it.
 struct TileLds {
-  uint32_t hist[kBins * kHistCopies];  // bin b, copy c at b * kHistCopies + c; lane l counts into copy l mod 32
+  uint32_t hist[kAllBins * kHistCopies];  // bin b, copy c at b * kHistCopies + c; lane l counts into copy l mod 32
   unsigned long long max_abs, max_rel;  // bits of non-negative doubles
   unsigned long long first;             // lowest differing element
-  uint32_t cnt[8];                      // kCntMis .. kCntNotClose below
-  uint32_t bins[kBins];                 // the histogram's totals, once a pair is done
+  uint32_t any[2];                      // some thread saw an element that differs or is NaN; pairs take turns
+  uint32_t cnt[4];                      // kCntMis .. kCntNotClose below
+  uint32_t bins[kAllBins];              // the histogram's totals, once a pair is done
 };
-enum : uint32_t { kCntMis = 0, kCntBytes, kCntNanBoth, kCntNanCand, kCntNanGold, kCntOver, kCntNotClose };
+enum : uint32_t { kCntMis = 0, kCntBytes, kCntOver, kCntNotClose };
 
 struct Partial {
   uint32_t mis_elems, mis_bytes, over, not_close;  // of this thread
@@ -233,23 +236,18 @@ template <typename B, uint32_t SIZE> __device__ __forceinline__ uint32_t byte_co
   return n;
 }
 
-// Exact path of one marked element: it differs, or it is a NaN.  Straight-line
-// but for NaNs and for new maxima of the relative error.
+__device__ __forceinline__ void count_nans(TileLds& lds, uint32_t which, uint32_t n) {
+  if (n != 0u) atomicAdd(&lds.hist[(kNanBins + which) * kHistCopies + threadIdx.x % kHistCopies], n);
+}
+
+// Exact path of one element that differs, neither side a NaN.  Straight-line
+// but for new maxima of the relative error.
 template <uint32_t DT>
 __device__ __forceinline__ void element(typename Fmt<DT>::B c, typename Fmt<DT>::B g, const Tol& tol, Partial& p,
                                         TileLds& lds) {
   using F = Fmt<DT>;
   using B = typename F::B;
   using D = B;  // distances of elements up to 32 bits fit in 32 bits
-  const bool nc = F::nan(c), ng = F::nan(g);
-  if (nc || ng) {
-    if (c != g) {
-      ++p.mis_elems;
-      p.mis_bytes += byte_count<B, F::size>(c ^ g);
-    }
-    atomicAdd(&lds.cnt[nc && ng ? kCntNanBoth : (nc ? kCntNanCand : kCntNanGold)], 1u);
-    return;
-  }
   ++p.mis_elems;
   p.mis_bytes += byte_count<B, F::size>(c ^ g);
   if constexpr (F::kind != 2) {
@@ -345,12 +343,65 @@ template <uint32_t ES> __device__ __forceinline__ uint4 ld_run(uint64_t addr) {
 template <uint32_t ES> struct Mask { typedef uint32_t T; };
 template <> struct Mask<1> { typedef uint64_t T; };
 
+// Marks elements of word j = 4 u + i of a lane's runs from their top bits: 8-bit
+// elements: byte k of word j is bit 8k + 7 - (j & 7) of half j >> 3; 16-bit:
+// half-word k of word j is bit 16k + 15 - j; 32-bit: bit j; 64-bit: element e
+// (its odd word's top bit) is bit e.
+template <uint32_t ES> __device__ __forceinline__ void add_marks(uint32_t (&m)[2], uint32_t j, uint32_t tops) {
+  if (ES == 8) m[0] |= tops >> (31u - (j >> 1));
+  else if (ES == 4) m[0] |= tops >> (31u - j);
+  else if (ES == 2) m[0] |= tops >> j;
+  else m[j >> 3] |= tops >> (j & 7u);
+}
+
+// The NaNs of a round, from its staged runs (bit u of `runs`: run u is staged;
+// v: this lane's first run, of nvec): counted by class, and where the two sides
+// differ the element, its bytes and the lowest of them; taken out of the marks m.
+// (Taken through the exact path one by one, 256 MiB of NaN in both sides took
+// 0.27 ms as f32 and 1.03 ms as fp8; so 0.13 for either.)
+template <uint32_t DT, uint32_t T>
+__device__ __forceinline__ void round_nans(const uint4* cs, const uint4* gs, uint32_t runs, uint32_t v, uint32_t nvec,
+                                           uint32_t (&m)[2], uint32_t& low, Partial& p, TileLds& lds) {
+  constexpr uint32_t es = Fmt<DT>::size;
+  uint32_t both = 0u, cand = 0u, gold = 0u, nans[2] = {0u, 0u};
+#pragma unroll
+  for (uint32_t u = 0; u < kUnroll; ++u) {
+    if (((runs >> u) & 1u) == 0u) continue;
+    const uint4 c = cs[u * T], g = gs[u * T];
+    const uint32_t cw[4] = {c.x, c.y, c.z, c.w}, gw[4] = {g.x, g.y, g.z, g.w};
+    const uint32_t in = v + u * T < nvec ? ~0u : 0u;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (es == 8u && !(i & 1)) continue;  // with the odd word
+      const uint32_t nc = nan_tops<DT>(cw, i) & in, ng = nan_tops<DT>(gw, i) & in, n = nc | ng;
+      both += (uint32_t)__popc(nc & ng);
+      cand += (uint32_t)__popc(nc & ~ng);
+      gold += (uint32_t)__popc(~nc & ng);
+      add_marks<es>(nans, 4u * u + (uint32_t)i, n);
+      // all bits of their lanes
+      const uint32_t lanes = es == 1u ? (n >> 7) * 0xFFu : es == 2u ? (n >> 15) * 0xFFFFu : 0u - (n >> 31);
+      const uint32_t x = (cw[i] ^ gw[i]) & lanes, y = es == 8u ? (cw[i & 2] ^ gw[i & 2]) & lanes : 0u;
+      const uint32_t d = nonzero_tops<es>(x | y);
+      p.mis_elems += (uint32_t)__popc(d);
+      p.mis_bytes += (uint32_t)(es == 1u ? __popc(d) : __popc(nonzero_tops<1>(x)) + __popc(nonzero_tops<1>(y)));
+      if (d != 0u)
+        low = min(low, (u * T + threadIdx.x) * (16u / es) + ((uint32_t)i * 4u + ((uint32_t)__builtin_ctz(d) >> 3)) / es);
+    }
+  }
+  m[0] &= ~nans[0];
+  m[1] &= ~nans[1];
+  count_nans(lds, 0u, both);
+  count_nans(lds, 1u, cand);
+  count_nans(lds, 2u, gold);
+}
+
 // The bytes [b0, b1) of a pair.  stage: kUnroll runs of each side per thread.
 template <uint32_t DT, uint32_t T>
 __device__ __forceinline__ void tile_body(const CmpPairDev& pr, uint64_t b0, uint64_t b1, Partial& p, TileLds& lds,
                                           uint4* stage) {
-  using B = typename Fmt<DT>::B;
-  constexpr uint32_t es = Fmt<DT>::size;
+  using F = Fmt<DT>;
+  using B = typename F::B;
+  constexpr uint32_t es = F::size;
   constexpr uint32_t epv = 16u / es;  // elements per run
   const uint32_t tid = threadIdx.x;
   const uint32_t n_el = (uint32_t)((b1 - b0) / es), per_round = T * kUnroll;
@@ -372,12 +423,9 @@ __device__ __forceinline__ void tile_body(const CmpPairDev& pr, uint64_t b0, uin
     for (uint32_t u = 0; u < kUnroll; ++u) load(u, 0u);
   }
   for (uint32_t v0 = 0; v0 < nvec; v0 += per_round) {
-    // Marked elements: those that differ or are NaN.  Word j = 4 u + i of this lane's runs; 8-bit elements: byte k of
-    // word j is bit 8k + 7 - (j & 7) of half j >> 3; 16-bit: half-word k of word j is bit 16k + 15 - j; 32-bit: bit j;
-    // 64-bit: element e is bit e.
-    using M = typename Mask<es>::T;
+    // Marked elements: those that differ or are NaN (add_marks).
     uint32_t m[2] = {0u, 0u};
-    bool work = false;  // of the wave
+    uint32_t runs = 0u, nan = 0u;  // of the wave: runs that hold one, as bits; of the lane: a NaN in some side
 #pragma unroll
     for (uint32_t u = 0; u < kUnroll; ++u) {
       const uint32_t cw[4] = {c[u].x, c[u].y, c[u].z, c[u].w}, gw[4] = {g[u].x, g[u].y, g[u].z, g[u].w};
@@ -385,31 +433,28 @@ __device__ __forceinline__ void tile_body(const CmpPairDev& pr, uint64_t b0, uin
 #pragma unroll
       for (int i = 0; i < 4; ++i) any |= (cw[i] ^ gw[i]) | nan_tops<DT>(gw, i);
       if (__ballot(any != 0u) != 0ull) {  // some lane's run holds one
-        work = true;
-        const bool in = v0 + u * T + tid < nvec;
+        runs |= 1u << u;
+        const uint32_t in = v0 + u * T + tid < nvec ? ~0u : 0u;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const uint32_t j = 4u * u + (uint32_t)i;
-          const uint32_t nt = nan_tops<DT>(gw, i);
-          if (es == 8) {
-            if (i & 1) m[0] |= in && ((cw[i] ^ gw[i]) | (cw[i - 1] ^ gw[i - 1]) | nt) != 0u ? 1u << (j >> 1) : 0u;
-          } else if (es == 4) {
-            m[0] |= in && ((cw[i] ^ gw[i]) | nt) != 0u ? 1u << j : 0u;
-          } else {
-            const uint32_t t = in ? nonzero_tops<es>(cw[i] ^ gw[i]) | nt : 0u;
-            if (es == 2) m[0] |= t >> j;
-            else m[j >> 3] |= t >> (j & 7u);
-          }
+          if (es == 8u && !(i & 1)) continue;  // with the odd word
+          const uint32_t x = es == 8u ? (cw[i] ^ gw[i]) | (cw[i & 2] ^ gw[i & 2]) : cw[i] ^ gw[i];
+          const uint32_t ng = nan_tops<DT>(gw, i);
+          add_marks<es>(m, 4u * u + (uint32_t)i, (nonzero_tops<es>(x) | ng) & in);
+          nan |= nan_tops<DT>(cw, i) | ng;
         }
         cs[u * T] = c[u];
         gs[u * T] = g[u];
       }
       load(u, v0 + per_round);  // the next round's, run by run (after the last round: its last run again)
     }
-    M mask = es == 1 ? (M)(((uint64_t)m[1] << 32) | m[0]) : (M)m[0];
     asm volatile("" ::: "memory");  // the runs are read back as elements of another type
-    if (!work) continue;
-    p.any = p.any || mask != 0;
+    if (runs == 0u) continue;
+    p.any = p.any || (m[0] | m[1]) != 0u;
+    uint32_t low = ~0u;  // lowest differing element of this lane, from the round's first
+    if (F::kind == 0 && __ballot(nan != 0u) != 0ull) round_nans<DT, T>(cs, gs, runs, v0 + tid, nvec, m, low, p, lds);
+    using M = typename Mask<es>::T;
+    M mask = es == 1 ? (M)(((uint64_t)m[1] << 32) | m[0]) : (M)m[0];
     p.max_abs = fmax_pos(p.max_abs, lds.max_abs);
     p.max_rel = fmax_pos(p.max_rel, lds.max_rel);
     p.half_ulp = half_gap(p.max_rel);
@@ -439,13 +484,11 @@ __device__ __forceinline__ void tile_body(const CmpPairDev& pr, uint64_t b0, uin
       return *reinterpret_cast<const B*>(x);
     };
     const double max_abs = p.max_abs, max_rel = p.max_rel;
-    uint32_t low = ~0u;
     for (; mask != 0; mask &= mask - 1) {
       uint32_t at;
       const uint32_t o = place(mask, at);
-      const B cv = get(cs, o), gv = get(gs, o);
-      low = cv != gv ? min(low, at) : low;
-      element<DT>(cv, gv, tol, p, lds);
+      low = min(low, at);
+      element<DT>(get(cs, o), get(gs, o), tol, p, lds);
     }
     share_found(p, max_abs, max_rel, round0, low, lds);
     asm volatile("" ::: "memory");
@@ -457,9 +500,14 @@ __device__ __forceinline__ void tile_body(const CmpPairDev& pr, uint64_t b0, uin
   uint32_t low = ~0u;
   if (at < n_el) {
     const B cv = load_elem<B, es>((const uint8_t*)ca, at), gv = load_elem<B, es>((const uint8_t*)ga, at);
-    if (cv != gv || Fmt<DT>::nan(gv)) {
-      p.any = true;
-      if (cv != gv) low = at;
+    const bool nc = F::nan(cv), ng = F::nan(gv);
+    p.any = p.any || cv != gv || ng;
+    if (cv != gv) low = at;
+    if (nc || ng) {
+      count_nans(lds, nc && ng ? 0u : nc ? 1u : 2u, 1u);
+      p.mis_elems += cv != gv ? 1u : 0u;
+      p.mis_bytes += cv != gv ? byte_count<B, es>(cv ^ gv) : 0u;
+    } else if (cv != gv) {
       element<DT>(cv, gv, tol, p, lds);
     }
   }
@@ -473,12 +521,23 @@ __device__ __forceinline__ uint32_t wave_reduce_sum(uint32_t x) {
   return x;
 }
 
+// A value for what is done where a pair ends, as the thread's index: lanes,
+// addresses and constants made from it there are not kept from the kernel's start
+// on, in registers that the rounds need (seven to thirteen of them were spilled).
+template <typename V> __device__ __forceinline__ V made_here(V x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
 __device__ __forceinline__ void clear_tile_lds(TileLds& lds) {
-  for (uint32_t i = threadIdx.x; i < kBins * kHistCopies; i += blockDim.x) lds.hist[i] = 0u;
-  if (threadIdx.x < 8u) lds.cnt[threadIdx.x] = 0u;
-  if (threadIdx.x == 0u) {
-    lds.max_abs = lds.max_rel = 0ull;
-    lds.first = ~0ull;
+  const uint32_t tid = made_here(threadIdx.x);
+  for (uint32_t i = tid; i < kAllBins * kHistCopies; i += blockDim.x) lds.hist[i] = 0u;
+  if (tid < 4u) lds.cnt[tid] = 0u;
+  if (tid < 2u) lds.any[tid] = 0u;
+  if (tid == 0u) {
+    const unsigned long long none = made_here(0ull);
+    lds.max_abs = lds.max_rel = none;
+    lds.first = ~none;
   }
 }
 
@@ -526,7 +585,7 @@ static_assert(sizeof(kc_cmp_result) == 61 * 8, "report layout");
 
 // One wave writes a pair's report; x: the accumulator word acc_of_word(lane).
 __device__ __forceinline__ void write_report(uint64_t n_elems, uint32_t dtype, uint64_t x, kc_cmp_result* r) {
-  const uint32_t lane = threadIdx.x % kWave;
+  const uint32_t lane = made_here(threadIdx.x) % kWave;
   const uint64_t rest = wave_sum_u64(lane > 10u && lane < 10u + kBins ? x : 0ull);  // counted at a distance above 0
   const uint64_t mis = __shfl(x, 1, 64), nb = __shfl(x, 4, 64), nc = __shfl(x, 5, 64), ng = __shfl(x, 6, 64);
   const uint64_t over = __shfl(x, 7, 64), not_close = __shfl(x, 59, 64);
@@ -546,7 +605,8 @@ __device__ __forceinline__ uint64_t found_word(const TileLds& lds, int i) {
   if (i == kAccMaxAbs) return lds.max_abs;
   if (i == kAccMaxRel) return lds.max_rel;
   if (i == kAccFirstInv) return ~lds.first;
-  return lds.cnt[i == kAccNotClose ? kCntNotClose : i];
+  if (i >= (int)kAccNanBoth && i <= (int)kAccNanGold) return lds.bins[kNanBins + (uint32_t)i - kAccNanBoth];
+  return lds.cnt[i == kAccMisElems ? kCntMis : i == kAccMisBytes ? kCntBytes : i == kAccOverTol ? kCntOver : kCntNotClose];
 }
 
 // Ends a workgroup's work on a pair; leaves lds clear.  DIRECT: it was the
@@ -558,9 +618,14 @@ __device__ __forceinline__ uint64_t found_word(const TileLds& lds, int i) {
 // 0.31 ms pass).
 template <bool DIRECT>
 __device__ __forceinline__ void end_pair(const CmpPairDev& pr, const Partial& p, unsigned long long* acc,
-                                         kc_cmp_result* res, TileLds& lds) {
-  const uint32_t tid = threadIdx.x, lane = tid & 63u;
-  if (!__syncthreads_or(p.any)) {  // nothing but equal elements, none NaN
+                                         kc_cmp_result* res, TileLds& lds, uint32_t& turn) {
+  const uint32_t tid = made_here(threadIdx.x), lane = tid & 63u;
+  // A wave past this barrier may reach the next pair's before another has read this flag: hence the turns.
+  uint32_t& any = lds.any[turn & 1u];
+  ++turn;
+  if (__ballot(p.any) != 0ull && lane == 0) any = 1u;
+  __syncthreads();
+  if (__builtin_amdgcn_readfirstlane(any) == 0u) {  // nothing but equal elements, none NaN
     if (DIRECT && tid < kWave) write_report(pr.n_elems, pr.dtype, 0ull, res);
     return;
   }
@@ -573,7 +638,7 @@ __device__ __forceinline__ void end_pair(const CmpPairDev& pr, const Partial& p,
     atomicAdd(&lds.cnt[kCntNotClose], v3);
   }
   // four threads per bin sum its copies (eight words each)
-  for (uint32_t i = tid; i < kBins * 4u; i += blockDim.x) {
+  for (uint32_t i = tid; i < kAllBins * 4u; i += blockDim.x) {
     const uint4* h = reinterpret_cast<const uint4*>(lds.hist + i * 8u);
     const uint4 x = h[0], y = h[1];
     uint32_t n = x.x + x.y + x.z + x.w + y.x + y.y + y.z + y.w;
@@ -602,7 +667,7 @@ constexpr uint64_t kMaxRun = 1ull << 30;
 template <uint32_t T, bool DIRECT>
 __device__ __forceinline__ void compare_tiles(const CmpPairDev& pr, uint64_t idx, uint64_t n, uint32_t tile_bytes,
                                               unsigned long long* acc, kc_cmp_result* res, TileLds& lds,
-                                              uint4* stage) {
+                                              uint4* stage, uint32_t& turn) {
   // The pair's maxima so far are thresholds below which nothing needs to be recorded (they only grow).
   Partial p{0, 0, 0, 0, false, 0.0, 0.0, 0.0};
   if (!DIRECT) {
@@ -612,7 +677,7 @@ __device__ __forceinline__ void compare_tiles(const CmpPairDev& pr, uint64_t idx
   const uint64_t end = min((idx + n) * tile_bytes, pr.n_elems * pr.esize);
   for (uint64_t b0 = idx * tile_bytes; b0 < end; b0 += kMaxRun)
     compare_bytes<T>(pr, b0, min(b0 + kMaxRun, end), p, lds, stage);
-  end_pair<DIRECT>(pr, p, acc, res, lds);
+  end_pair<DIRECT>(pr, p, acc, res, lds, turn);
 }
 
 // The tiles of workgroup b of a launch over n: consecutive ones, so that a
@@ -622,9 +687,7 @@ __device__ __forceinline__ uint32_t first_tile(uint32_t b, uint32_t n) {
   return b * each + min(b, more);
 }
 
-static_assert(kAccMisElems == kCntMis && kAccMisBytes == kCntBytes && kAccNanBoth == kCntNanBoth &&
-                  kAccNanCand == kCntNanCand && kAccNanGold == kCntNanGold && kAccOverTol == kCntOver,
-              "counter order");
+static_assert(kAccNanCand == kAccNanBoth + 1 && kAccNanGold == kAccNanBoth + 2, "order of the NaN classes");
 
 // T threads per workgroup: kThreads, or kWideThreads when the tiles are no more
 // than the CUs (a tile of 64 KiB is then one round).  DIRECT: every pair of the
@@ -638,12 +701,14 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) void k_c
   __shared__ __attribute__((aligned(16))) TileLds lds;
   clear_tile_lds(lds);
   __syncthreads();
+  uint32_t turn = 0;
   const uint32_t end = first_tile(blockIdx.x + 1u, n_tiles);
   for (uint32_t t = first_tile(blockIdx.x, n_tiles); t < end;) {
     const CmpTileDev tl = const_load(tiles + t);
     const CmpPairDev pr = const_load(pairs + tl.pair);
     const uint32_t n = min(end - t, pr.n_tiles - tl.idx);
-    compare_tiles<T, DIRECT>(pr, tl.idx, n, tile_bytes, acc_all + (uint64_t)tl.pair * kAccWords, res + tl.pair, lds, stage);
+    compare_tiles<T, DIRECT>(pr, tl.idx, n, tile_bytes, acc_all + (uint64_t)tl.pair * kAccWords, res + tl.pair, lds, stage,
+                             turn);
     t += n;
   }
 }
@@ -657,6 +722,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) void k_c
   __shared__ __attribute__((aligned(16))) TileLds lds;
   clear_tile_lds(lds);
   __syncthreads();
+  uint32_t turn = 0;
   const uint32_t end = first_tile(blockIdx.x + 1u, a.n_tiles);
   for (uint32_t t = first_tile(blockIdx.x, a.n_tiles); t < end;) {
     uint32_t lo = 0, hi = a.n - 1u;
@@ -666,7 +732,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) void k_c
     }
     const uint32_t start = lo == 0u ? 0u : a.tile_end[lo - 1u], n = min(end, a.tile_end[lo]) - t;
     compare_tiles<T, DIRECT>(a.pair[lo], t - start, n, tile_bytes, acc_all + (uint64_t)lo * kAccWords, res + lo, lds,
-                             stage);
+                             stage, turn);
     t += n;
   }
 }
