@@ -484,11 +484,23 @@ __device__ __forceinline__ void tile_body(const CmpPairDev& pr, uint64_t b0, uin
       return *reinterpret_cast<const B*>(x);
     };
     const double max_abs = p.max_abs, max_rel = p.max_rel;
-    for (; mask != 0; mask &= mask - 1) {
-      uint32_t at;
-      const uint32_t o = place(mask, at);
-      low = min(low, at);
-      element<DT>(get(cs, o), get(gs, o), tol, p, lds);
+    if constexpr (F::kind == 2) {  // raw bytes: the marks are all there is to know (256 MiB all off: 203 us one by one, so 117)
+      const uint32_t n = (uint32_t)(__popc(m[0]) + __popc(m[1]));
+      p.mis_elems += n;
+      p.mis_bytes += n;
+      if (n != 0u) {
+        const uint32_t half = m[0] == 0u ? 1u : 0u, x = half ? m[1] : m[0], word = x | (x >> 16);
+        const uint32_t top = 31u - (uint32_t)__clz((word | (word >> 8)) & 0xFFu);  // the half's lowest word: highest bit
+        const uint32_t j = half * 8u + 7u - top, k = (uint32_t)__builtin_ctz((x >> top) & 0x01010101u) >> 3;
+        low = ((j >> 2) * T + tid) * epv + (j & 3u) * 4u + k;
+      }
+    } else {
+      for (; mask != 0; mask &= mask - 1) {
+        uint32_t at;
+        const uint32_t o = place(mask, at);
+        low = min(low, at);
+        element<DT>(get(cs, o), get(gs, o), tol, p, lds);
+      }
     }
     share_found(p, max_abs, max_rel, round0, low, lds);
     asm volatile("" ::: "memory");

@@ -111,3 +111,35 @@ def test_nan_filled_time(kc, dt):
     assert us["NaN in both"] < 1.25 * us["all off"]
     assert us["NaN in one"] < 1.25 * us["all off"]
     ctx.close()
+
+
+def test_raw_bytes(kc):
+    """One differing byte at every place of a run, of a few runs and past the
+    last one, then all and half of them."""
+    rng = np.random.default_rng(9)
+    host = []
+    for n in (7, 300, 5000, 40000, 150001):
+        gold = rng.integers(0, 256, size=n, dtype=np.uint8)
+        spots = [[i] for i in list(range(min(n, 70))) + [n - 1, n // 2]]
+        spots += [rng.integers(0, n, size=3) for _ in range(4)] + [np.flatnonzero(rng.random(n) < 0.5), np.arange(n)]
+        for at in spots:
+            cand = gold.copy()
+            cand[at] ^= rng.integers(1, 256, size=len(at)).astype(np.uint8)
+            host.append((cand, gold))
+    check(kc, host, W.DT_U8, "raw bytes that differ at every place")
+
+
+def test_raw_bytes_time(kc):
+    """Raw bytes that all differ cost little more than equal ones."""
+    gold = torch.randint(0, 256, (128 << 20,), dtype=torch.uint8, device="cuda")
+    ctx = kc.Context(0)
+    us = {}
+    for name, cand in (("equal", gold.clone()), ("all off", gold ^ 3)):
+        say(f"compare contents: time, raw bytes, {name}")
+        ps = kc.PairSet(ctx, [(cand, gold, W.DT_U8, 0)])
+        res = kc.compare_pairset(ctx, ps)
+        us[name] = best_us(lambda: kc.compare_pairset(ctx, ps, res))
+        ps.close()
+    say(f"compare contents: {us}")
+    assert us["all off"] < 2.0 * us["equal"]
+    ctx.close()
