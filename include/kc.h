@@ -195,9 +195,11 @@ typedef struct {
 
 /* Launch shape of one operation.  Zero fields keep the built-in choice. */
 typedef struct {
-  uint32_t grid_per_cu; /* waves per compute unit (the compare: four-wave
-                           workgroups per compute unit), which stride over
-                           the work                                         */
+  uint32_t grid_per_cu; /* waves per compute unit, which stride over the work
+                           (the compare: four-wave workgroups per compute
+                           unit, each with an even run of it; where a run
+                           would exceed 512 KiB of each side, 1 MiB beyond
+                           16 GiB, the built-in runs)                       */
   uint32_t tile_bytes;  /* compare: bytes of each side per work item        */
   uint32_t per_item;    /* 1 = one launch per range / pair (no batching)    */
   uint32_t depth;       /* 0 to 4; accepted, without effect (every hashing

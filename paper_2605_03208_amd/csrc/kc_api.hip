@@ -808,11 +808,22 @@ bool compare_wide(const kc_ctx* c, uint64_t n_pairs, uint64_t n_tiles, uint32_t 
   return n_pairs == n_tiles && n_tiles <= c->n_cu && tile_bytes >= kCompareWideTile;
 }
 
-uint32_t compare_grid(const kc_ctx* c, uint64_t n_tiles, uint32_t tile_bytes) {
+CmpWalk compare_walk(const kc_ctx* c, uint64_t n_pairs, uint64_t n_tiles, uint32_t tile_bytes) {
   const uint64_t bytes = n_tiles * tile_bytes, per_cu = bytes / std::max(1u, c->n_cu);
-  if (per_cu < kCompareFewBytes) return grid_for(c, KC_OP_COMPARE, kCompareGridPerCu / 2u);
-  if (c->tune[KC_OP_COMPARE].grid_per_cu) return grid_for(c, KC_OP_COMPARE, 0);
-  return std::max(c->n_cu * kCompareGridPerCu, (uint32_t)std::min<uint64_t>(bytes / kCompareRunBytes, 1u << 22));
+  const uint32_t per = per_cu < kCompareFewBytes ? kCompareGridPerCu / 2u : kCompareGridPerCu;
+  const uint32_t even = (uint32_t)std::min<uint64_t>(grid_for(c, KC_OP_COMPARE, per), n_tiles);
+  const uint64_t run_bytes = bytes > kCompareLongBytes ? 2u * kCompareRunBytes : kCompareRunBytes;
+  if (bytes <= run_bytes * even) return CmpWalk{even, 0u, 0u};  // tuned grids too, unless their runs are longer
+  uint32_t run = 1, phases = 0;  // tiles of a whole run; halvings of it down to one tile
+  while (run * 2ull * tile_bytes <= run_bytes) {
+    run *= 2u;
+    ++phases;
+  }
+  const uint64_t taper = (run - 1ull) << kTaperShift;  // tiles of the shrinking runs
+  if (n_pairs < kTaperPairs || n_tiles < 2u * taper)
+    return CmpWalk{(uint32_t)((n_tiles + run - 1u) / run), run, 0xFFFFFFFFu};
+  const uint64_t whole = (n_tiles - taper) / run, rest = n_tiles - taper - whole * run;  // rest: one tile each at the end
+  return CmpWalk{(uint32_t)(whole + ((uint64_t)phases << kTaperShift) + rest), run, (uint32_t)whole};
 }
 
 }  // namespace kc
@@ -873,19 +884,21 @@ void fill_pair_tables(const kc_pair* pairs, uint32_t n_pairs, const std::vector<
 int run_compare(kc_ctx* c, const CmpPairDev* dpairs, const CmpTileDev* dtiles, const std::vector<uint64_t>& tile_off,
                 uint32_t n_pairs, uint32_t tile_bytes, unsigned long long* dacc, uint64_t acc_words, bool* acc_dirty,
                 kc_cmp_result* res_d, hipStream_t s) {
-  const uint32_t grid = compare_grid(c, tile_off[n_pairs], tile_bytes);
+  const CmpWalk walk = compare_walk(c, n_pairs, tile_off[n_pairs], tile_bytes);
   const bool direct = tile_off[n_pairs] == n_pairs;  // every pair one tile
   if (*acc_dirty) KC_HIP(launch_fill_u64(reinterpret_cast<uint64_t*>(dacc), acc_words, 0, s));
   *acc_dirty = true;
   {
     KernelTimer timer(c, KC_OP_COMPARE, s);
     if (!c->tune[KC_OP_COMPARE].per_item) {
-      KC_HIP(launch_compare(dpairs, dtiles, (uint32_t)tile_off[n_pairs], tile_bytes, dacc, res_d, grid,
+      KC_HIP(launch_compare(dpairs, dtiles, (uint32_t)tile_off[n_pairs], tile_bytes, dacc, res_d, walk,
                             compare_wide(c, n_pairs, tile_off[n_pairs], tile_bytes), direct, s));
     } else {
-      for (uint32_t i = 0; i < n_pairs; ++i)
-        KC_HIP(launch_compare(dpairs, dtiles + tile_off[i], (uint32_t)(tile_off[i + 1] - tile_off[i]), tile_bytes,
-                              dacc, res_d, grid, false, direct, s));
+      for (uint32_t i = 0; i < n_pairs; ++i) {
+        const uint32_t n = (uint32_t)(tile_off[i + 1] - tile_off[i]);
+        KC_HIP(launch_compare(dpairs, dtiles + tile_off[i], n, tile_bytes, dacc, res_d, compare_walk(c, 1, n, tile_bytes),
+                              false, direct, s));
+      }
     }
   }
   if (!direct) KC_HIP(launch_compare_finalize(dpairs, n_pairs, dacc, res_d, s));

@@ -692,11 +692,25 @@ __device__ __forceinline__ void compare_tiles(const CmpPairDev& pr, uint64_t idx
   end_pair<DIRECT>(pr, p, acc, res, lds, turn);
 }
 
-// The tiles of workgroup b of a launch over n: consecutive ones, so that a
-// workgroup meets few pairs and reads on where it was.
-__device__ __forceinline__ uint32_t first_tile(uint32_t b, uint32_t n) {
-  const uint32_t each = n / gridDim.x, more = n % gridDim.x;
-  return b * each + min(b, more);
+// The tiles [t, end) of this workgroup of a launch over n: consecutive ones, so
+// that a workgroup meets few pairs and reads on where it was.
+__device__ __forceinline__ void my_tiles(const CmpWalk& w, uint32_t n, uint32_t& t, uint32_t& end) {
+  const uint32_t b = blockIdx.x;
+  if (w.run == 0u) {
+    const uint32_t each = n / w.grid, more = n % w.grid;
+    t = b * each + min(b, more);
+    end = t + each + (b < more ? 1u : 0u);
+  } else if (b < w.whole) {
+    t = b * w.run;
+    end = min(t + w.run, n);
+  } else {  // kTaperRuns runs of each half of the last length, then single tiles
+    const uint32_t i = b - w.whole, k = i >> kTaperShift, phases = 31u - (uint32_t)__clz(w.run);
+    const bool single = k >= phases;
+    const uint32_t len = single ? 1u : w.run >> (k + 1u);
+    const uint32_t before = single ? phases : k;  // phases before this one
+    t = w.whole * w.run + ((w.run - (w.run >> before)) << kTaperShift) + (i - (before << kTaperShift)) * len;
+    end = min(t + len, n);
+  }
 }
 
 static_assert(kAccNanCand == kAccNanBoth + 1 && kAccNanGold == kAccNanBoth + 2, "order of the NaN classes");
@@ -708,14 +722,15 @@ static_assert(kAccNanCand == kAccNanBoth + 1 && kAccNanGold == kAccNanBoth + 2, 
 template <uint32_t T, bool DIRECT>
 __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) void k_compare(
     const CmpPairDev* pairs, const CmpTileDev* tiles, uint32_t n_tiles, uint32_t tile_bytes,
-    unsigned long long* acc_all, kc_cmp_result* res) {
+    unsigned long long* acc_all, kc_cmp_result* res, CmpWalk walk) {
   __shared__ uint4 stage[2 * kUnroll * T];
   __shared__ __attribute__((aligned(16))) TileLds lds;
   clear_tile_lds(lds);
   __syncthreads();
   uint32_t turn = 0;
-  const uint32_t end = first_tile(blockIdx.x + 1u, n_tiles);
-  for (uint32_t t = first_tile(blockIdx.x, n_tiles); t < end;) {
+  uint32_t t, end;
+  my_tiles(walk, n_tiles, t, end);
+  while (t < end) {
     const CmpTileDev tl = const_load(tiles + t);
     const CmpPairDev pr = const_load(pairs + tl.pair);
     const uint32_t n = min(end - t, pr.n_tiles - tl.idx);
@@ -729,14 +744,15 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) void k_c
 // belongs to the first pair whose inclusive tile prefix exceeds t.
 template <uint32_t T, bool DIRECT>
 __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) void k_compare_args(
-    CmpArgPairs a, uint32_t tile_bytes, unsigned long long* acc_all, kc_cmp_result* res) {
+    CmpArgPairs a, uint32_t tile_bytes, unsigned long long* acc_all, kc_cmp_result* res, CmpWalk walk) {
   __shared__ uint4 stage[2 * kUnroll * T];
   __shared__ __attribute__((aligned(16))) TileLds lds;
   clear_tile_lds(lds);
   __syncthreads();
   uint32_t turn = 0;
-  const uint32_t end = first_tile(blockIdx.x + 1u, a.n_tiles);
-  for (uint32_t t = first_tile(blockIdx.x, a.n_tiles); t < end;) {
+  uint32_t t, end;
+  my_tiles(walk, a.n_tiles, t, end);
+  while (t < end) {
     uint32_t lo = 0, hi = a.n - 1u;
     while (lo < hi) {
       const uint32_t mid = (lo + hi) >> 1;
@@ -782,7 +798,7 @@ __global__ __launch_bounds__(64) void k_compare_args_finalize(CmpArgPairs a, uns
 #define KC_COMPARE_CASE(KERNEL, W, D, ...)                                                                      \
   if (wide == W && direct == D) {                                                                               \
     constexpr uint32_t kT = W ? kWideThreads : kThreads;                                                        \
-    hipLaunchKernelGGL((KERNEL<kT, D>), dim3(grid), dim3(kT), 0, s, __VA_ARGS__);                               \
+    hipLaunchKernelGGL((KERNEL<kT, D>), dim3(walk.grid), dim3(kT), 0, s, __VA_ARGS__);                               \
   }
 #define KC_COMPARE_LAUNCH(KERNEL, ...)              \
   KC_COMPARE_CASE(KERNEL, true, true, __VA_ARGS__)  \
@@ -790,11 +806,10 @@ __global__ __launch_bounds__(64) void k_compare_args_finalize(CmpArgPairs a, uns
   KC_COMPARE_CASE(KERNEL, false, false, __VA_ARGS__)
 
 hipError_t launch_compare(const CmpPairDev* pairs, const CmpTileDev* tiles, uint32_t n_tiles, uint32_t tile_bytes,
-                          unsigned long long* acc, kc_cmp_result* res, uint32_t grid, bool wide, bool direct,
+                          unsigned long long* acc, kc_cmp_result* res, CmpWalk walk, bool wide, bool direct,
                           hipStream_t s) {
   if (n_tiles == 0) return hipSuccess;
-  grid = grid < 1u ? 1u : (grid > n_tiles ? n_tiles : grid);
-  KC_COMPARE_LAUNCH(k_compare, pairs, tiles, n_tiles, tile_bytes, acc, res)
+  KC_COMPARE_LAUNCH(k_compare, pairs, tiles, n_tiles, tile_bytes, acc, res, walk)
   return hipGetLastError();
 }
 
@@ -806,11 +821,10 @@ hipError_t launch_compare_finalize(const CmpPairDev* pairs, uint32_t n_pairs, un
 }
 
 hipError_t launch_compare_args(const CmpArgPairs& a, uint32_t tile_bytes, unsigned long long* acc,
-                               kc_cmp_result* res, uint32_t grid, bool wide, hipStream_t s) {
+                               kc_cmp_result* res, CmpWalk walk, bool wide, hipStream_t s) {
   if (a.n == 0) return hipSuccess;
-  grid = grid < 1u ? 1u : (grid > a.n_tiles ? a.n_tiles : grid);
   const bool direct = a.n_tiles == a.n;  // every pair one tile: the pass writes the reports
-  KC_COMPARE_LAUNCH(k_compare_args, a, tile_bytes, acc, res)
+  KC_COMPARE_LAUNCH(k_compare_args, a, tile_bytes, acc, res, walk)
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || direct) return e;
   hipLaunchKernelGGL(k_compare_args_finalize, dim3(a.n), dim3(64), 0, s, a, acc, res);

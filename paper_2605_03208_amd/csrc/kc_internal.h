@@ -235,19 +235,39 @@ static_assert(sizeof(CmpArgPairs) <= 3072, "kernel arguments");
 
 // Built-in grid of the compare, in workgroups per CU: twice what is resident
 // (four), so that CUs whose workgroups met few differing elements take another
-// one.  Each workgroup reads one run of consecutive tiles.  Measured at 2 / 4 /
-// 8 / 16 per CU: 10,000 uneven pairs of 8 GiB a side, 1e-4 of the elements off,
-// 2.48 / 2.52 / 2.54 / 2.57 ms; 768 MiB a side of mixed types with 11.3 % off
-// 0.47 / 0.39 / 0.35 / 0.35 ms.  With less than 1 MiB of tiles per CU, half as
-// many: the end of a run, and the adds of all workgroups at one pair's
-// accumulators, weigh more (4 / 8 per CU, 11.3 % off: 1000 pairs of 128 KiB 76 /
-// 100 us, 5 pairs of 167 MiB in all 119 / 135; 417 pairs of 548 MiB 301 / 293).
+// one.  Each workgroup reads one run of consecutive tiles.  With less than 1 MiB of
+// tiles per CU, half as many: the end of a run, and the adds of all workgroups at
+// one pair's accumulators, weigh more (4 / 8 per CU, 11.3 % off: 1000 pairs of 128
+// KiB 76 / 100 us, 5 pairs of 167 MiB in all 119 / 135; 417 pairs of 548 MiB 301 /
+// 293).
 constexpr uint32_t kCompareGridPerCu = 8;
-// Beyond 16 GiB a side, more, of 8 MiB each: the workgroups in flight then cover
-// a window of the buffers (200 pairs of 150 MiB, all equal, runs of 30 / 7.5 /
-// 0.5 MiB a side: 9.23 / 9.16 / 9.05 ms).
 constexpr uint64_t kCompareFewBytes = 1u << 20;
-constexpr uint64_t kCompareRunBytes = 8u << 20;
+// Larger compares take runs of a fixed length instead, which the hardware hands out
+// in order as workgroups end: a run whose elements all differ costs its workgroup
+// many times an equal one (0.2, 0.4 and 0.8 ms per MiB of f32, bf16 and fp8), and
+// with even runs of 4 to 15 MiB one wrong output among many right ones was the
+// work of a few workgroups while the chip waited (10,000 uneven pairs, the last of
+// 10 MiB all off, f32 / bf16 / fp8: 3.30 / 4.37 / 6.75 ms, so 2.51 / 2.53 / 2.57, all
+// equal 2.49; 200 pairs of 150 MiB, the last all off as fp8: 17.1 ms, so 9.2, all
+// equal 8.8).  Shorter runs cost nothing while pairs are many (those 10,000 of 8 GiB
+// a side, runs of 4 / 1 / 0.5 / 0.25 MiB: equal 2.58 / 2.57 / 2.55 / 2.54 ms, 11.3 %
+// off 2.79 / 2.66 / 2.63 / 2.61), but about 0.1 us each at one pair's accumulators
+// when elements differ (one pair of 1 GiB, 1e-4 off, runs of 0.5 / 0.25 / 0.13 MiB:
+// 350 / 413 / 781 us; 200 pairs of 150 MiB, runs of 1.8 / 0.9 / 0.5 MiB: 9.33 / 9.37 /
+// 9.49 ms).
+constexpr uint64_t kCompareRunBytes = 512u << 10;      // 1 MiB beyond kCompareLongBytes
+constexpr uint64_t kCompareLongBytes = 16ull << 30;    // of a side
+// Of lists of at least kTaperPairs pairs the end is cut finer: after the whole runs
+// kTaperRuns of half a run, as many of a quarter, and so on to one tile, so that
+// what differs at the very end is shared out as well.  With fewer pairs those runs
+// would meet at one pair's accumulators.
+constexpr uint32_t kTaperShift = 9, kTaperRuns = 1u << kTaperShift, kTaperPairs = 16;
+
+// The tiles of each workgroup of a compare: the first `whole` take `run` tiles (a
+// power of two) each, the others shrinking runs; run 0: all tiles shared out evenly.
+struct CmpWalk {
+  uint32_t grid, run, whole;
+};
 
 // Tile of a small compare: when the pairs are no more than the CUs and none is
 // larger than this, each gets a workgroup of 1024 threads, which reads it in one
@@ -302,21 +322,21 @@ hipError_t launch_oob_emit(const Tile* tiles, uint32_t n_tiles, const ScanDev& s
 // wide: workgroups of 1024 threads.  direct: every pair is one tile and the pass writes the reports (else the
 // finalize does).
 hipError_t launch_compare(const CmpPairDev* pairs, const CmpTileDev* tiles, uint32_t n_tiles, uint32_t tile_bytes,
-                          unsigned long long* acc, kc_cmp_result* res, uint32_t grid, bool wide, bool direct,
+                          unsigned long long* acc, kc_cmp_result* res, CmpWalk walk, bool wide, bool direct,
                           hipStream_t s);
 hipError_t launch_compare_finalize(const CmpPairDev* pairs, uint32_t n_pairs, unsigned long long* acc,
                                    kc_cmp_result* res, hipStream_t s);
 // The pass and the reports of the pairs in `a` (accumulators acc[pair * kAccWords ...], zero on entry and
 // zeroed again; reports res[0 .. a.n)).
 hipError_t launch_compare_args(const CmpArgPairs& a, uint32_t tile_bytes, unsigned long long* acc,
-                               kc_cmp_result* res, uint32_t grid, bool wide, hipStream_t s);
+                               kc_cmp_result* res, CmpWalk walk, bool wide, hipStream_t s);
 
 // ---- shared host helpers (kc_api.hip) ----------------------------------------
 uint32_t grid_for(const kc_ctx* c, uint32_t op, uint32_t fallback_per_cu);  // persistent grid of an op
 uint32_t elem_size(uint32_t dtype);                                         // bytes of one element
 uint32_t compare_tile_bytes(const kc_ctx* c, const kc_pair* pairs, uint32_t n_pairs);
 bool compare_wide(const kc_ctx* c, uint64_t n_pairs, uint64_t n_tiles, uint32_t tile_bytes);  // 1024-thread workgroups
-uint32_t compare_grid(const kc_ctx* c, uint64_t n_tiles, uint32_t tile_bytes);
+CmpWalk compare_walk(const kc_ctx* c, uint64_t n_pairs, uint64_t n_tiles, uint32_t tile_bytes);
 
 // ---- the compare that allocates nothing (kc_noalloc.hip) ---------------------
 // Looks up, once per device, the device address of the static scratch array

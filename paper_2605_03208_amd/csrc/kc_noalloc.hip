@@ -112,8 +112,8 @@ int kc_compare_noalloc(kc_ctx* c, const kc_pair* pairs, uint32_t n_pairs, kc_cmp
       a.tile_end[j] = (uint32_t)t;
     }
     a.n_tiles = (uint32_t)t;
-    const uint32_t grid = compare_grid(c, t, tile_bytes);
-    KC_HIP(launch_compare_args(a, tile_bytes, acc + (uint64_t)b0 * kAccWords, res_d + b0, grid,
+    const CmpWalk walk = compare_walk(c, a.n, t, tile_bytes);
+    KC_HIP(launch_compare_args(a, tile_bytes, acc + (uint64_t)b0 * kAccWords, res_d + b0, walk,
                                compare_wide(c, a.n, t, tile_bytes), s));
   }
   return KC_OK;
