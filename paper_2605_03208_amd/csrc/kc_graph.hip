@@ -2,8 +2,8 @@
 // the pointer graph between ranges and the per-range byte difference against
 // a snapshot.  Same execution model as the snapshot kernels: persistent grids
 // of 64-lane waves over the 16-page tile list, range fences in LDS (the graph:
-// up to eight waves per workgroup sharing the wide table; the region diff:
-// one wave per workgroup).
+// up to eight waves per workgroup sharing the wide table; the region diff: up to
+// four for pages, up to sixteen for larger units).
 #include <algorithm>
 
 #include "kc_device.h"
@@ -86,183 +86,231 @@ __device__ __forceinline__ void flush_region(kc_region_diff_result* res, int32_t
   atomicMin((unsigned long long*)&r->first_diff_va, (unsigned long long)first);
 }
 
-// Groups of `tpg` consecutive tiles (four, one of units above 4 KiB) are taken
-// one lane per unit: each lane resolves its unit's snapshot copy and changed bit,
-// then the changed units are compared two at a time, and what differs is added up
-// per unit in LDS.  SHARE (larger units): the waves of a workgroup share out the
-// 4 KiB blocks of a unit.  Else each wave takes groups of its own.  Runs of
-// groups are contiguous and folded per range, which touches a range's counters
-// only when the run moves to the next range or ends (for the waves of a
-// workgroup together, where they end in one range): folds that all add into one
-// range's counters as they go queue on those addresses.  The bytes of the changed
-// units bound it, and with few of them a chain of three round trips per group.
-// Measured against one wave per unit, 2048 waves: 6.3 GiB in 2 MiB units with 5 %
-// of the pages changed 25.0 -> 2.2 ms, 3.9 GiB in 64 KiB units with 1 % 0.53 ->
-// 0.25 ms; pages: 2 GiB with 50 % changed 439 -> 394 us, 4.2 GiB in one range
-// with 1 % 98 -> 65 us.
-constexpr uint32_t kDiffWaves = 16, kDiffApart = 4;
+// What one lane knows of its unit: its place, its snapshot copy (gp: address; zero:
+// all zeros; bad: none that is accepted), whether its bytes are to be compared.
+struct DiffUnit {
+  uint64_t va, gp;
+  int32_t a;  // range
+  uint32_t len;
+  bool live, zero, bad, need;
+};
+__device__ __forceinline__ DiffUnit diff_unit(const Tile& tile, uint32_t j, uint32_t ushift, const FenceLds& fences,
+                                              const RangeTable& rt, const uint64_t* changed_bm,
+                                              const uint64_t* gold_zero_bm, const uint64_t* rank_prefix,
+                                              const uint64_t* gold_page_va, uint64_t n_valid,
+                                              const uint8_t* gold_packed) {
+  DiffUnit u{};
+  u.a = -1;
+  u.live = j < tile.npages;
+  u.va = tile.va + ((uint64_t)j << ushift);
+  if (!u.live) return u;
+  const uint64_t g = (uint64_t)tile.g + j;
+  u.len = unit_bytes(tile, j, 1u << ushift);
+  u.a = range_index(u.va, fences, rt);
+  const uint64_t zw = gold_zero_bm[g >> 6];
+  u.zero = (zw >> (g & 63u)) & 1ull;
+  if (!u.zero) {
+    const uint64_t slot = rank_prefix[g >> 6] + (uint64_t)__popcll(~zw & ((1ull << (g & 63u)) - 1ull));
+    u.bad = slot >= n_valid || gold_page_va[slot] != u.va;
+    u.gp = (uint64_t)gold_packed + (slot << ushift);
+  }
+  u.need = !u.bad && ((changed_bm[g >> 6] >> (g & 63u)) & 1ull);
+  return u;
+}
 
-template <bool SHARE>
-__global__ __launch_bounds__((SHARE ? kDiffWaves : kDiffApart) * kWave) __attribute__((amdgpu_waves_per_eu(4))) void
-k_region_diff(const Tile* tiles, uint32_t n_tiles, uint32_t tpg, RangeTable rt, const uint64_t* changed_bm,
-              const uint64_t* gold_zero_bm, const uint64_t* rank_prefix, const uint64_t* gold_page_va,
-              const uint64_t* gold_n_kept, uint64_t cap, const uint8_t* gold_packed, kc_region_diff_result* res,
-              uint32_t ushift) {
-  constexpr uint32_t kRows = SHARE ? 2u : kDiffApart;
+// The lane's part of a 16-byte block's difference: bytes that differ, and the
+// lowest of them (off: the block's offset) unless there is one already.
+__device__ __forceinline__ void add_diff(const uint4& c, const uint4& d, uint32_t off, uint32_t& nd, uint32_t& fo) {
+  const uint32_t x[4] = {c.x ^ d.x, c.y ^ d.y, c.z ^ d.z, c.w ^ d.w};
+#pragma unroll
+  for (uint32_t i = 0; i < 4; ++i) {
+    nd += nonzero_bytes(x[i]);
+    if (x[i] != 0u && fo == ~0u) fo = off + 4u * i + ((uint32_t)__builtin_ctz(x[i]) >> 3);
+  }
+}
+
+// The range that a wave is adding up, and its totals so far.
+struct DiffFold {
+  int32_t cur = -1;
+  uint64_t bytes = 0, pages = 0, first = ~0ull;
+  __device__ __forceinline__ void add(kc_region_diff_result* res, bool writes, int32_t a, uint64_t b, uint64_t p, uint64_t at) {
+    if (a != cur) {
+      if (writes) flush_region(res, cur, bytes, pages, first);
+      cur = a;
+      bytes = pages = 0;
+      first = ~0ull;
+    }
+    bytes += b;
+    pages += p;
+    first = min(first, at);
+  }
+};
+
+// Pages.  A wave takes groups of four consecutive tiles, one lane per page: each
+// lane resolves its page's snapshot copy and changed bit, then the whole wave
+// compares the changed pages one after another, 8 KiB in flight, and adds up what
+// differs in registers.  Runs of groups are contiguous and folded per range, which
+// touches a range's counters only when the run moves to the next range or ends (for
+// the waves of a workgroup together, where they end in one range): folds that all
+// add into one range's counters as they go queue on those addresses.
+//
+// What bounds it: the bytes of the changed pages, and with few of them a chain of
+// three round trips per group; hence few registers and as many waves as are
+// resident (20 per CU with these; the built-in grid of 16 suits dense changes
+// better).  30 GiB with 1 % / 0.1 % of the pages changed: 148 / 71 us, at 20 waves
+// per CU 134 / 64; two pages at a time with their sums in LDS, as the larger units
+// below: 203 / 90.  One wave per workgroup: 4.2 GiB in one range, 1 % changed, 146
+// us, four 54; 2 GiB in 4096 ranges, half changed, 365 and 340, eight 377.
+constexpr uint32_t kDiffWaves = 16, kDiffPageWaves = 4;
+
+__global__ __launch_bounds__(kDiffPageWaves * kWave) __attribute__((amdgpu_waves_per_eu(5))) void k_region_diff_pages(
+    const Tile* tiles, uint32_t n_tiles, RangeTable rt, const uint64_t* changed_bm, const uint64_t* gold_zero_bm,
+    const uint64_t* rank_prefix, const uint64_t* gold_page_va, const uint64_t* gold_n_kept, uint64_t cap,
+    const uint8_t* gold_packed, kc_region_diff_result* res) {
   __shared__ FenceLds fences;
-  __shared__ uint32_t unit_off[kRows][kWave], unit_first[kRows][kWave];  // of a group's units; SHARE: groups take turns
-  __shared__ int32_t end_range[kDiffApart];  // where the runs of the waves end
-  __shared__ uint64_t end_bytes[kDiffApart], end_pages[kDiffApart], end_first[kDiffApart];
+  __shared__ int32_t end_range[kDiffPageWaves];  // where the runs of the waves end
+  __shared__ uint64_t end_bytes[kDiffPageWaves], end_pages[kDiffPageWaves], end_first[kDiffPageWaves];
   const uint32_t lane = threadIdx.x % kWave, sub = lane >> 4, j = lane & 15u, wpb = blockDim.x / kWave;
   const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const uint32_t unit = 1u << ushift;
   load_fences(fences, rt, threadIdx.x, blockDim.x);
-  if (wv < kRows) {
-    unit_off[wv][lane] = 0u;
-    unit_first[wv][lane] = ~0u;
+  __syncthreads();
+  const uint64_t n_valid = min(*gold_n_kept, cap);
+  const uint32_t n_groups = (n_tiles + 3u) / 4u, n_runs = gridDim.x * wpb;
+  const uint32_t per_run = (n_groups + n_runs - 1u) / n_runs;
+  const uint32_t gbeg = min((blockIdx.x * wpb + wv) * per_run, n_groups), gend = min(gbeg + per_run, n_groups);
+  DiffFold fold;
+  for (uint32_t gi = gbeg; gi < gend; ++gi) {
+    Tile tile{0, 0, 0};
+    if (gi * 4u + sub < n_tiles) tile = tiles[gi * 4u + sub];
+    const DiffUnit u = diff_unit(tile, j, kMinUnitShift, fences, rt, changed_bm, gold_zero_bm, rank_prefix, gold_page_va,
+                                 n_valid, gold_packed);
+    const uint64_t bad_mask = __ballot(u.bad);
+    if (j == 0u && u.live && u.a >= 0) {  // the 16 lanes of a tile share its range
+      const uint32_t nb = (uint32_t)__popcll((bad_mask >> (16u * sub)) & 0xFFFFull);
+      if (nb) atomicAdd((unsigned long long*)&res[u.a].n_bad_pages, (unsigned long long)nb);
+    }
+    for (uint64_t m = __ballot(u.need); m != 0ull; m &= m - 1ull) {
+      const int32_t L = __ffsll((long long)m) - 1;
+      const uint64_t pva = __shfl((unsigned long long)u.va, L, 64), pgp = __shfl((unsigned long long)u.gp, L, 64);
+      const bool pz = __shfl((int)u.zero, L, 64) != 0;
+      const uint32_t plen = __shfl(u.len, L, 64);  // of a range's last page perhaps less than a page
+      uint32_t nd = 0u, fo = ~0u;
+#pragma unroll
+      for (uint32_t k = 0; k < 4; ++k) {
+        const uint32_t off = k * 1024u + lane * 16u;
+        const uint4 c = off < plen ? clip16(ld16nt(pva + off), off, plen) : make_uint4(0, 0, 0, 0);
+        const uint4 d = pz || off >= plen ? make_uint4(0, 0, 0, 0) : clip16(ld16nt(pgp + off), off, plen);
+        add_diff(c, d, off, nd, fo);
+      }
+      nd = wave_sum_u32(nd);
+#pragma unroll
+      for (int dd = 32; dd >= 1; dd >>= 1) fo = min(fo, (uint32_t)__shfl_xor(fo, dd, 64));
+      if (nd) fold.add(res, lane == 0, __shfl(u.a, L, 64), nd, 1u, pva + fo);
+    }
   }
-  if (SHARE && wpb == 1u) {
-    unit_off[1][lane] = 0u;
-    unit_first[1][lane] = ~0u;
+  if (wpb == 1u) {
+    if (lane == 0) flush_region(res, fold.cur, fold.bytes, fold.pages, fold.first);
+    return;
+  }
+  if (lane == 0) {
+    end_range[wv] = fold.cur;
+    end_bytes[wv] = fold.bytes;
+    end_pages[wv] = fold.pages;
+    end_first[wv] = fold.first;
   }
   __syncthreads();
-  const uint64_t kept = *gold_n_kept;
-  const uint64_t n_valid = kept < cap ? kept : cap;
-  const uint32_t n_groups = (n_tiles + tpg - 1u) / tpg;
-  const uint32_t n_runs = SHARE ? gridDim.x : gridDim.x * wpb, run = SHARE ? blockIdx.x : blockIdx.x * wpb + wv;
-  const uint32_t per_run = (n_groups + n_runs - 1u) / n_runs;
-  const uint32_t gbeg = min(run * per_run, n_groups), gend = min(gbeg + per_run, n_groups);
-  int32_t cur = -1;  // the range being folded (SHARE: by the first wave), and its totals so far
-  uint64_t dbytes = 0, dpages = 0, first = ~0ull;
-  uint32_t row = SHARE ? 0u : wv;
-  for (uint32_t gi = gbeg; gi < gend; ++gi) {
-    const uint32_t t = gi * tpg + sub;
+  if (threadIdx.x != 0) return;
+  for (uint32_t w = 1; w < wpb; ++w)  // the next wave's run follows: its range is this one or a later one
+    if (end_range[w] >= 0) fold.add(res, true, end_range[w], end_bytes[w], end_pages[w], end_first[w]);
+  flush_region(res, fold.cur, fold.bytes, fold.pages, fold.first);
+}
+
+// Larger units, which are few: a workgroup takes a tile at a time, its waves share
+// out the 4 KiB blocks of the changed units, two units at a time, what differs is
+// added up per unit in LDS, and the first wave folds it per range as above.
+// Measured against one wave per unit, 2048 waves: 6.3 GiB in 2 MiB units with 5 %
+// of the pages changed 25.0 -> 2.2 ms, 3.9 GiB in 64 KiB units with 1 % 0.53 -> 0.25.
+__global__ __launch_bounds__(kDiffWaves * kWave) __attribute__((amdgpu_waves_per_eu(4))) void k_region_diff_units(
+    const Tile* tiles, uint32_t n_tiles, RangeTable rt, const uint64_t* changed_bm, const uint64_t* gold_zero_bm,
+    const uint64_t* rank_prefix, const uint64_t* gold_page_va, const uint64_t* gold_n_kept, uint64_t cap,
+    const uint8_t* gold_packed, kc_region_diff_result* res, uint32_t ushift) {
+  __shared__ FenceLds fences;
+  __shared__ uint32_t unit_off[2][kWave], unit_first[2][kWave];  // of a tile's units; changed tiles take turns
+  const uint32_t lane = threadIdx.x % kWave, wpb = blockDim.x / kWave;
+  const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  load_fences(fences, rt, threadIdx.x, blockDim.x);
+  for (uint32_t i = threadIdx.x; i < 2u * kWave; i += blockDim.x) {
+    unit_off[i / kWave][i % kWave] = 0u;
+    unit_first[i / kWave][i % kWave] = ~0u;
+  }
+  __syncthreads();
+  const uint64_t n_valid = min(*gold_n_kept, cap);
+  const uint32_t per_run = (n_tiles + gridDim.x - 1u) / gridDim.x;
+  const uint32_t tbeg = min(blockIdx.x * per_run, n_tiles), tend = min(tbeg + per_run, n_tiles);
+  DiffFold fold;  // of the first wave
+  uint32_t row = 0u;
+  for (uint32_t t = tbeg; t < tend; ++t) {
     Tile tile{0, 0, 0};
-    if (sub < tpg && t < n_tiles) tile = tiles[t];
-    const bool live = j < tile.npages;
-    const uint64_t g = (uint64_t)tile.g + j, va = tile.va + ((uint64_t)j << ushift);
-    bool zero = false, bad = false, need = false;
-    uint64_t gp = 0;
-    int32_t a = -1;
-    const uint32_t len = live ? unit_bytes(tile, j, unit) : 0u;
-    if (live) {
-      a = range_index(va, fences, rt);
-      const uint64_t zw = gold_zero_bm[g >> 6];
-      zero = (zw >> (g & 63u)) & 1ull;
-      if (!zero) {
-        const uint64_t slot = rank_prefix[g >> 6] + (uint64_t)__popcll(~zw & ((1ull << (g & 63u)) - 1ull));
-        bad = slot >= n_valid || gold_page_va[slot] != va;
-        gp = (uint64_t)gold_packed + (slot << ushift);
-      }
-      need = !bad && ((changed_bm[g >> 6] >> (g & 63u)) & 1ull);
-    }
-    const uint64_t bad_mask = __ballot(bad);
-    if ((!SHARE || wv == 0) && j == 0u && live && a >= 0) {  // the 16 lanes of a tile share its range
-      const uint32_t nb = (uint32_t)__popcll((bad_mask >> (16u * sub)) & 0xFFFFull);
-      if (nb) atomicAdd((unsigned long long*)&res[a].n_bad_pages, (unsigned long long)nb);
-    }
-    uint64_t need_mask = __ballot(need);  // SHARE: the same in every wave
+    if (lane < kTilePages) tile = tiles[t];
+    const DiffUnit u = diff_unit(tile, lane, ushift, fences, rt, changed_bm, gold_zero_bm, rank_prefix, gold_page_va,
+                                 n_valid, gold_packed);
+    const uint32_t n_bad = (uint32_t)__popcll(__ballot(u.bad));
+    if (wv == 0 && lane == 0u && u.a >= 0 && n_bad != 0u)  // the units of a tile share its range
+      atomicAdd((unsigned long long*)&res[u.a].n_bad_pages, (unsigned long long)n_bad);
+    const uint64_t need_mask = __ballot(u.need);  // the same in every wave
     if (need_mask == 0ull) continue;
     uint32_t* const s_off = unit_off[row];
     uint32_t* const s_first = unit_first[row];
-    if (SHARE) row ^= 1u;
+    row ^= 1u;
     for (uint64_t m = need_mask; m != 0ull;) {  // two units at a time: 16 KiB in flight
       int32_t L[2];
       uint64_t pva[2], pgp[2];
       uint32_t plen[2], nd[2] = {0u, 0u}, fo[2] = {~0u, ~0u};  // bytes of the unit (a range's last may be partial)
       bool pz[2];
 #pragma unroll
-      for (uint32_t u = 0; u < 2; ++u) {
-        L[u] = m ? __ffsll((long long)m) - 1 : 0;
-        pva[u] = __shfl((unsigned long long)va, L[u], 64);
-        pgp[u] = __shfl((unsigned long long)gp, L[u], 64);
-        pz[u] = __shfl((int)zero, L[u], 64) != 0;
-        plen[u] = m ? __shfl(len, L[u], 64) : 0u;
+      for (uint32_t i = 0; i < 2; ++i) {
+        L[i] = m ? __ffsll((long long)m) - 1 : 0;
+        pva[i] = __shfl((unsigned long long)u.va, L[i], 64);
+        pgp[i] = __shfl((unsigned long long)u.gp, L[i], 64);
+        pz[i] = __shfl((int)u.zero, L[i], 64) != 0;
+        plen[i] = m ? __shfl(u.len, L[i], 64) : 0u;
         m &= m - 1ull;
       }
-      for (uint32_t o0 = SHARE ? wv * kPage : 0u; o0 < max(plen[0], plen[1]); o0 += SHARE ? wpb * kPage : kPage) {  // in address order
+      for (uint32_t o0 = wv * kPage; o0 < max(plen[0], plen[1]); o0 += wpb * kPage) {  // in address order
         uint4 c[8], d[8];
 #pragma unroll
         for (uint32_t k = 0; k < 8; ++k) {
-          const uint32_t u = k >> 2, off = o0 + (k & 3u) * 1024u + lane * 16u;
-          c[k] = off < plen[u] ? clip16(ld16nt(pva[u] + off), off, plen[u]) : make_uint4(0, 0, 0, 0);
-          d[k] = pz[u] || off >= plen[u] ? make_uint4(0, 0, 0, 0) : clip16(ld16nt(pgp[u] + off), off, plen[u]);
+          const uint32_t i = k >> 2, off = o0 + (k & 3u) * 1024u + lane * 16u;
+          c[k] = off < plen[i] ? clip16(ld16nt(pva[i] + off), off, plen[i]) : make_uint4(0, 0, 0, 0);
+          d[k] = pz[i] || off >= plen[i] ? make_uint4(0, 0, 0, 0) : clip16(ld16nt(pgp[i] + off), off, plen[i]);
         }
 #pragma unroll
-        for (uint32_t k = 0; k < 8; ++k) {
-          const uint32_t u = k >> 2, off = o0 + (k & 3u) * 1024u + lane * 16u;
-          const uint32_t x[4] = {c[k].x ^ d[k].x, c[k].y ^ d[k].y, c[k].z ^ d[k].z, c[k].w ^ d[k].w};
-#pragma unroll
-          for (uint32_t i = 0; i < 4; ++i) {
-            nd[u] += nonzero_bytes(x[i]);
-            if (x[i] != 0u && fo[u] == ~0u) fo[u] = off + 4u * i + ((uint32_t)__builtin_ctz(x[i]) >> 3);
-          }
-        }
+        for (uint32_t k = 0; k < 8; ++k) add_diff(c[k], d[k], o0 + (k & 3u) * 1024u + lane * 16u, nd[k >> 2], fo[k >> 2]);
       }
 #pragma unroll
-      for (uint32_t u = 0; u < 2; ++u) {
-        if (__ballot(nd[u] != 0u) == 0ull) continue;
-        nd[u] = wave_sum_u32(nd[u]);
+      for (uint32_t i = 0; i < 2; ++i) {
+        if (__ballot(nd[i] != 0u) == 0ull) continue;
+        nd[i] = wave_sum_u32(nd[i]);
 #pragma unroll
-        for (int dd = 32; dd >= 1; dd >>= 1) {
-          const uint32_t y = __shfl_xor(fo[u], dd, 64);
-          fo[u] = y < fo[u] ? y : fo[u];
-        }
+        for (int dd = 32; dd >= 1; dd >>= 1) fo[i] = min(fo[i], (uint32_t)__shfl_xor(fo[i], dd, 64));
         if (lane == 0) {
-          atomicAdd(&s_off[L[u]], nd[u]);
-          atomicMin(&s_first[L[u]], fo[u]);
+          atomicAdd(&s_off[L[i]], nd[i]);
+          atomicMin(&s_first[L[i]], fo[i]);
         }
       }
     }
-    if (SHARE) {
-      __syncthreads();  // the one barrier per changed group: sums two apart share a row
-      if (wv != 0) continue;
-    }
-    wave_lds_order();
+    __syncthreads();  // the one barrier per changed tile: sums two apart share a row
+    if (wv != 0) continue;
     const uint32_t nd = s_off[lane], fo = s_first[lane];
     s_off[lane] = 0u;
     s_first[lane] = ~0u;
-    for (uint64_t diff = __ballot(nd != 0u); diff != 0ull;) {
-      const int32_t L = __ffsll((long long)diff) - 1;
-      const int32_t pa = __shfl(a, L, 64);
-      const uint64_t same = __ballot(nd != 0u && a == pa);
-      if (pa != cur) {
-        if (lane == 0) flush_region(res, cur, dbytes, dpages, first);
-        cur = pa;
-        dbytes = dpages = 0;
-        first = ~0ull;
-      }
-      dbytes += wave_sum_u32(a == pa ? nd : 0u);  // 64 units of 2 MiB at most
-      dpages += (uint64_t)__popcll(same);
-      if (first == ~0ull) first = __shfl((unsigned long long)va, L, 64) + __shfl(fo, L, 64);  // units ascend
-      diff &= ~same;
-    }
+    const uint64_t diff = __ballot(nd != 0u);
+    if (diff == 0ull) continue;
+    const int32_t L = __ffsll((long long)diff) - 1;  // the lowest unit that differs: units ascend
+    const uint64_t first = __shfl((unsigned long long)u.va, L, 64) + __shfl(fo, L, 64);
+    fold.add(res, lane == 0, __shfl(u.a, L, 64), wave_sum_u32(nd), (uint64_t)__popcll(diff), first);  // 16 units of 2 MiB at most
   }
-  if (SHARE) {
-    if (threadIdx.x == 0) flush_region(res, cur, dbytes, dpages, first);
-    return;
-  }
-  if (lane == 0) {
-    end_range[wv] = cur;
-    end_bytes[wv] = dbytes;
-    end_pages[wv] = dpages;
-    end_first[wv] = first;
-  }
-  __syncthreads();
-  if (threadIdx.x != 0) return;
-  for (uint32_t w = 1; w < wpb; ++w) {  // the next wave's run follows: its range is this one or a later one
-    if (end_range[w] < 0) continue;
-    if (end_range[w] != cur) {
-      flush_region(res, cur, dbytes, dpages, first);
-      cur = end_range[w];
-      dbytes = dpages = 0;
-      first = ~0ull;
-    }
-    dbytes += end_bytes[w];
-    dpages += end_pages[w];
-    first = min(first, end_first[w]);
-  }
-  flush_region(res, cur, dbytes, dpages, first);
+  if (threadIdx.x == 0) flush_region(res, fold.cur, fold.bytes, fold.pages, fold.first);
 }
 
 }  // namespace
@@ -294,17 +342,18 @@ hipError_t launch_region_diff(const Tile* tiles, uint32_t n_tiles, const RangeTa
                               kc_region_diff_result* res, uint32_t ushift, uint32_t grid, uint32_t n_cu,
                               hipStream_t s) {
   if (n_tiles == 0) return hipSuccess;
-  // Pages: four waves per workgroup, each with runs of four tiles.  Larger units, which are few: a tile at a time, a
-  // wave for each 16 KiB of a unit, eight waves per CU and two workgroups at least.  grid counts waves.
+  // grid counts waves.  Pages: a group of four tiles per wave at least, the waves of a workgroup few while there are few
+  // of them.  Larger units: a wave for each 16 KiB of a unit, and two workgroups per CU at least.
   if (ushift == kMinUnitShift) {
-    const uint32_t blocks = std::max(1u, std::min(blocks_for(grid, kDiffApart), blocks_for(n_tiles, 4u * kDiffApart)));
-    hipLaunchKernelGGL((k_region_diff<false>), dim3(blocks), dim3(kDiffApart * kWave), 0, s, tiles, n_tiles, 4u, rt,
-                       changed_bm, gold_zero_bm, rank_prefix, gold_page_va, gold_n_kept, cap, gold_packed, res, ushift);
+    const uint32_t waves = std::max(1u, std::min(grid, blocks_for(n_tiles, 4u)));
+    const uint32_t wpb = std::min(kDiffPageWaves, std::max(1u, waves / n_cu)), blocks = blocks_for(waves, wpb);
+    hipLaunchKernelGGL(k_region_diff_pages, dim3(blocks), dim3(wpb * kWave), 0, s, tiles, n_tiles, rt, changed_bm,
+                       gold_zero_bm, rank_prefix, gold_page_va, gold_n_kept, cap, gold_packed, res);
     return hipGetLastError();
   }
   const uint32_t wpb = std::max(1u, std::min(kDiffWaves, (1u << ushift) >> 14));
   const uint32_t blocks = std::max(1u, std::min(std::max(2u * n_cu, grid / wpb), n_tiles));
-  hipLaunchKernelGGL((k_region_diff<true>), dim3(blocks), dim3(wpb * kWave), 0, s, tiles, n_tiles, 1u, rt, changed_bm,
+  hipLaunchKernelGGL(k_region_diff_units, dim3(blocks), dim3(wpb * kWave), 0, s, tiles, n_tiles, rt, changed_bm,
                      gold_zero_bm, rank_prefix, gold_page_va, gold_n_kept, cap, gold_packed, res, ushift);
   return hipGetLastError();
 }
