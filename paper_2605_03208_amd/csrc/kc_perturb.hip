@@ -173,10 +173,9 @@ __device__ __forceinline__ void vec_set(uint32_t (&x)[4], uint32_t e, uint32_t w
   }
 }
 
-// Candidates in one pass, for blocks that span at least kRunBlockBytes: a wave
-// copies one piece of a buffer (8 KiB, all its loads in flight before the first
-// store), the pieces of a launch in order over its waves as a plain copy would
-// take them.  The moves are worked out once per piece, lane l for the l-th block
+// Candidates in one pass, for long blocks: a wave copies one piece of a buffer (8
+// KiB, all its loads in flight before the first store), the pieces of a launch in
+// order over its waves as a plain copy would take them.  The moves are worked out once per piece, lane l for the l-th block
 // that overlaps it, and those that land in the piece (about one in 10,000
 // elements) are applied in the registers of the lane that holds the element.
 // What bounds it: memory.  The form below looks up the buffer and divides by
@@ -185,9 +184,13 @@ __device__ __forceinline__ void vec_set(uint32_t (&x)[4], uint32_t e, uint32_t w
 // against 0.36.
 constexpr uint32_t kPieceUnroll = 8, kPieceVecs = kPieceUnroll * kWave;
 constexpr uint32_t kPieceBytes = kPieceVecs * 16u;
-// From this many bytes per block a piece overlaps at most kPieceBytes / 256 + 2 = 34 blocks: one lane each.
-constexpr uint32_t kRunBlockBytes = 256;
-static_assert(kPieceBytes / kRunBlockBytes + 2 <= kWave, "a lane per block of a piece");
+// The moves of a piece are applied one after another, so their number decides: from 1 KiB per block on this form is
+// the faster one whatever the buffers (10,000 of 20 KB 2.56 ms against 2.76, 32 of 64 KiB 14.7 us and 17.2), from 512
+// bytes on where buffers are 1 MiB or more on average, mostly whole pieces (300 of 1 MiB 232 us and 253, one of 256
+// MiB 114 and 124; 10,000 of 20 KB 3.4 ms and 2.8).  At 256 bytes it takes 163 us for that one and 5.1 ms.
+constexpr uint32_t kRunBlockBytes = 1024, kRunBlockLeast = 512;
+constexpr uint64_t kRunBufBytes = 1u << 20;
+static_assert(kPieceBytes / kRunBlockLeast + 2 <= kWave, "a lane per block of a piece");
 constexpr uint64_t kMaxPieces = (1ull << 26) - 4;  // per launch: 2^32 threads less a workgroup (512 GiB)
 
 __global__ __launch_bounds__(kPerturbThreads) void k_materialize_runs(MatArgs a) {
@@ -380,8 +383,10 @@ int kc_materialize(kc_ctx* c, void* arena_d, uint64_t arena_elems, uint32_t dtyp
   MatArgs a{};
   if (!perturb_format(dtype, a.f)) return KC_EDTYPE;
   const uint64_t w = a.f.width;
+  uint64_t bytes = 0;
   for (uint32_t b = 0; b < n_bufs; ++b) {
     const kc_materialize_buf& m = bufs[b];
+    bytes += m.length * w;
     if (m.offset > arena_elems || m.length > arena_elems - m.offset) return KC_EINVAL;
     if (m.length > 0 && m.src_d == nullptr) return KC_EINVAL;
     if (((reinterpret_cast<uintptr_t>(m.src_d) | (reinterpret_cast<uintptr_t>(arena_d) + m.offset * w)) & 15u) != 0)
@@ -392,7 +397,7 @@ int kc_materialize(kc_ctx* c, void* arena_d, uint64_t arena_elems, uint32_t dtyp
   const hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   a.block = block;
   a.kmax = kmax;
-  const bool runs = block >= kRunBlockBytes / w;
+  const bool runs = block >= (bytes >= n_bufs * kRunBufBytes ? kRunBlockLeast : kRunBlockBytes) / w;
   for (uint32_t b0 = 0; b0 < n_bufs;) {
     a.n = 0;
     a.total = 0;
