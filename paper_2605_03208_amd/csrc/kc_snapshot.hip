@@ -42,7 +42,10 @@ __global__ void k_zero4(uint64_t* a, uint64_t na, uint64_t* b, uint64_t nb, uint
 // the first 16 bytes of each, one lane per unit, and lists the units that begin
 // with zeros; the listed units' 4 KiB blocks are then shared out to the waves,
 // four blocks (16 KiB in flight) at a time, until a non-zero byte shows in the
-// unit or it ends.  A unit's tile is found from the tile of its bitmap word's
+// unit or it ends: the first block of every unit, then the second of every unit,
+// and so on, so that units that only begin with zeros are left after their first
+// (8 GiB in units of 64 KiB that hold a byte in every page: 4.17 ms a snapshot with
+// a unit's blocks together, so 3.47).  A unit's tile is found from the tile of its bitmap word's
 // first unit: each lane holds one of the 64 tiles from there on, and every lane
 // searches them for its unit's.
 //
@@ -57,6 +60,7 @@ __global__ void k_zero4(uint64_t* a, uint64_t na, uint64_t* b, uint64_t nb, uint
 // It also clears the two arrays that a closure scan accumulates into.
 constexpr uint32_t kProbeWaves = 16;
 
+template <bool PAGES>  // units of one block
 __global__ __launch_bounds__(kProbeWaves * kWave) void k_probe_zero(ProbeParams p) {
   __shared__ uint64_t unit_va[kWave];
   __shared__ uint32_t unit_len[kWave], unit_at[kWave];  // of the listed units: bytes, place in the group
@@ -104,9 +108,14 @@ __global__ __launch_bounds__(kProbeWaves * kWave) void k_probe_zero(ProbeParams 
       const uint64_t seen = *(volatile unsigned long long*)&nonzero;  // blocks of units known not to be zero: skipped
       uint4 x[16];
       uint32_t place[4], bytes[4];
+      uint32_t nth = PAGES ? 0u : b0 / n_listed, which = b0 - nth * n_listed;  // block b0 is the nth of this listed unit
 #pragma unroll
       for (uint32_t i = 0; i < 4; ++i) {
-        const uint32_t b = b0 + i, c = min(b >> bshift, n_listed - 1u), off = (b & ((1u << bshift) - 1u)) * kPage;
+        const uint32_t b = b0 + i, c = min(which, n_listed - 1u), off = nth * kPage;
+        if (++which == n_listed && !PAGES) {
+          which = 0u;
+          ++nth;
+        }
         place[i] = unit_at[c];
         const bool skip = b >= n_blocks || ((seen >> place[i]) & 1ull) != 0ull || off >= unit_len[c];
         bytes[i] = skip ? 0u : min(unit_len[c] - off, kPage);
@@ -618,7 +627,8 @@ hipError_t launch_probe_zero(ProbeParams p, uint64_t n_words, uint32_t n_cu, hip
   uint32_t wpb = 1;
   while (wpb < kProbeWaves && (wpb < fill || (uint64_t)wpb << 18 < zeros)) wpb *= 2u;
   const uint32_t grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(p.n_groups, 1u << 21));
-  hipLaunchKernelGGL(k_probe_zero, dim3(grid), dim3(wpb * kWave), 0, s, p);
+  if (p.ushift == kMinUnitShift) hipLaunchKernelGGL(k_probe_zero<true>, dim3(grid), dim3(wpb * kWave), 0, s, p);
+  else hipLaunchKernelGGL(k_probe_zero<false>, dim3(grid), dim3(wpb * kWave), 0, s, p);
   return hipGetLastError();
 }
 
