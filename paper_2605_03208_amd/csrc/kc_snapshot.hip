@@ -260,18 +260,21 @@ __global__ __launch_bounds__(256) void k_scan_small(ScanSrc src, uint64_t* out, 
 }
 
 // --------------------------------------------------------------- gather ---
-// Kept units copied to their packed slots.  A wave takes 64 KiB of a tile (a
-// whole tile of pages, a part of one of larger units): one lane per 4 KiB block
+// Kept units copied to their packed slots.  A wave takes a part of a tile, 64 KiB
+// (a whole tile of pages) or, of many larger units, 256 KiB: one lane per 4 KiB block
 // resolves whether its unit is kept and where its slot is, then the kept blocks
 // are copied four at a time, 16 KiB in flight; a partial unit's slot is filled up
 // with zeros.  The bytes moved bound it.  One such part per wave, in address
 // order (2 GiB in 4096 ranges, 5 % of the pages kept, 43 us, eight persistent
 // waves per CU 54; 8 GiB, all kept, 3.29 ms and 3.40; before, with whole tiles,
-// 60 us and 3.38 ms, and 2 GiB in units of 2 MiB 1.68 ms, now 0.77).
-constexpr uint32_t kGatherShift = 16;
-constexpr uint64_t kGatherPart = 1ull << kGatherShift;
+// 60 us and 3.38 ms, and 2 GiB in units of 2 MiB 1.68 ms, now 0.77).  Beyond
+// kGatherLong of larger units, that is more workgroups than a call with little to
+// copy is worth: 40 GiB in units of 64 KiB, nothing kept, 151 us, so 47; 1 % kept
+// 234 and 170; all kept 15.5 and 15.8 ms.  Below, short parts spread few units better
+// (2 GiB in units of 2 MiB, 1 % kept, 23 us, long ones 36).
+constexpr uint64_t kGatherLong = 4ull << 30;
 
-__global__ __launch_bounds__(64) void k_gather(const Tile* tiles, uint32_t n_tiles, uint32_t part_shift,
+__global__ __launch_bounds__(64) void k_gather(const Tile* tiles, uint32_t n_tiles, uint32_t part, uint32_t part_shift,
                                                const uint64_t* zero_bm, const uint64_t* changed_bm,
                                                const uint64_t* word_prefix, uint8_t* packed, uint64_t* page_va,
                                                uint64_t cap, uint32_t ushift) {
@@ -279,12 +282,12 @@ __global__ __launch_bounds__(64) void k_gather(const Tile* tiles, uint32_t n_til
   const uint64_t n_items = (uint64_t)n_tiles << part_shift;
   for (uint64_t it = blockIdx.x; it < n_items; it += gridDim.x) {
     const Tile tile = const_load(tiles + (it >> part_shift));
-    // this lane's block, of the 16 of the part: its unit and place in it
-    const uint32_t off = (((uint32_t)it & ((1u << part_shift) - 1u)) << kGatherShift) + lane * kPage;
+    // this lane's block, of the part's 16 or 64: its unit and place in it
+    const uint32_t off = ((uint32_t)it & ((1u << part_shift) - 1u)) * part + lane * kPage;
     const uint32_t j = off >> ushift, inside = off & (unit - 1u);
     bool go = false;
     uint64_t dst = 0;
-    if (lane < 16u && j < tile.npages) {
+    if (lane * kPage < part && j < tile.npages) {
       const uint64_t g = (uint64_t)tile.g + j;
       uint64_t kw = ~zero_bm[g >> 6];
       if (changed_bm) kw &= changed_bm[g >> 6];
@@ -295,18 +298,18 @@ __global__ __launch_bounds__(64) void k_gather(const Tile* tiles, uint32_t n_til
     }
     const uint32_t bytes = j < tile.npages ? unit_bytes(tile, j, unit) : 0u;
     const uint32_t len = bytes > inside ? min(bytes - inside, kPage) : 0u;  // of the block
-    uint32_t mask = (uint32_t)__ballot(go);
+    uint64_t mask = __ballot(go);
     while (mask) {
       uint64_t from[4], to[4];
       uint32_t cnt = 0, n[4];
 #pragma unroll
       for (uint32_t i = 0; i < 4; ++i) {
-        const uint32_t b = mask ? (uint32_t)__builtin_ctz(mask) : 0u;
+        const uint32_t b = mask ? (uint32_t)__builtin_ctzll(mask) : 0u;
         from[i] = tile.va + __shfl(off, b, 64);
         to[i] = __shfl((unsigned long long)dst, b, 64);
         n[i] = __shfl(len, b, 64);
         if (mask) {
-          mask &= mask - 1u;
+          mask &= mask - 1ull;
           ++cnt;
         }
       }
@@ -655,11 +658,13 @@ hipError_t launch_gather(const Tile* tiles, uint32_t n_tiles, uint32_t per_tile,
                          const uint64_t* changed_bm, const uint64_t* word_prefix, uint8_t* packed,
                          uint64_t* page_va, uint64_t cap_pages, uint32_t ushift, uint32_t grid, hipStream_t s) {
   if (n_tiles == 0) return hipSuccess;
-  uint32_t part_shift = 0;
-  while ((kGatherPart << part_shift) < (uint64_t)per_tile << ushift) ++part_shift;
+  const uint64_t tile = (uint64_t)per_tile << ushift;
+  const uint32_t part = (ushift > kMinUnitShift && n_tiles * tile > kGatherLong ? kWave : 16u) * kPage;
+  uint32_t part_shift = 0;  // 1 << part_shift parts per tile
+  while (((uint64_t)part << part_shift) < tile) ++part_shift;
   const uint64_t n_items = (uint64_t)n_tiles << part_shift;
   const uint32_t blocks = (uint32_t)std::min<uint64_t>(grid == 0u ? n_items : std::min<uint64_t>(grid, n_items), 1u << 25);
-  hipLaunchKernelGGL(k_gather, dim3(blocks), dim3(64), 0, s, tiles, n_tiles, part_shift, zero_bm, changed_bm,
+  hipLaunchKernelGGL(k_gather, dim3(blocks), dim3(64), 0, s, tiles, n_tiles, part, part_shift, zero_bm, changed_bm,
                      word_prefix, packed, page_va, cap_pages, ushift);
   return hipGetLastError();
 }

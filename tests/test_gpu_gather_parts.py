@@ -66,3 +66,37 @@ def test_gather_parts(kc, unit, n_ranges, most):
             assert np.array_equal(s["packed"][:k * unit].cpu().numpy(), op)
     rs.close()
     ctx.close()
+
+
+@pytest.mark.parametrize("unit,n_ranges,most", [(16 * KiB, 16500, 2 * PAGE), (64 * KiB, 4200, 20 * PAGE), (2 * MiB, 270, 5 * PAGE)])
+def test_gather_long_parts(kc, unit, n_ranges, most):
+    """So many tiles of larger units that a wave takes 256 KiB of one: mostly
+    ranges under a unit, some of several."""
+    print(f"[gpu-case] gather: {n_ranges} ranges, units of {unit}, long parts", flush=True)
+    sys.stdout.flush()
+    rng = np.random.default_rng(unit + n_ranges)
+    sizes = rng.integers(1, most + 1, size=n_ranges)
+    long_ones = rng.choice(n_ranges, size=6, replace=False)
+    sizes[long_ones] = rng.integers(1, 4, size=6) * unit + rng.choice([0, 1, 4096, unit - 4095], size=6)
+    lay = W.make_layout(rng, sizes, gap_pages=(0, 2))
+    arena = W.Arena(lay, "cuda")
+    ranges = lay.ranges(arena.va_base)
+    host = rng.integers(1, 256, size=lay.arena_bytes, dtype=np.uint8)
+    views = W.host_views(lay, host)
+    arena.buf.copy_(torch.from_numpy(host))
+    ctx = kc.Context(0)
+    rs = kc.RangeSet(ctx, ranges, unit=unit)
+    zb = np.zeros(rs.n_words, dtype=np.uint64)
+    for share in (0.0, 0.02, 0.7, 1.0):
+        keep = rng.random(rs.n_pages) < share
+        zb[:] = np.packbits(~np.pad(keep, (0, rs.n_words * 64 - rs.n_pages)), bitorder="little").view(np.uint64)
+        zb[-1] &= np.uint64((1 << (rs.n_pages - 64 * (rs.n_words - 1))) - 1)
+        for grid in (0, 1):
+            ctx.set_tuning(kc.OP_COMPACT, grid_per_cu=grid)
+            packed, va, nk = kc.compact(ctx, rs, torch.from_numpy(zb.view(np.int64)).cuda(), cap_pages=max(1, int(keep.sum())))
+            op, ova, onk = oracle.compact(ranges, views, zb, cap_pages=max(1, int(keep.sum())), unit=unit)
+            assert int(u64(nk)[0]) == onk == int(keep.sum())
+            assert np.array_equal(u64(va)[:onk], ova[:onk])
+            assert np.array_equal(packed[:onk * unit].cpu().numpy(), op[:onk * unit])
+    rs.close()
+    ctx.close()
