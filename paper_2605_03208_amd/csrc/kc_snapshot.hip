@@ -444,19 +444,21 @@ __global__ __launch_bounds__(kWideWaves * kWave) __attribute__((amdgpu_waves_per
 
 // Writes the out-of-range words of each tile at its prefix position, in
 // ascending address order, up to the list capacity.  A block owns a run of
-// consecutive tiles, a slice of up to 1024 at a time: one parallel read of
-// their counts lists the tiles with entries below the capacity, then each
-// listed tile is read again with one wave per page (its four 1-KiB segments in
+// up to 1024 consecutive tiles, one per thread: one parallel read of their counts
+// lists the tiles with entries below the capacity, then each listed tile is read
+// again with one wave per page (its four 1-KiB segments in
 // one round trip, under way while the tile before it is searched), the waves'
 // entries placed by a prefix over their counts.  Without a prefix per tile, a
 // block with entries sums the counts before its run itself (up to kInlineTiles
-// tiles: half a MiB from the caches at most).  A chain of round trips bounds it,
+// tiles: 768 KiB from the caches at most).  A chain of round trips bounds it,
 // so what can be is loaded ahead, a block without entries ends after the first,
 // and the range table is the wide one, all of it in LDS up to 4096 ranges.
 // 2 GiB in 4096 ranges with 134 entries: 16.2 us, 21.4 before with three
 // launches of 4.8 us for the prefix.
 constexpr uint32_t kEmitThreads = kTilePages * kWave;  // one wave per page of a tile
-constexpr uint32_t kEmitMaxBlocks = 256;
+// As many blocks while there are tiles (one per CU: few tiles each, listed tiles are revisited in parallel), or twice,
+// three times as many, so that a block has no more tiles than threads.
+constexpr uint32_t kEmitBlocks = 256;
 
 __global__ __launch_bounds__(kEmitThreads) void k_oob_emit(const Tile* tiles, uint32_t n_tiles, uint32_t run,
                                                            ScanDev sd, const uint64_t* tile_prefix, kc_oob* oob,
@@ -497,104 +499,88 @@ __global__ __launch_bounds__(kEmitThreads) void k_oob_emit(const Tile* tiles, ui
     res->truncated = total > cap ? 1u : 0u;
   }
   if (total == 0 || cap == 0) return;  // nothing to list: no tile to revisit
-  if (end - first <= kEmitThreads && !__syncthreads_or(count != 0u)) return;  // none in this run
+  if (!__syncthreads_or(count != 0u)) return;  // none in this run
   const uint64_t below = (1ull << lane) - 1ull;
   load_wide_fences(sd.rt, tid, kEmitThreads);  // the first barrier below makes it whole
-  uint64_t before = 0;  // entries before the slice
-  if (!tile_prefix) {
+  if (tid == 0) n_listed = 0u;
+  uint64_t at = 0;  // entries before this thread's tile
+  if (tile_prefix) {
+    at = first + tid < end ? tile_prefix[first + tid] : 0ull;
+    __syncthreads();
+  } else {  // those before the run, and those before this tile in it
     for (uint64_t i = tid + kEmitThreads; i < first / 4u; i += kEmitThreads) {
       const uint4 x = counts[i];
       n += x.x + x.y + x.z + x.w;
     }
     const unsigned long long w = wave_sum_u64(n);
-    if (lane == 0) sums[1][wv] = w;
-    __syncthreads();
+    uint32_t inc = count;
 #pragma unroll
-    for (uint32_t i = 0; i < kTilePages; ++i) before += sums[1][i];
-    if (before >= cap) return;
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint32_t y = __shfl_up(inc, d, 64);
+      if (lane >= (uint32_t)d) inc += y;
+    }
+    if (lane == kWave - 1u) {
+      sums[0][wv] = inc;
+      sums[1][wv] = w;
+    }
+    __syncthreads();
+    at = inc - count;
+#pragma unroll
+    for (uint32_t i = 0; i < kTilePages; ++i) at += sums[1][i] + (i < wv ? sums[0][i] : 0ull);
   }
-  for (uint64_t t0 = first; t0 < end; t0 += kEmitThreads) {
-    if (tid == 0) n_listed = 0u;
-    const uint64_t t = t0 + tid;
-    if (t0 != first) {
-      count = t < end ? sd.tile_oob[t] : 0u;
-      if (count) tile = ld16((uint64_t)(tiles + t));
+  if (count != 0u && at < cap) {
+    const uint32_t i = atomicAdd(&n_listed, 1u);
+    listed[i] = tile;
+    listed_at[i] = at;
+  }
+  __syncthreads();
+  const uint32_t n_list = n_listed;  // the same in every thread
+  uint4 next[4];
+  auto load = [&](uint32_t i) {
+    const Tile it = i < n_list ? __builtin_bit_cast(Tile, listed[i]) : Tile{0, 0, 0, 0};
+    const bool mine = wv < it.npages;
+#pragma unroll
+    for (uint32_t j = 0; j < 4; ++j)
+      next[j] = mine ? ld16(it.va + (uint64_t)(wv * 4u + j) * 1024u + lane * 16u) : make_uint4(0, 0, 0, 0);
+  };
+  load(0);
+  for (uint32_t i = 0; i < n_list; ++i) {
+    const Tile it = __builtin_bit_cast(Tile, listed[i]);
+    uint4 x[4];
+    uint64_t b0[4], b1[4];
+    uint32_t cnt = 0;
+#pragma unroll
+    for (uint32_t j = 0; j < 4; ++j)  // zero words (and pages past the tile) are never pointer-like
+      x[j] = seg_words(it, wv * 4u + j, lane, next[j]);  // same words as the counting pass
+    load(i + 1u);
+#pragma unroll
+    for (uint32_t j = 0; j < 4; ++j) {
+      const uint64_t w0 = ((uint64_t)x[j].y << 32) | x[j].x;
+      const uint64_t w1 = ((uint64_t)x[j].w << 32) | x[j].z;
+      b0[j] = __ballot((w0 - sd.lo) < sd.span && wide_range_index(w0, sd.rt) < 0);
+      b1[j] = __ballot((w1 - sd.lo) < sd.span && wide_range_index(w1, sd.rt) < 0);
+      cnt += (uint32_t)(__popcll(b0[j]) + __popcll(b1[j]));
     }
-    uint64_t at = 0;
-    if (tile_prefix) {
-      at = t < end ? tile_prefix[t] : 0ull;
-      __syncthreads();
-    } else {  // the counts before this thread's in the slice
-      uint32_t inc = count;
+    if (lane == 0) wave_cnt[i & 1u][wv] = cnt;
+    __syncthreads();  // the one barrier per tile: the counts of two tiles apart share a row
+    uint64_t done = listed_at[i];
+    for (uint32_t w = 0; w < wv; ++w) done += wave_cnt[i & 1u][w];
 #pragma unroll
-      for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t y = __shfl_up(inc, d, 64);
-        if (lane >= (uint32_t)d) inc += y;
+    for (uint32_t j = 0; j < 4; ++j) {  // segments in order, lanes in order, word 0 before word 1
+      const uint64_t a = it.va + (uint64_t)(wv * 4u + j) * 1024u + lane * 16u;
+      const bool o0 = ((b0[j] >> lane) & 1ull) != 0ull, o1 = ((b1[j] >> lane) & 1ull) != 0ull;
+      const uint64_t r0 = done + (uint64_t)__popcll(b0[j] & below) + (uint64_t)__popcll(b1[j] & below);
+      const uint64_t r1 = r0 + (o0 ? 1u : 0u);
+      if (o0 && r0 < cap) {
+        oob[r0].word_va = a;
+        oob[r0].value = ((uint64_t)x[j].y << 32) | x[j].x;
       }
-      if (lane == kWave - 1u) sums[0][wv] = inc;
-      __syncthreads();
-      at = before + inc - count;
-#pragma unroll
-      for (uint32_t w = 0; w < kTilePages; ++w) {
-        if (w < wv) at += sums[0][w];
-        before += sums[0][w];
+      if (o1 && r1 < cap) {
+        oob[r1].word_va = a + 8u;
+        oob[r1].value = ((uint64_t)x[j].w << 32) | x[j].z;
       }
+      done += (uint64_t)__popcll(b0[j]) + (uint64_t)__popcll(b1[j]);
     }
-    if (count != 0u && at < cap) {
-      const uint32_t i = atomicAdd(&n_listed, 1u);
-      listed[i] = tile;
-      listed_at[i] = at;
-    }
-    __syncthreads();
-    const uint32_t n_list = n_listed;  // the same in every thread
-    uint4 next[4];
-    auto load = [&](uint32_t i) {
-      const Tile it = i < n_list ? __builtin_bit_cast(Tile, listed[i]) : Tile{0, 0, 0, 0};
-      const bool mine = wv < it.npages;
-#pragma unroll
-      for (uint32_t j = 0; j < 4; ++j)
-        next[j] = mine ? ld16(it.va + (uint64_t)(wv * 4u + j) * 1024u + lane * 16u) : make_uint4(0, 0, 0, 0);
-    };
-    load(0);
-    for (uint32_t i = 0; i < n_list; ++i) {
-      const Tile it = __builtin_bit_cast(Tile, listed[i]);
-      uint4 x[4];
-      uint64_t b0[4], b1[4];
-      uint32_t cnt = 0;
-#pragma unroll
-      for (uint32_t j = 0; j < 4; ++j)  // zero words (and pages past the tile) are never pointer-like
-        x[j] = seg_words(it, wv * 4u + j, lane, next[j]);  // same words as the counting pass
-      load(i + 1u);
-#pragma unroll
-      for (uint32_t j = 0; j < 4; ++j) {
-        const uint64_t w0 = ((uint64_t)x[j].y << 32) | x[j].x;
-        const uint64_t w1 = ((uint64_t)x[j].w << 32) | x[j].z;
-        b0[j] = __ballot((w0 - sd.lo) < sd.span && wide_range_index(w0, sd.rt) < 0);
-        b1[j] = __ballot((w1 - sd.lo) < sd.span && wide_range_index(w1, sd.rt) < 0);
-        cnt += (uint32_t)(__popcll(b0[j]) + __popcll(b1[j]));
-      }
-      if (lane == 0) wave_cnt[i & 1u][wv] = cnt;
-      __syncthreads();  // the one barrier per tile: the counts of two tiles apart share a row
-      uint64_t done = listed_at[i];
-      for (uint32_t w = 0; w < wv; ++w) done += wave_cnt[i & 1u][w];
-#pragma unroll
-      for (uint32_t j = 0; j < 4; ++j) {  // segments in order, lanes in order, word 0 before word 1
-        const uint64_t a = it.va + (uint64_t)(wv * 4u + j) * 1024u + lane * 16u;
-        const bool o0 = ((b0[j] >> lane) & 1ull) != 0ull, o1 = ((b1[j] >> lane) & 1ull) != 0ull;
-        const uint64_t r0 = done + (uint64_t)__popcll(b0[j] & below) + (uint64_t)__popcll(b1[j] & below);
-        const uint64_t r1 = r0 + (o0 ? 1u : 0u);
-        if (o0 && r0 < cap) {
-          oob[r0].word_va = a;
-          oob[r0].value = ((uint64_t)x[j].y << 32) | x[j].x;
-        }
-        if (o1 && r1 < cap) {
-          oob[r1].word_va = a + 8u;
-          oob[r1].value = ((uint64_t)x[j].w << 32) | x[j].z;
-        }
-        done += (uint64_t)__popcll(b0[j]) + (uint64_t)__popcll(b1[j]);
-      }
-    }
-    __syncthreads();  // every thread is done with the list before it is written again
   }
 }
 
@@ -715,8 +701,9 @@ hipError_t launch_closure(const Tile* tiles, uint32_t n_tiles, uint32_t tile0, c
 
 hipError_t launch_oob_emit(const Tile* tiles, uint32_t n_tiles, const ScanDev& sd, const uint64_t* tile_prefix,
                            kc_oob* oob, uint64_t cap, kc_scan_result* res, uint64_t n_words, hipStream_t s) {
-  // a block per CU at most: few tiles per block on small sets, so that listed tiles are revisited in parallel
-  const uint32_t run = std::max(1u, blocks_for(n_tiles, kEmitMaxBlocks));
+  static_assert(kInlineTiles <= kEmitBlocks * kEmitThreads, "a tile per thread");
+  const uint32_t rounds = std::max(1u, blocks_for(n_tiles, kEmitBlocks * kEmitThreads));
+  const uint32_t run = std::max(1u, blocks_for(n_tiles, kEmitBlocks * rounds));
   const uint32_t blocks = std::max(1u, blocks_for(n_tiles, run));
   hipLaunchKernelGGL(k_oob_emit, dim3(blocks), dim3(kEmitThreads), wide_lds_bytes(sd.rt), s, tiles, n_tiles, run, sd, tile_prefix, oob,
                      cap, res, n_words);
