@@ -259,7 +259,7 @@ int kc_ctx_enable_timing(kc_ctx *ctx, int on);
 int kc_ctx_kernel_ms(kc_ctx *ctx, uint32_t op, float *ms);
 
 /* Upload a validated range list (the tracked-allocation map) and allocate
- * the scratch its calls need (about 40 bytes per page).  Synchronous.
+ * the scratch its calls need (about 2 bytes per page; ranges of one page 44).  Synchronous.
  * Errors: KC_EINVAL / KC_EALIGN / KC_EORDER as kc_range_check, KC_ELIMIT,
  * KC_ENOMEM, KC_EHIP.  *n_pages (if non-NULL) receives the page count. */
 int kc_rangeset_create(kc_ctx *ctx, const kc_range *ranges, uint32_t n,
@@ -278,9 +278,8 @@ int kc_rangeset_create(kc_ctx *ctx, const kc_range *ranges, uint32_t n,
  * `unit` bytes apart, a restore accepts a page-VA entry only if it is the
  * start of a unit of some range, snapshot files record the unit and load
  * only into a set of the same unit.  The closure scan and the pointer graph
- * are unchanged (they read every word); with a unit above 4096 a scan asked
- * of kc_page_hash / kc_snapshot runs as its own pass over the ranges after
- * the hashing pass (same results).  *n_units (if non-NULL) receives the unit
+ * are unchanged (they read every word), also where the scan rides on
+ * kc_page_hash / kc_snapshot.  *n_units (if non-NULL) receives the unit
  * count.  kc_rangeset_create is this call with unit = 4096. */
 int kc_rangeset_create_unit(kc_ctx *ctx, const kc_range *ranges, uint32_t n,
                             uint64_t unit, kc_rangeset **out, uint64_t *n_units);

@@ -19,10 +19,11 @@
 // per LDS bank, so that lanes with the same distance do not queue on one bin.
 //
 // Measured (16 pairs of f16, bf16, f32 and fp8, 768 MiB a side, 11.3 % of the
-// elements off): 0.39 ms a call, 1.95 ms when every element of a run that
+// elements off): 0.38 ms a call, 1.95 ms when every element of a run that
 // differed took the exact path with its division; 10,000 uneven pairs of 8 GiB
-// a side with 1e-4 off: 2.53 ms (6.8 TB/s) against 3.16 (2.58 when the loads of
-// the next round were issued together, after the last run was looked at).
+// a side with 1e-4 off: 2.50 ms (6.9 TB/s) against 3.16.  The loads of the next
+// round are issued run by run, as each run has been looked at: issued together
+// after the last, those 10,000 pairs took 2 % longer.
 //
 // A workgroup's totals of a pair go to per-pair accumulators with integer
 // atomics (max of non-negative doubles via their bit patterns, first mismatch
@@ -527,12 +528,6 @@ __device__ __forceinline__ void tile_body(const CmpPairDev& pr, uint64_t b0, uin
 }
 
 
-__device__ __forceinline__ uint32_t wave_reduce_sum(uint32_t x) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) x += __shfl_xor(x, d, 64);
-  return x;
-}
-
 // A value for what is done where a pair ends, as the thread's index: lanes,
 // addresses and constants made from it there are not kept from the kernel's start
 // on, in registers that the rounds need (seven to thirteen of them were spilled).
@@ -641,8 +636,8 @@ __device__ __forceinline__ void end_pair(const CmpPairDev& pr, const Partial& p,
     if (DIRECT && tid < kWave) write_report(pr.n_elems, pr.dtype, 0ull, res);
     return;
   }
-  const uint32_t v0 = wave_reduce_sum(p.mis_elems), v1 = wave_reduce_sum(p.mis_bytes);
-  const uint32_t v2 = wave_reduce_sum(p.over), v3 = wave_reduce_sum(p.not_close);
+  const uint32_t v0 = wave_sum_u32(p.mis_elems), v1 = wave_sum_u32(p.mis_bytes);
+  const uint32_t v2 = wave_sum_u32(p.over), v3 = wave_sum_u32(p.not_close);
   if (lane == 0) {
     atomicAdd(&lds.cnt[kCntMis], v0);
     atomicAdd(&lds.cnt[kCntBytes], v1);

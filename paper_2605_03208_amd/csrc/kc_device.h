@@ -142,8 +142,6 @@ __device__ __forceinline__ int32_t range_index(uint64_t w, const FenceLds& f, co
   return search_fences(w, f.base, f.end, f.bucket, rt.stride, rt.n_fence, rt);
 }
 
-// True iff w lies in [base_r, end_r) for some range r.
-
 // ------------------------------------------------------------ wide table --
 // Kernels whose workgroups hold several independent waves share one copy of
 // up to kWideFences fences in dynamic LDS: n_fence_w bases, n_fence_w ends,

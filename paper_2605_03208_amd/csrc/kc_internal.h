@@ -13,9 +13,9 @@ namespace kc {
 
 constexpr uint32_t kPage = 4096;
 constexpr uint32_t kWave = 64;
-constexpr uint32_t kTilePages = 16;     // pages per wave tile (one lane quad per page)
-constexpr uint32_t kFences = 256;       // range-table entries held in LDS by one-wave workgroups
-constexpr uint32_t kWideFences = 4096;  // the same, shared by the waves of a multi-wave workgroup
+constexpr uint32_t kTilePages = 16;     // most pages, or units, of a tile
+constexpr uint32_t kFences = 256;       // range-table entries in LDS: hashing pass, region diff
+constexpr uint32_t kWideFences = 4096;  // the same: closure scan, pointer graph, list of out-of-range words
 constexpr uint32_t kBuckets = 1024;     // entries of the LDS bucket index over the ranges
 
 // 16-byte global accesses.  Data that streams through once (pages, packed
@@ -66,10 +66,6 @@ struct Tile {
 };
 static_assert(sizeof(Tile) == 16, "tile layout");
 
-// Bytes of page j of a 4 KiB page tile.
-__device__ __forceinline__ uint32_t page_bytes(const Tile& t, uint32_t j) {
-  return j + 1u == t.npages ? (uint32_t)t.last_len : kPage;
-}
 // Bytes of unit j of a tile of units of `unit` bytes.
 __device__ __forceinline__ uint32_t unit_bytes(const Tile& t, uint32_t j, uint32_t unit) {
   return j + 1u == t.npages ? (uint32_t)t.last_len : unit;
@@ -282,7 +278,7 @@ enum : uint32_t {
   kAccMaxAbs, kAccMaxRel, kAccFirstInv, kAccNotClose, kAccHist = 16  // 48 bins: words 16..63
 };
 
-// ---- launchers (kc_kernels.hip) ------------------------------------------
+// ---- launchers (in the files of their kernels) ---------------------------
 hipError_t launch_fill_u64(uint64_t* p, uint64_t n, uint64_t v, hipStream_t s);
 hipError_t launch_zero4(uint64_t* a, uint64_t na, uint64_t* b, uint64_t nb, uint64_t* c, uint64_t nc, uint64_t* d,
                         uint64_t nd, hipStream_t s);

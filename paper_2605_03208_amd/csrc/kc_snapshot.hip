@@ -1,9 +1,11 @@
 // kc_snapshot.hip -- gfx950 kernels of the snapshot around the hashing pass
 // (kc_hash.hip), of the restore and of the closure scan.
 //
-// Memory-bound streaming kernels: persistent grids of 64-lane waves striding
-// over a tile list (16 pages of one range per tile).  Most workgroups are one
-// wave; the standalone scan puts several independent waves in a workgroup to
+// Memory-bound streaming kernels over a tile list (up to 16 pages or units of one
+// range per tile).  The standalone scan and the restore's zero fill are persistent
+// grids of waves that stride over the tiles; the probe, the gather and the
+// restore's scatter take one group, part or block per workgroup or wave, in address
+// order.  The standalone scan puts several independent waves in a workgroup to
 // share one range table, and the out-of-range emission uses one wave per page
 // of a tile.  Global traffic is 16-byte loads / stores that cover whole 1-KiB
 // runs.

@@ -1,6 +1,5 @@
 // kc_xxh64.h -- device-side XXH64 with one lane quad per hash unit, and the
-// bitmap helpers shared by the hashing passes (the 4 KiB pass and the
-// pipelined pass of larger units).
+// bitmap helper of the hashing pass.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -99,14 +98,6 @@ __device__ __forceinline__ void or_page_bits(uint64_t* bm, uint32_t g0, uint32_t
   if ((b << s) != 0ull) atomicOr(reinterpret_cast<unsigned long long*>(bm + w), (unsigned long long)(b << s));
   if (s + np > 64u && (b >> (64u - s)) != 0ull)
     atomicOr(reinterpret_cast<unsigned long long*>(bm + w + 1), (unsigned long long)(b >> (64u - s)));
-}
-
-// Compress ballot bits at lanes 4q (q < 16) into bit q.
-__device__ __forceinline__ uint32_t quad_bits(uint64_t ballot) {
-  uint32_t out = 0;
-#pragma unroll
-  for (uint32_t q = 0; q < 16; ++q) out |= (uint32_t)((ballot >> (4u * q)) & 1ull) << q;
-  return out;
 }
 
 }  // namespace kc
