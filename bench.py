@@ -49,10 +49,10 @@ PAGE = 4096
 # device copy gives (fetch x2.0, write x1.0).  Valid only for the kernel
 # sources they were taken from.
 PMC_TRAFFIC = {
-    "source_sha256": "917568fabc86ba8fa148f9621927b3ad81b17f149c4f11d0cf59a8c42db25695",
-    "snapshot": 62934620777,  # fetch 31401060297 + write 31533560480
-    "restore": 63687210009,   # fetch 32333206195 + write 31354003814
-    "compare": 64428289434,   # fetch 64428289434 + write 0
+    "source_sha256": "a28f7370783f7f8730eeaafc6101eda6b46dbcf48c1aaa44dd8aefa50dc12253",
+    "snapshot": 62930404242,   # fetch 31401073737 + write 31529330505
+    "restore": 63687250201,   # fetch 32333206195 + write 31354044006
+    "compare": 64441212518,   # fetch 64441212518 + write 0
 }
 
 
