@@ -464,8 +464,9 @@ static int run_closure(kc_rangeset* rs, const ScanDev& sd, hipStream_t s) {
 //     14.0 / 12.3 / 11.8: 16 from 1024 tiles on;
 //   64 KiB units: 30 GiB 10.9 / 11.9 / 11.6 ms, 1 GiB 483 / 455 / 465 us, 64 MiB 131 / 109 / 98;
 //   2 MiB units: 30 GiB 14.9 / 11.3 / 12.7 ms, 8 GiB 4.5 / 3.9 / 5.3, 4 GiB 4.0 / 3.6 / 2.9.
-// (Before, with 16 or 8 units per wave, 512-byte chunks and for larger units skewed rows: 11.4 ms for the 30 GiB of
-// pages, 13.3 and 13.0 ms for 64 KiB and 2 MiB units.)
+// Each row is of one process; the same code on the 30 GiB moves between processes, with where the buffers lie (64 KiB
+// units 10.9 to 11.7 ms, 2 MiB 11.3 to 12.6).  Side by side in one process the former pass (512-byte chunks, for larger
+// units skewed rows) and this one, 40 GiB, whole snapshot: 64 KiB units 17.5 and 15.0 ms, 2 MiB 20.3 and 16.7.
 static uint32_t hash_rows(const kc_rangeset* rs, bool gather) {
   const uint32_t n_cu = rs->ctx->n_cu;
   if (rs->ushift > kMinUnitShift) {
