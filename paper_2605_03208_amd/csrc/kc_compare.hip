@@ -241,6 +241,17 @@ __device__ __forceinline__ void count_nans(TileLds& lds, uint32_t which, uint32_
   if (n != 0u) atomicAdd(&lds.hist[(kNanBins + which) * kHistCopies + threadIdx.x % kHistCopies], n);
 }
 
+// One element that is a NaN on some side; true if the two differ.
+template <uint32_t DT>
+__device__ __forceinline__ bool nan_element(typename Fmt<DT>::B c, typename Fmt<DT>::B g, Partial& p, TileLds& lds) {
+  const bool nc = Fmt<DT>::nan(c), ng = Fmt<DT>::nan(g);
+  count_nans(lds, nc && ng ? 0u : nc ? 1u : 2u, 1u);
+  if (c == g) return false;
+  ++p.mis_elems;
+  p.mis_bytes += byte_count<typename Fmt<DT>::B, Fmt<DT>::size>(c ^ g);
+  return true;
+}
+
 // Exact path of one element that differs, neither side a NaN.  Straight-line
 // but for new maxima of the relative error.
 template <uint32_t DT>
@@ -355,6 +366,19 @@ template <uint32_t ES> __device__ __forceinline__ void add_marks(uint32_t (&m)[2
   else m[j >> 3] |= tops >> (j & 7u);
 }
 
+// Marks of one lane that may be NaNs from which its wave counts a round's NaNs
+// together (round_nans); with fewer each lane takes its own one by one.  Together
+// costs the same however many there are, about 14 of them one by one.  256 MiB with
+// 11.3 % off, one by one / together: as bf16 with 0.1, 1 and 10 % NaNs 118 / 158, 123 /
+// 163 and 145 / 160 us, as fp8 with 0.1 and 3 % 157 / 198 and 180 / 196; half of each
+// 256 bytes NaN, as fp8, 310 / 102.  Binary64 has 8 elements a lane: always one by one.
+constexpr uint32_t kManyNans = 12;
+
+// From marks of the first words of runs: of all their words.
+template <uint32_t ES> __device__ __forceinline__ uint32_t any_word(uint32_t m) {
+  return ES == 8 ? m * 3u : ES == 4 ? m * 15u : (m >> 3) * 15u;
+}
+
 // The NaNs of a round, from its staged runs (bit u of `runs`: run u is staged;
 // v: this lane's first run, of nvec): counted by class, and where the two sides
 // differ the element, its bytes and the lowest of them; taken out of the marks m.
@@ -364,6 +388,7 @@ template <uint32_t DT, uint32_t T>
 __device__ __forceinline__ void round_nans(const uint4* cs, const uint4* gs, uint32_t runs, uint32_t v, uint32_t nvec,
                                            uint32_t (&m)[2], uint32_t& low, Partial& p, TileLds& lds) {
   constexpr uint32_t es = Fmt<DT>::size;
+  static_assert(es < 8u, "one word holds whole elements");
   uint32_t both = 0u, cand = 0u, gold = 0u, nans[2] = {0u, 0u};
 #pragma unroll
   for (uint32_t u = 0; u < kUnroll; ++u) {
@@ -373,7 +398,6 @@ __device__ __forceinline__ void round_nans(const uint4* cs, const uint4* gs, uin
     const uint32_t in = v + u * T < nvec ? ~0u : 0u;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      if (es == 8u && !(i & 1)) continue;  // with the odd word
       const uint32_t nc = nan_tops<DT>(cw, i) & in, ng = nan_tops<DT>(gw, i) & in, n = nc | ng;
       both += (uint32_t)__popc(nc & ng);
       cand += (uint32_t)__popc(nc & ~ng);
@@ -381,10 +405,9 @@ __device__ __forceinline__ void round_nans(const uint4* cs, const uint4* gs, uin
       add_marks<es>(nans, 4u * u + (uint32_t)i, n);
       // all bits of their lanes
       const uint32_t lanes = es == 1u ? (n >> 7) * 0xFFu : es == 2u ? (n >> 15) * 0xFFFFu : 0u - (n >> 31);
-      const uint32_t x = (cw[i] ^ gw[i]) & lanes, y = es == 8u ? (cw[i & 2] ^ gw[i & 2]) & lanes : 0u;
-      const uint32_t d = nonzero_tops<es>(x | y);
+      const uint32_t x = (cw[i] ^ gw[i]) & lanes, d = nonzero_tops<es>(x);
       p.mis_elems += (uint32_t)__popc(d);
-      p.mis_bytes += (uint32_t)(es == 1u ? __popc(d) : __popc(nonzero_tops<1>(x)) + __popc(nonzero_tops<1>(y)));
+      p.mis_bytes += (uint32_t)(es == 1u ? __popc(d) : __popc(nonzero_tops<1>(x)));
       if (d != 0u)
         low = min(low, (u * T + threadIdx.x) * (16u / es) + ((uint32_t)i * 4u + ((uint32_t)__builtin_ctz(d) >> 3)) / es);
     }
@@ -426,7 +449,8 @@ __device__ __forceinline__ void tile_body(const CmpPairDev& pr, uint64_t b0, uin
   for (uint32_t v0 = 0; v0 < nvec; v0 += per_round) {
     // Marked elements: those that differ or are NaN (add_marks).
     uint32_t m[2] = {0u, 0u};
-    uint32_t runs = 0u, nan = 0u;  // of the wave: runs that hold one, as bits; of the lane: a NaN in some side
+    uint32_t runs = 0u;          // of the wave: runs that hold one, as bits
+    uint32_t nan[2] = {0u, 0u};  // NaNs in any word of a run, marked as if in its first
 #pragma unroll
     for (uint32_t u = 0; u < kUnroll; ++u) {
       const uint32_t cw[4] = {c[u].x, c[u].y, c[u].z, c[u].w}, gw[4] = {g[u].x, g[u].y, g[u].z, g[u].w};
@@ -436,14 +460,16 @@ __device__ __forceinline__ void tile_body(const CmpPairDev& pr, uint64_t b0, uin
       if (__ballot(any != 0u) != 0ull) {  // some lane's run holds one
         runs |= 1u << u;
         const uint32_t in = v0 + u * T + tid < nvec ? ~0u : 0u;
+        uint32_t run_nan = 0u;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           if (es == 8u && !(i & 1)) continue;  // with the odd word
           const uint32_t x = es == 8u ? (cw[i] ^ gw[i]) | (cw[i & 2] ^ gw[i & 2]) : cw[i] ^ gw[i];
           const uint32_t ng = nan_tops<DT>(gw, i);
           add_marks<es>(m, 4u * u + (uint32_t)i, (nonzero_tops<es>(x) | ng) & in);
-          nan |= nan_tops<DT>(cw, i) | ng;
+          run_nan |= nan_tops<DT>(cw, i) | ng;
         }
+        add_marks<es>(nan, 4u * u, run_nan);
         cs[u * T] = c[u];
         gs[u * T] = g[u];
       }
@@ -453,7 +479,16 @@ __device__ __forceinline__ void tile_body(const CmpPairDev& pr, uint64_t b0, uin
     if (runs == 0u) continue;
     p.any = p.any || (m[0] | m[1]) != 0u;
     uint32_t low = ~0u;  // lowest differing element of this lane, from the round's first
-    if (F::kind == 0 && __ballot(nan != 0u) != 0ull) round_nans<DT, T>(cs, gs, runs, v0 + tid, nvec, m, low, p, lds);
+    if constexpr (F::kind == 0) {  // nan: the marks that may be NaNs
+      nan[0] = any_word<es>(nan[0]) & m[0];
+      nan[1] = es == 1u ? any_word<es>(nan[1]) & m[1] : 0u;
+      if constexpr (epv * kUnroll >= kManyNans) {
+        if (__ballot((uint32_t)(__popc(nan[0]) + __popc(nan[1])) >= kManyNans) != 0ull) {
+          round_nans<DT, T>(cs, gs, runs, v0 + tid, nvec, m, low, p, lds);
+          nan[0] = nan[1] = 0u;
+        }
+      }
+    }
     using M = typename Mask<es>::T;
     M mask = es == 1 ? (M)(((uint64_t)m[1] << 32) | m[0]) : (M)m[0];
     p.max_abs = fmax_pos(p.max_abs, lds.max_abs);
@@ -496,6 +531,16 @@ __device__ __forceinline__ void tile_body(const CmpPairDev& pr, uint64_t b0, uin
         low = ((j >> 2) * T + tid) * epv + (j & 3u) * 4u + k;
       }
     } else {
+      if (F::kind == 0) {  // few NaNs: one by one, taken out of the marks
+        for (M left = es == 1 ? (M)(((uint64_t)nan[1] << 32) | nan[0]) : (M)nan[0]; left != 0; left &= left - 1) {
+          uint32_t at;
+          const uint32_t o = place(left, at);
+          const B cv = get(cs, o), gv = get(gs, o);
+          if (!F::nan(cv) && !F::nan(gv)) continue;
+          if (nan_element<DT>(cv, gv, p, lds)) low = min(low, at);
+          mask &= ~(left & (~left + 1));
+        }
+      }
       for (; mask != 0; mask &= mask - 1) {
         uint32_t at;
         const uint32_t o = place(mask, at);

@@ -92,6 +92,42 @@ def test_nan_filled(kc, dt):
     check(kc, host, dt, "NaN all over, in half of the elements, in a stretch")
 
 
+@pytest.mark.parametrize("dt", FLOATS)
+def test_few_nans(kc, dt):
+    """NaNs as a thread of the pass meets them: k of its 16-byte runs' elements
+    (four runs, 256 * 16 bytes apart) for k around the number from which a wave
+    counts them together, in few or all threads, among elements that differ; then
+    scattered ones."""
+    rng = np.random.default_rng(100 + dt)
+    w = W.ELEM_SIZE[dt]
+    per = 16 // w
+    one, two = (np.frombuffer(c, dtype=np.uint8) for c in nan_codes(dt))
+    n = 2 * 16384 // w + 5 * per + 3  # two rounds of a workgroup, some runs and a tail
+    host = []
+
+    def add(at, first, second, off):
+        gold = torch.from_numpy(rng.standard_normal(n)).to(W.TORCH_DTYPE[dt]).view(torch.uint8).numpy().copy().reshape(n, w)
+        cand = gold.copy()
+        cand[rng.random(n) < off, 0] ^= 1
+        for side, code in ((cand, first), (gold, second)):
+            if code is not None:
+                side[at] = code
+        host.append((cand.reshape(-1), gold.reshape(-1)))
+
+    for k in sorted({1, 2, min(11, 4 * per), min(12, 4 * per), min(13, 4 * per), 4 * per}):
+        for threads in ([5], [0, 63, 64, 200, 255], range(256)):
+            of_thread = [rng.permutation(4 * per)[:k] for _ in threads]
+            at = np.concatenate([(t + 256 * (e // per)) * per + e % per for t, e in zip(threads, of_thread)])
+            add(at, one, None, 0.1)
+            add(at, one, one, 0.0)
+            add(at, two, one, 0.5)
+    for p in (1e-3, 0.01, 0.1):
+        at = np.flatnonzero(rng.random(n) < p)
+        add(at, one, two, 0.113)
+        add(at, None, two, 0.0)
+    check(kc, host, dt, "few NaNs")
+
+
 @pytest.mark.parametrize("dt", [d for d in FLOATS if W.ELEM_SIZE[d] < 8])
 def test_nan_filled_time(kc, dt):
     """A pass over NaNs is no longer than over elements that all differ."""
