@@ -72,8 +72,18 @@ __global__ void k_region_init(kc_region_diff_result* res, uint32_t n, uint64_t* 
 }
 
 __device__ __forceinline__ uint32_t nonzero_bytes(uint32_t x) {
-  return (uint32_t)((x & 0xFFu) != 0u) + (uint32_t)((x & 0xFF00u) != 0u) + (uint32_t)((x & 0xFF0000u) != 0u) +
-         (uint32_t)((x & 0xFF000000u) != 0u);
+  return (uint32_t)__popc((((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x) & 0x80808080u);
+}
+
+__device__ __forceinline__ uint64_t read_lane64(uint64_t x, uint32_t lane) {
+  return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)(x >> 32), lane) << 32) |
+         (uint32_t)__builtin_amdgcn_readlane((uint32_t)x, lane);
+}
+
+__device__ __forceinline__ uint64_t wave_min_u64(uint64_t x) {
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) x = min(x, (uint64_t)__shfl_xor((unsigned long long)x, d, 64));
+  return x;
 }
 
 __device__ __forceinline__ void flush_region(kc_region_diff_result* res, int32_t a, uint64_t dbytes, uint64_t dpages,
@@ -147,19 +157,22 @@ struct DiffFold {
 
 // Pages.  A wave takes groups of four consecutive tiles, one lane per page: each
 // lane resolves its page's snapshot copy and changed bit, then the whole wave
-// compares the changed pages one after another, 8 KiB in flight, and adds up what
-// differs in registers.  Runs of groups are contiguous and folded per range, which
-// touches a range's counters only when the run moves to the next range or ends (for
-// the waves of a workgroup together, where they end in one range): folds that all
-// add into one range's counters as they go queue on those addresses.
+// compares the changed pages one after another, 8 KiB in flight, and each lane adds
+// up what differs in its part of them; the lanes are summed up where the wave leaves
+// a range (done for every page, that chain of shuffles took as long as the loads:
+// half of 32 MiB changed 65 us, so 42).  Runs of groups are contiguous and folded
+// per range, which touches a range's counters only when the run moves to the next
+// range or ends (for the waves of a workgroup together, where they end in one
+// range): folds that all add into one range's counters as they go queue there.
 //
 // What bounds it: the bytes of the changed pages, and with few of them a chain of
 // three round trips per group; hence few registers and as many waves as are
 // resident (20 per CU with these; the built-in grid of 16 suits dense changes
-// better).  30 GiB with 1 % / 0.1 % of the pages changed: 148 / 71 us, at 20 waves
-// per CU 134 / 64; two pages at a time with their sums in LDS, as the larger units
-// below: 203 / 90.  One wave per workgroup: 4.2 GiB in one range, 1 % changed, 146
-// us, four 54; 2 GiB in 4096 ranges, half changed, 365 and 340, eight 377.
+// better).  30 GiB with 1 % / 0.1 % of the pages changed: 133 / 71 us, at 20 waves
+// per CU 120 / 63; two pages at a time with their sums in LDS, as the larger units
+// below: 206 / 90.  2 GiB in 4096 ranges, half changed, 325 us, at 20 waves per CU
+// 350.  With one wave per workgroup (and sums for every page) 4.2 GiB in one range,
+// 1 % changed, took 146 us, with four 54, now 53.
 constexpr uint32_t kDiffWaves = 16, kDiffPageWaves = 4;
 
 __global__ __launch_bounds__(kDiffPageWaves * kWave) __attribute__((amdgpu_waves_per_eu(5))) void k_region_diff_pages(
@@ -177,7 +190,20 @@ __global__ __launch_bounds__(kDiffPageWaves * kWave) __attribute__((amdgpu_waves
   const uint32_t n_groups = (n_tiles + 3u) / 4u, n_runs = gridDim.x * wpb;
   const uint32_t per_run = (n_groups + n_runs - 1u) / n_runs;
   const uint32_t gbeg = min((blockIdx.x * wpb + wv) * per_run, n_groups), gend = min(gbeg + per_run, n_groups);
-  DiffFold fold;
+  // the range that the wave is in; what differs there: of this lane, pages of the wave, first of this lane
+  int32_t cur = -1;
+  uint64_t bytes = 0, pages = 0, first = ~0ull;
+  auto add_up = [&] {
+    if (cur < 0) return;
+    bytes = wave_sum_u64(bytes);
+    first = wave_min_u64(first);
+  };
+  auto end_region = [&] {
+    add_up();
+    if (lane == 0) flush_region(res, cur, bytes, pages, first);
+    bytes = pages = 0;
+    first = ~0ull;
+  };
   for (uint32_t gi = gbeg; gi < gend; ++gi) {
     Tile tile{0, 0, 0};
     if (gi * 4u + sub < n_tiles) tile = tiles[gi * 4u + sub];
@@ -189,24 +215,38 @@ __global__ __launch_bounds__(kDiffPageWaves * kWave) __attribute__((amdgpu_waves
       if (nb) atomicAdd((unsigned long long*)&res[u.a].n_bad_pages, (unsigned long long)nb);
     }
     for (uint64_t m = __ballot(u.need); m != 0ull; m &= m - 1ull) {
-      const int32_t L = __ffsll((long long)m) - 1;
-      const uint64_t pva = __shfl((unsigned long long)u.va, L, 64), pgp = __shfl((unsigned long long)u.gp, L, 64);
-      const bool pz = __shfl((int)u.zero, L, 64) != 0;
-      const uint32_t plen = __shfl(u.len, L, 64);  // of a range's last page perhaps less than a page
-      uint32_t nd = 0u, fo = ~0u;
+      const uint32_t L = (uint32_t)__builtin_ctzll(m);
+      const uint64_t pva = read_lane64(u.va, L), pgp = read_lane64(u.gp, L);
+      const bool pz = __builtin_amdgcn_readlane((int)u.zero, L) != 0;
+      const uint32_t plen = __builtin_amdgcn_readlane(u.len, L);  // of a range's last page perhaps less than a page
+      uint4 x[4];
+      uint32_t nd = 0u;
 #pragma unroll
       for (uint32_t k = 0; k < 4; ++k) {
         const uint32_t off = k * 1024u + lane * 16u;
         const uint4 c = off < plen ? clip16(ld16nt(pva + off), off, plen) : make_uint4(0, 0, 0, 0);
         const uint4 d = pz || off >= plen ? make_uint4(0, 0, 0, 0) : clip16(ld16nt(pgp + off), off, plen);
-        add_diff(c, d, off, nd, fo);
+        x[k] = make_uint4(c.x ^ d.x, c.y ^ d.y, c.z ^ d.z, c.w ^ d.w);
+        nd += nonzero_bytes(x[k].x) + nonzero_bytes(x[k].y) + nonzero_bytes(x[k].z) + nonzero_bytes(x[k].w);
       }
-      nd = wave_sum_u32(nd);
+      if (__ballot(nd != 0u) == 0ull) continue;
+      const int32_t a = __builtin_amdgcn_readlane(u.a, L);
+      if (a != cur) {
+        end_region();
+        cur = a;
+      }
+      bytes += nd;
+      ++pages;
+      if (nd != 0u && first == ~0ull) {  // the pages of a range come in address order
+        uint32_t fo = ~0u, none = 0u;
 #pragma unroll
-      for (int dd = 32; dd >= 1; dd >>= 1) fo = min(fo, (uint32_t)__shfl_xor(fo, dd, 64));
-      if (nd) fold.add(res, lane == 0, __shfl(u.a, L, 64), nd, 1u, pva + fo);
+        for (uint32_t k = 0; k < 4; ++k) add_diff(x[k], make_uint4(0, 0, 0, 0), k * 1024u + lane * 16u, none, fo);
+        first = pva + fo;
+      }
     }
   }
+  add_up();
+  DiffFold fold{cur, bytes, pages, first};
   if (wpb == 1u) {
     if (lane == 0) flush_region(res, fold.cur, fold.bytes, fold.pages, fold.first);
     return;
