@@ -809,12 +809,12 @@ bool compare_wide(const kc_ctx* c, uint64_t n_pairs, uint64_t n_tiles, uint32_t 
   return n_pairs == n_tiles && n_tiles <= c->n_cu && tile_bytes >= kCompareWideTile;
 }
 
-CmpWalk compare_walk(const kc_ctx* c, uint64_t n_pairs, uint64_t n_tiles, uint32_t tile_bytes) {
+CmpWalk compare_walk(const kc_ctx* c, uint64_t n_pairs, uint64_t n_tiles, uint32_t tile_bytes, uint32_t copies) {
   const uint64_t bytes = n_tiles * tile_bytes, per_cu = bytes / std::max(1u, c->n_cu);
   const uint32_t per = per_cu < kCompareFewBytes ? kCompareGridPerCu / 2u : kCompareGridPerCu;
   const uint32_t even = (uint32_t)std::min<uint64_t>(grid_for(c, KC_OP_COMPARE, per), n_tiles);
   const uint64_t run_bytes = bytes > kCompareLongBytes ? 2u * kCompareRunBytes : kCompareRunBytes;
-  if (bytes <= run_bytes * even) return CmpWalk{even, 0u, 0u};  // tuned grids too, unless their runs are longer
+  if (bytes <= run_bytes * even) return CmpWalk{even, 0u, 0u, copies};  // tuned grids too, unless their runs are longer
   uint32_t run = 1, phases = 0;  // tiles of a whole run; halvings of it down to one tile
   while (run * 2ull * tile_bytes <= run_bytes) {
     run *= 2u;
@@ -822,9 +822,9 @@ CmpWalk compare_walk(const kc_ctx* c, uint64_t n_pairs, uint64_t n_tiles, uint32
   }
   const uint64_t taper = (run - 1ull) << kTaperShift;  // tiles of the shrinking runs
   if (n_pairs < kTaperPairs || n_tiles < 2u * taper)
-    return CmpWalk{(uint32_t)((n_tiles + run - 1u) / run), run, 0xFFFFFFFFu};
+    return CmpWalk{(uint32_t)((n_tiles + run - 1u) / run), run, 0xFFFFFFFFu, copies};
   const uint64_t whole = (n_tiles - taper) / run, rest = n_tiles - taper - whole * run;  // rest: one tile each at the end
-  return CmpWalk{(uint32_t)(whole + ((uint64_t)phases << kTaperShift) + rest), run, (uint32_t)whole};
+  return CmpWalk{(uint32_t)(whole + ((uint64_t)phases << kTaperShift) + rest), run, (uint32_t)whole, copies};
 }
 
 }  // namespace kc
@@ -883,9 +883,9 @@ void fill_pair_tables(const kc_pair* pairs, uint32_t n_pairs, const std::vector<
 // the next call clears the whole accumulator area first (fill kernel, so the
 // call stays capturable).
 int run_compare(kc_ctx* c, const CmpPairDev* dpairs, const CmpTileDev* dtiles, const std::vector<uint64_t>& tile_off,
-                uint32_t n_pairs, uint32_t tile_bytes, unsigned long long* dacc, uint64_t acc_words, bool* acc_dirty,
-                kc_cmp_result* res_d, hipStream_t s) {
-  const CmpWalk walk = compare_walk(c, n_pairs, tile_off[n_pairs], tile_bytes);
+                uint32_t n_pairs, uint32_t tile_bytes, unsigned long long* dacc, uint32_t copies, uint64_t acc_words,
+                bool* acc_dirty, kc_cmp_result* res_d, hipStream_t s) {
+  const CmpWalk walk = compare_walk(c, n_pairs, tile_off[n_pairs], tile_bytes, copies);
   const bool direct = tile_off[n_pairs] == n_pairs;  // every pair one tile
   if (*acc_dirty) KC_HIP(launch_fill_u64(reinterpret_cast<uint64_t*>(dacc), acc_words, 0, s));
   *acc_dirty = true;
@@ -897,12 +897,12 @@ int run_compare(kc_ctx* c, const CmpPairDev* dpairs, const CmpTileDev* dtiles, c
     } else {
       for (uint32_t i = 0; i < n_pairs; ++i) {
         const uint32_t n = (uint32_t)(tile_off[i + 1] - tile_off[i]);
-        KC_HIP(launch_compare(dpairs, dtiles + tile_off[i], n, tile_bytes, dacc, res_d, compare_walk(c, 1, n, tile_bytes),
-                              false, direct, s));
+        KC_HIP(launch_compare(dpairs, dtiles + tile_off[i], n, tile_bytes, dacc, res_d,
+                              compare_walk(c, 1, n, tile_bytes, copies), false, direct, s));
       }
     }
   }
-  if (!direct) KC_HIP(launch_compare_finalize(dpairs, n_pairs, dacc, res_d, s));
+  if (!direct) KC_HIP(launch_compare_finalize(dpairs, n_pairs, dacc, copies, res_d, s));
   *acc_dirty = false;
   return KC_OK;
 }
@@ -921,7 +921,8 @@ int kc_compare(kc_ctx* c, const kc_pair* pairs, uint32_t n_pairs, kc_cmp_result*
   const uint64_t n_tiles = tile_off[n_pairs];
   const size_t sz_pairs = align_up(sizeof(CmpPairDev) * n_pairs, 256);
   const size_t sz_tiles = align_up(sizeof(CmpTileDev) * n_tiles, 256);
-  const size_t sz_acc = (size_t)n_pairs * kAccWords * 8;
+  const uint32_t copies = acc_copies(n_pairs, n_tiles * tile_bytes);
+  const size_t sz_acc = (size_t)n_pairs * copies * kAccWords * 8;
   const size_t need_dev = sz_pairs + sz_tiles, need_host = sz_pairs + sz_tiles;
   DeviceGuard g(c->device);
   if (!g.ok) return KC_EHIP;
@@ -978,8 +979,8 @@ int kc_compare(kc_ctx* c, const kc_pair* pairs, uint32_t n_pairs, kc_cmp_result*
   KC_HIP(hipMemcpyAsync(c->cmp_dev, c->cmp_host, need_host, hipMemcpyHostToDevice, s));
   KC_HIP(hipEventRecord(c->staged, s));
   c->staged_pending = true;
-  return run_compare(c, dpairs, dtiles, tile_off, n_pairs, tile_bytes, dacc, c->cmp_acc_cap / 8, &c->cmp_acc_dirty,
-                     res_d, s);
+  return run_compare(c, dpairs, dtiles, tile_off, n_pairs, tile_bytes, dacc, copies, c->cmp_acc_cap / 8,
+                     &c->cmp_acc_dirty, res_d, s);
 }
 
 int kc_pairset_create(kc_ctx* c, const kc_pair* pairs, uint32_t n_pairs, kc_pairset** out) {
@@ -1001,7 +1002,8 @@ int kc_pairset_create(kc_ctx* c, const kc_pair* pairs, uint32_t n_pairs, kc_pair
   ps->tile_off = std::move(tile_off);
   const size_t sz_pairs = align_up(sizeof(CmpPairDev) * std::max<uint32_t>(1, n_pairs), 256);
   const size_t sz_tiles = align_up(sizeof(CmpTileDev) * std::max<uint64_t>(1, ps->n_tiles), 256);
-  const size_t sz_acc = (size_t)std::max<uint32_t>(1, n_pairs) * kAccWords * 8;
+  ps->copies = acc_copies(n_pairs, ps->n_tiles * tile_bytes);
+  const size_t sz_acc = (size_t)std::max<uint32_t>(1, n_pairs) * ps->copies * kAccWords * 8;
   hipError_t e = hipMalloc(&ps->dev, sz_pairs + sz_tiles + sz_acc);
   if (e != hipSuccess) {
     set_error("hipMalloc(pairset)", e);
@@ -1038,8 +1040,8 @@ int kc_compare_pairset(kc_ctx* c, const kc_pairset* ps, kc_cmp_result* res_d, vo
   if (ps->n_pairs == 0) return KC_OK;
   DeviceGuard g(c->device);
   if (!g.ok) return KC_EHIP;
-  return run_compare(c, ps->pairs, ps->tiles, ps->tile_off, ps->n_pairs, ps->tile_bytes, ps->acc,
-                     (uint64_t)ps->n_pairs * kAccWords, &ps->acc_dirty, res_d, as_stream(stream));
+  return run_compare(c, ps->pairs, ps->tiles, ps->tile_off, ps->n_pairs, ps->tile_bytes, ps->acc, ps->copies,
+                     (uint64_t)ps->n_pairs * ps->copies * kAccWords, &ps->acc_dirty, res_d, as_stream(stream));
 }
 
 }  // extern "C"

@@ -753,6 +753,12 @@ __device__ __forceinline__ void my_tiles(const CmpWalk& w, uint32_t n, uint32_t&
   }
 }
 
+// The accumulators of a pair that this workgroup adds to.
+__device__ __forceinline__ unsigned long long* my_acc(unsigned long long* acc_all, uint32_t pair, const CmpWalk& w) {
+  return acc_all + ((uint64_t)pair * w.copies + (blockIdx.x & (w.copies - 1u))) * kAccWords;
+}
+
+static_assert((kAccCopies & (kAccCopies - 1u)) == 0u, "a power of two");
 static_assert(kAccNanCand == kAccNanBoth + 1 && kAccNanGold == kAccNanBoth + 2, "order of the NaN classes");
 
 // T threads per workgroup: kThreads, or kWideThreads when the tiles are no more
@@ -774,8 +780,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) void k_c
     const CmpTileDev tl = const_load(tiles + t);
     const CmpPairDev pr = const_load(pairs + tl.pair);
     const uint32_t n = min(end - t, pr.n_tiles - tl.idx);
-    compare_tiles<T, DIRECT>(pr, tl.idx, n, tile_bytes, acc_all + (uint64_t)tl.pair * kAccWords, res + tl.pair, lds, stage,
-                             turn);
+    compare_tiles<T, DIRECT>(pr, tl.idx, n, tile_bytes, my_acc(acc_all, tl.pair, walk), res + tl.pair, lds, stage, turn);
     t += n;
   }
 }
@@ -799,37 +804,42 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) void k_c
       if (a.tile_end[mid] > t) hi = mid; else lo = mid + 1u;
     }
     const uint32_t start = lo == 0u ? 0u : a.tile_end[lo - 1u], n = min(end, a.tile_end[lo]) - t;
-    compare_tiles<T, DIRECT>(a.pair[lo], t - start, n, tile_bytes, acc_all + (uint64_t)lo * kAccWords, res + lo, lds,
-                             stage, turn);
+    compare_tiles<T, DIRECT>(a.pair[lo], t - start, n, tile_bytes, my_acc(acc_all, lo, walk), res + lo, lds, stage, turn);
     t += n;
   }
 }
 
-// One wave per pair turns its accumulators into the report and zeroes them for
-// the next call.
-__device__ __forceinline__ void finalize_pair(uint64_t n_elems, uint32_t dtype, unsigned long long* acc,
-                                              kc_cmp_result* r) {
+// One wave per pair turns its accumulators (all copies of them) into the report
+// and zeroes them for the next call.
+__device__ __forceinline__ void finalize_pair(uint64_t n_elems, uint32_t dtype, unsigned long long* acc_all,
+                                              uint64_t pair, uint32_t copies, kc_cmp_result* r) {
   const uint32_t lane = threadIdx.x % kWave;
   const int i = acc_of_word(lane);
-  const uint64_t x = i >= 0 ? acc[i] : 0ull;
+  unsigned long long* const acc = acc_all + pair * copies * kAccWords;
+  uint64_t x = 0ull;
+  for (uint32_t c = 0; c < copies; ++c) {
+    const uint64_t y = i >= 0 ? acc[c * kAccWords + (uint32_t)i] : 0ull;
+    x = i >= (int)kAccMaxAbs && i <= (int)kAccFirstInv ? max(x, y) : x + y;
+  }
   write_report(n_elems, dtype, x, r);
   asm volatile("" ::: "memory");  // the lanes clear words that other lanes have read above
-  acc[lane] = 0ull;
+  for (uint32_t c = 0; c < copies; ++c) acc[c * kAccWords + lane] = 0ull;
 }
 static_assert(kAccWords == kWave, "one accumulator word per lane");
 
 __global__ __launch_bounds__(256) void k_compare_finalize(const CmpPairDev* pairs, uint32_t n_pairs,
-                                                          unsigned long long* acc_all, kc_cmp_result* res) {
+                                                          unsigned long long* acc_all, uint32_t copies,
+                                                          kc_cmp_result* res) {
   const uint32_t i = __builtin_amdgcn_readfirstlane(blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave);
   if (i >= n_pairs) return;
   const CmpPairDev pr = const_load(pairs + i);
-  finalize_pair(pr.n_elems, pr.dtype, acc_all + (uint64_t)i * kAccWords, res + i);
+  finalize_pair(pr.n_elems, pr.dtype, acc_all, i, copies, res + i);
 }
 
 __global__ __launch_bounds__(64) void k_compare_args_finalize(CmpArgPairs a, unsigned long long* acc_all,
-                                                              kc_cmp_result* res) {
+                                                              uint32_t copies, kc_cmp_result* res) {
   const uint32_t i = blockIdx.x;
-  finalize_pair(a.pair[i].n_elems, a.pair[i].dtype, acc_all + (uint64_t)i * kAccWords, res + i);
+  finalize_pair(a.pair[i].n_elems, a.pair[i].dtype, acc_all, i, copies, res + i);
 }
 
 }  // namespace
@@ -853,10 +863,10 @@ hipError_t launch_compare(const CmpPairDev* pairs, const CmpTileDev* tiles, uint
   return hipGetLastError();
 }
 
-hipError_t launch_compare_finalize(const CmpPairDev* pairs, uint32_t n_pairs, unsigned long long* acc,
+hipError_t launch_compare_finalize(const CmpPairDev* pairs, uint32_t n_pairs, unsigned long long* acc, uint32_t copies,
                                    kc_cmp_result* res, hipStream_t s) {
   if (n_pairs == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_compare_finalize, dim3((n_pairs + 3) / 4), dim3(256), 0, s, pairs, n_pairs, acc, res);
+  hipLaunchKernelGGL(k_compare_finalize, dim3((n_pairs + 3) / 4), dim3(256), 0, s, pairs, n_pairs, acc, copies, res);
   return hipGetLastError();
 }
 
@@ -867,7 +877,7 @@ hipError_t launch_compare_args(const CmpArgPairs& a, uint32_t tile_bytes, unsign
   KC_COMPARE_LAUNCH(k_compare_args, a, tile_bytes, acc, res, walk)
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || direct) return e;
-  hipLaunchKernelGGL(k_compare_args_finalize, dim3(a.n), dim3(64), 0, s, a, acc, res);
+  hipLaunchKernelGGL(k_compare_args_finalize, dim3(a.n), dim3(64), 0, s, a, acc, walk.copies, res);
   return hipGetLastError();
 }
 #undef KC_COMPARE_LAUNCH

@@ -247,10 +247,10 @@ constexpr uint64_t kCompareFewBytes = 1u << 20;
 // equal 2.49; 200 pairs of 150 MiB, the last all off as fp8: 17.1 ms, so 9.2, all
 // equal 8.8).  Shorter runs cost nothing while pairs are many (those 10,000 of 8 GiB
 // a side, runs of 4 / 1 / 0.5 / 0.25 MiB: equal 2.58 / 2.57 / 2.55 / 2.54 ms, 11.3 %
-// off 2.79 / 2.66 / 2.63 / 2.61), but about 0.1 us each at one pair's accumulators
-// when elements differ (one pair of 1 GiB, 1e-4 off, runs of 0.5 / 0.25 / 0.13 MiB:
-// 350 / 413 / 781 us; 200 pairs of 150 MiB, runs of 1.8 / 0.9 / 0.5 MiB: 9.33 / 9.37 /
-// 9.49 ms).
+// off 2.79 / 2.66 / 2.63 / 2.61), but with one copy of the accumulators (kAccCopies)
+// about 0.1 us each there when elements differ (one pair of 1 GiB, 1e-4 off, runs of
+// 0.5 / 0.25 / 0.13 MiB: 350 / 413 / 781 us; 200 pairs of 150 MiB, runs of 1.8 / 0.9 /
+// 0.5 MiB: 9.33 / 9.37 / 9.49 ms).
 constexpr uint64_t kCompareRunBytes = 512u << 10;      // 1 MiB beyond kCompareLongBytes
 constexpr uint64_t kCompareLongBytes = 16ull << 30;    // of a side
 // Of lists of at least kTaperPairs pairs the end is cut finer: after the whole runs
@@ -263,6 +263,7 @@ constexpr uint32_t kTaperShift = 9, kTaperRuns = 1u << kTaperShift, kTaperPairs 
 // power of two) each, the others shrinking runs; run 0: all tiles shared out evenly.
 struct CmpWalk {
   uint32_t grid, run, whole;
+  uint32_t copies = 1;  // of each pair's accumulators (kAccCopies or one); workgroup b adds to copy b mod copies
 };
 
 // Tile of a small compare: when the pairs are no more than the CUs and none is
@@ -272,6 +273,18 @@ struct CmpWalk {
 // of such pairs differ one CU has the work of four: as f32 17.7 us, as fp8 47.8,
 // where a tile of 16 KiB per workgroup and a second kernel took 16.4 and 32.7.
 constexpr uint32_t kCompareWideTile = 64u << 10;
+
+// Large lists of few pairs keep kAccCopies copies of each pair's accumulators, one
+// per XCD (workgroups go to the XCDs in turn), which the reports combine: adds from
+// all XCDs to one copy cost about 0.1 us each and keep the loads of others waiting.
+// bf16 with 1e-4 off, runs as above, one copy / eight: one pair of 8 GiB 2.91 / 2.64
+// ms (runs of 4 MiB, one copy, 2.61), four of 4 GiB 5.72 / 5.13 (5.19), 40 of 4 GiB in
+// all, one of them 2.5, 1.39 / 1.27 (1.36); the same when all is equal.  Not below the
+// lengths where runs are short, where a run ends with a few thousand adds in all; nor
+// with more pairs, which meet less and would have the reports read 4 KiB each.
+constexpr uint32_t kAccCopies = 8;
+constexpr uint32_t kAccCopyPairs = 512;
+constexpr uint64_t kAccCopyBytes = 1ull << 30;  // of a side
 
 constexpr uint32_t kAccWords = 64;  // per-pair accumulator words
 // accumulator word map
@@ -322,10 +335,10 @@ hipError_t launch_oob_emit(const Tile* tiles, uint32_t n_tiles, const ScanDev& s
 hipError_t launch_compare(const CmpPairDev* pairs, const CmpTileDev* tiles, uint32_t n_tiles, uint32_t tile_bytes,
                           unsigned long long* acc, kc_cmp_result* res, CmpWalk walk, bool wide, bool direct,
                           hipStream_t s);
-hipError_t launch_compare_finalize(const CmpPairDev* pairs, uint32_t n_pairs, unsigned long long* acc,
+hipError_t launch_compare_finalize(const CmpPairDev* pairs, uint32_t n_pairs, unsigned long long* acc, uint32_t copies,
                                    kc_cmp_result* res, hipStream_t s);
-// The pass and the reports of the pairs in `a` (accumulators acc[pair * kAccWords ...], zero on entry and
-// zeroed again; reports res[0 .. a.n)).
+// The pass and the reports of the pairs in `a` (accumulators acc[pair * walk.copies * kAccWords ...], zero on entry
+// and zeroed again; reports res[0 .. a.n)).
 hipError_t launch_compare_args(const CmpArgPairs& a, uint32_t tile_bytes, unsigned long long* acc,
                                kc_cmp_result* res, CmpWalk walk, bool wide, hipStream_t s);
 
@@ -334,7 +347,11 @@ uint32_t grid_for(const kc_ctx* c, uint32_t op, uint32_t fallback_per_cu);  // p
 uint32_t elem_size(uint32_t dtype);                                         // bytes of one element
 uint32_t compare_tile_bytes(const kc_ctx* c, const kc_pair* pairs, uint32_t n_pairs);
 bool compare_wide(const kc_ctx* c, uint64_t n_pairs, uint64_t n_tiles, uint32_t tile_bytes);  // 1024-thread workgroups
-CmpWalk compare_walk(const kc_ctx* c, uint64_t n_pairs, uint64_t n_tiles, uint32_t tile_bytes);
+CmpWalk compare_walk(const kc_ctx* c, uint64_t n_pairs, uint64_t n_tiles, uint32_t tile_bytes, uint32_t copies);
+// Copies of each pair's accumulators, for a list of `bytes` a side in whole tiles.
+inline uint32_t acc_copies(uint64_t n_pairs, uint64_t bytes) {
+  return n_pairs <= kAccCopyPairs && bytes > kAccCopyBytes ? kAccCopies : 1u;
+}
 
 // ---- the compare that allocates nothing (kc_noalloc.hip) ---------------------
 // Looks up, once per device, the device address of the static scratch array
@@ -438,6 +455,7 @@ struct kc_pairset {
   kc::CmpPairDev* pairs = nullptr;
   kc::CmpTileDev* tiles = nullptr;
   unsigned long long* acc = nullptr;
+  uint32_t copies = 1;             // of each pair's accumulators
   mutable bool acc_dirty = false;  // a failed compare left accumulators set
 };
 

@@ -60,7 +60,7 @@ int kc_compare_noalloc(kc_ctx* c, const kc_pair* pairs, uint32_t n_pairs, kc_cmp
   }
   const uint32_t tile_bytes = compare_tile_bytes(c, pairs, n_pairs);
   // the checks of kc_compare, pair by pair, before anything is launched
-  uint64_t chunk_tiles = 0;
+  uint64_t chunk_tiles = 0, all_tiles = 0;
   for (uint32_t i = 0; i < n_pairs; ++i) {
     const kc_pair& pr = pairs[i];
     if (pr.dtype > KC_I64) return KC_EDTYPE;
@@ -74,7 +74,9 @@ int kc_compare_noalloc(kc_ctx* c, const kc_pair* pairs, uint32_t n_pairs, kc_cmp
     }
     if (i % kArgPairs == 0) chunk_tiles = 0;
     const uint64_t nb = pr.n_elems * elem_size(pr.dtype);
-    chunk_tiles += nb == 0 ? 1 : (nb + tile_bytes - 1) / tile_bytes;
+    const uint64_t nt = nb == 0 ? 1 : (nb + tile_bytes - 1) / tile_bytes;
+    chunk_tiles += nt;
+    all_tiles += nt;
     if (chunk_tiles > 0xFFFFFFFFull) return KC_ELIMIT;
   }
   DeviceGuard g(c->device);
@@ -89,7 +91,9 @@ int kc_compare_noalloc(kc_ctx* c, const kc_pair* pairs, uint32_t n_pairs, kc_cmp
   // whose pairs are all one tile uses none
   bool multi = false;
   for (uint32_t i = 0; i < n_pairs && !multi; ++i) multi = pairs[i].n_elems * elem_size(pairs[i].dtype) > tile_bytes;
-  if (multi) KC_HIP(launch_fill_u64(reinterpret_cast<uint64_t*>(acc), (uint64_t)n_pairs * kAccWords, 0, s));
+  static_assert(kAccCopyPairs * kAccCopies <= KC_NOALLOC_MAX_PAIRS, "the copies fit the static scratch");
+  const uint32_t copies = acc_copies(n_pairs, all_tiles * tile_bytes);
+  if (multi) KC_HIP(launch_fill_u64(reinterpret_cast<uint64_t*>(acc), (uint64_t)n_pairs * copies * kAccWords, 0, s));
   for (uint32_t b0 = 0; b0 < n_pairs; b0 += kArgPairs) {
     CmpArgPairs a{};
     a.n = std::min(kArgPairs, n_pairs - b0);
@@ -112,8 +116,8 @@ int kc_compare_noalloc(kc_ctx* c, const kc_pair* pairs, uint32_t n_pairs, kc_cmp
       a.tile_end[j] = (uint32_t)t;
     }
     a.n_tiles = (uint32_t)t;
-    const CmpWalk walk = compare_walk(c, a.n, t, tile_bytes);
-    KC_HIP(launch_compare_args(a, tile_bytes, acc + (uint64_t)b0 * kAccWords, res_d + b0, walk,
+    const CmpWalk walk = compare_walk(c, a.n, t, tile_bytes, copies);
+    KC_HIP(launch_compare_args(a, tile_bytes, acc + (uint64_t)b0 * copies * kAccWords, res_d + b0, walk,
                                compare_wide(c, a.n, t, tile_bytes), s));
   }
   return KC_OK;

@@ -97,3 +97,36 @@ def test_one_wrong_pair_time(kc, shape):
         assert us[wrong] < 1.4 * us[None], us
     ps.close()
     ctx.close()
+
+
+def test_copies_of_the_accumulators(kc):
+    """Lists on both sides of the lines from which pairs have several copies of
+    their accumulators, through one context and one resident list each, in turn
+    and again: every report equals that of its pair alone (a small list)."""
+    rng = np.random.default_rng(3)
+    total = (1 << 30) + (64 << 20)
+    gold = torch.randint(0, 120, (total,), dtype=torch.uint8, device="cuda")
+    cand = gold.clone()
+    at = torch.from_numpy(rng.integers(0, total, size=200000)).cuda()
+    cand[at] ^= 3
+    lists = []
+    for n, size in ((2, total), (1, 1 << 30), (40, total), (512, total), (513, total)):
+        cuts = np.sort(rng.choice(np.arange(1, size // 4096), size=n - 1, replace=False)) * 4096
+        first = np.concatenate([[0], cuts, [size]])
+        lists.append([(cand[a:b], gold[a:b], (W.DT_FP8, W.DT_F32, W.DT_F16, W.DT_U8, W.DT_I64)[i % 5], 2, 1e-3, 1e-2)
+                      for i, (a, b) in enumerate(zip(first[:-1].tolist(), first[1:].tolist()))])
+    ctx = kc.Context(0)
+    expect = []
+    for pairs in lists:
+        say(f"compare copies: {len(pairs)} pairs alone")
+        expect.append([kc.decode_cmp(kc.compare(ctx, [p]), 1)[0] for p in pairs])
+    resident = [kc.PairSet(ctx, pairs) for pairs in lists]
+    for again in range(2):
+        for pairs, ps, want in zip(lists, resident, expect):
+            say(f"compare copies: {len(pairs)} pairs, time {again}")
+            res = torch.zeros(len(pairs) * kc.RESULT_BYTES, dtype=torch.uint8, device="cuda")
+            for got in (kc.compare(ctx, pairs), kc.compare_pairset(ctx, ps), kc.compare_noalloc(ctx, pairs, res)):
+                assert kc.decode_cmp(got, len(pairs)) == want
+    for ps in resident:
+        ps.close()
+    ctx.close()
