@@ -49,10 +49,10 @@ PAGE = 4096
 # device copy gives (fetch x2.0, write x1.0).  Valid only for the kernel
 # sources they were taken from.
 PMC_TRAFFIC = {
-    "source_sha256": "a28f7370783f7f8730eeaafc6101eda6b46dbcf48c1aaa44dd8aefa50dc12253",
-    "snapshot": 62930404242,   # fetch 31401073737 + write 31529330505
-    "restore": 63687250201,   # fetch 32333206195 + write 31354044006
-    "compare": 64441212518,   # fetch 64441212518 + write 0
+    "source_sha256": "24b3a7ea7418157ad918712dae2eb402a279b8169565bc1e1c5b6573fd475de4",
+    "snapshot": 62927393673,   # fetch 31401071378 + write 31526322295
+    "restore": 63687451930,   # fetch 32333206144 + write 31354245786
+    "compare": 64441360794,   # fetch 64441360794 + write 0
 }
 
 
